@@ -1913,11 +1913,10 @@ int conv4d_backward(dfl_ctx* c, const float* in, int cin, const float* W, int co
         fail(DFL_EINVAL, "channels: 1 <= cin <= 96, 1 <= cout <= 576");
     if (din && (din == g || din == in))
         fail(DFL_EINVAL, "din must not overlap g or in");
-    long chunk = 0;
-    int nchunk = 0;
-    const size_t need = conv_wgrad_chunk_floats(c->g, cin, cout, &chunk, &nchunk);
-    c->net_part = grow<float>(c, c->net_part, c->net_part_n, need);
-    launch_conv_backward(c->g, in, cin, W, cout, g, dW, db, din, z_in, c->net_part, chunk, nchunk, c->stream);
+    WgradPlan plan;
+    conv_wgrad_plan(c->g, cin, cout, ~size_t(0) / 16, &plan);
+    c->net_part = grow<float>(c, c->net_part, c->net_part_n, plan.floats);
+    launch_conv_backward(c->g, in, cin, W, cout, g, dW, db, din, z_in, c->net_part, plan, c->stream);
     HIPCHECK(hipGetLastError());
     API_END
 }
@@ -1936,13 +1935,12 @@ int conv4d_backward_noalloc(dfl_ctx* c, const float* in, int cin, const float* W
         fail(DFL_EINVAL, "channels: 1 <= cin <= 96, 1 <= cout <= 576");
     if (din && (din == g || din == in))
         fail(DFL_EINVAL, "din must not overlap g or in");
-    long chunk = 0;
-    int nchunk = 0;
-    if (!conv_wgrad_chunk_fit(c->g, cin, cout, kNoAllocFloats, &chunk, &nchunk))
+    WgradPlan plan;
+    if (!conv_wgrad_plan(c->g, cin, cout, kNoAllocFloats, &plan))
         fail(DFL_EINVAL, "conv4d_backward_noalloc: one chunk of the weight-gradient partial sums (81 cin cout "
                          "floats) exceeds the 64 MiB scratch");
     float* part = noalloc_scratch();
-    launch_conv_backward(c->g, in, cin, W, cout, g, dW, db, din, z_in, part, chunk, nchunk, c->stream);
+    launch_conv_backward(c->g, in, cin, W, cout, g, dW, db, din, z_in, part, plan, c->stream);
     HIPCHECK(hipGetLastError());
     API_END
 }

@@ -361,7 +361,16 @@ void launch_little_copies(const c64* A, c32* A32, c64* At64, c32* At32, long nbl
 void launch_net_features(const Geom& g, const c64* U64, const float* noise, float* x, hipStream_t s);
 void launch_conv_forward(const Geom& g, const float* in, int cin, const float* W, const float* b, int cout, float* z,
                          float* a, hipStream_t s);
-size_t conv_wgrad_chunk_floats(const Geom& g, int cin, int cout, long* chunk, int* nchunk);
+// Weight gradient: partial sums over nchunk ranges of `chunk` tiles (mfma) or
+// sites, nparts partials of 81 cin cout floats; false if not even one range's
+// partials fit `cap` floats.
+struct WgradPlan {
+    bool mfma, pair;
+    long chunk;
+    int nchunk, nparts;
+    size_t floats;
+};
+bool conv_wgrad_plan(const Geom& g, int cin, int cout, size_t cap, WgradPlan* p);
 // BF16-operand forward (FP32 sums) for lattices with L3 % 32 == 0 and L2 % 4 == 0
 // (conv_bf16_fits); Wb holds conv_bf16_weight_elems(cin, cout) BF16 entries
 bool conv_bf16_fits(const Geom& g);
@@ -369,7 +378,7 @@ size_t conv_bf16_weight_elems(int cin, int cout);
 void launch_conv_forward_bf16(const Geom& g, const float* in, int cin, const float* W, const float* b, int cout,
                               float* z, float* a, uint16_t* Wb, hipStream_t s);
 void launch_conv_backward(const Geom& g, const float* in, int cin, const float* W, int cout, const float* gr,
-                          float* dW, float* db, float* din, const float* zprev, float* part, long chunk, int nchunk,
+                          float* dW, float* db, float* din, const float* zprev, float* part, const WgradPlan& p,
                           hipStream_t s);
 void launch_out_to_fields(const Geom& g, const float* out, int Ns, c64* f, hipStream_t s);
 void launch_fields_to_out(const Geom& g, const c64* gr, int Ns, float* dout, hipStream_t s);
@@ -380,12 +389,10 @@ void launch_deficit_grad(const Geom& g, const c64* Psi, int Ns, const c64* T, in
 void launch_adam(float* th, const float* gr, float* m, float* v, long n, float lr, float b1, float b2, float eps,
                  float c1, float c2, hipStream_t s);
 // allocation-free weight gradient: floats of the device scratch array (64 MiB
-// per device), its device address on the current device, and a chunking of
-// the partial sums that fits cap floats (false if one chunk does not fit)
+// per device) and its device address on the current device
 constexpr size_t kNoAllocFloats = size_t(16) << 20;
 constexpr int kMaxDevices = 64;
 float* noalloc_scratch();
-bool conv_wgrad_chunk_fit(const Geom& g, int cin, int cout, size_t cap, long* chunk, int* nchunk);
 constexpr int kNetMaxCin = 96;     // input channels of a convolution (weight gradient bound)
 constexpr int kNetMaxCout = 576;   // output channels (input-gradient staging bound)
 constexpr int kLossMaxN = 32;      // fields and targets of the deficit loss

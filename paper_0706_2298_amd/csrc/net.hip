@@ -7,6 +7,7 @@
 // so a tap's neighbour is a fixed shift of the site index up to the periodic
 // wrap. Weights are [81][Cin][Cout], tap t = sum_mu (o_mu + 1) 3^(3 - mu) for
 // the offset o in {-1,0,1}^4. Quark fields are native FP64 fields (common.h).
+#include <algorithm>
 #include <mutex>
 
 #include "internal.h"
@@ -59,6 +60,8 @@ __device__ inline float silu_grad_f(float z)
     return s * (1.0f + z * (1.0f - s));
 }
 
+// The vector kernel, for lattices whose rows along x3 are too long for the
+// staged tiles of the matrix-core kernels (conv_lds_bytes):
 // out[oc][i] = bias[oc] + sum_t sum_ic Wt(t, ic, oc) in[ic][i + s*o_t]
 //   forward (TRANS = false, s = +1): Wt(t, ic, oc) = W[t][ic][oc], nic = Cin
 //   input gradient (TRANS = true, s = -1): Wt(t, ic, oc) = W[t][oc][ic], nic = Cout of W
@@ -131,107 +134,270 @@ __global__ __launch_bounds__(256) void k_conv(Lat lt, const float* __restrict__ 
     }
 }
 
-// The same map on the matrix cores (v_mfma_f32_16x16x4f32, FP32 products
-// and sums), as a GEMM per tap: out[oc][x] += sum_ic Wt(t, ic, oc) in[ic][x + s o_t].
-// Workgroup: 32 consecutive sites along x3 (L3 % 32 == 0) and 32 output
-// channels; wavefront w computes the 16 x 16 tile (channels (w / 2) * 16..,
-// sites (w % 2) * 16..). For each of the 27 neighbour lines (o0, o1, o2) and
-// each chunk of kMC input channels, the line segment with its +-1 halo along
-// x3 and the weights of the three taps o3 = -1, 0, 1 are staged in LDS; the
-// three taps then read the segment at shifts of one site. Operand layout of
-// the 16x16x4 instruction: lane l supplies A[l % 16][l / 16] and
-// B[l / 16][l % 16] and holds C[4 (l / 16) + i][l % 16], i < 4.
-// Measured on MI355X: 44-50 TFLOP/s per layer on 64 x 32^3, 15% faster than
-// k_conv; 16-site segments (for L3 = 16) ran three times slower than k_conv
-// and two channel tiles per wavefront did not help, so only this shape is
-// used and other lattices take k_conv.
-constexpr int kMC = 32;  // input channels per LDS chunk
-constexpr int kXS = 48;  // LDS row stride of the staged segment (34 used; 48 = 16 mod 32 banks)
-template <bool TRANS>
-__global__ __launch_bounds__(256) void k_conv_mfma(Lat lt, const float* __restrict__ in, int nic,
-                                                   const float* __restrict__ W, int w_cin, int w_cout,
-                                                   const float* __restrict__ bias, int noc, float* __restrict__ out,
-                                                   float* __restrict__ act, const float* __restrict__ zprev)
+// ------------------------------------------------------- staged site tiles
+//
+// The matrix-core convolutions work on tiles of T consecutive canonical sites.
+// For a pair of offsets (o0, o1) the tile's rows along x3, each with its two
+// neighbours along x3, and the rows x2 - 1 and x2 + 1 around every run of rows
+// of one (x0, x1) plane are staged in LDS ("slots" of L3 + 2 positions); all
+// nine taps (o2, o3) then read the same staged values at a constant shift of
+// o2 (L3 + 2) + o3 positions. Any lattice works: a tile may start inside a
+// row and cross planes.
+struct Tile {
+    long site0;   // first site
+    int n;        // sites (T, fewer at the end of the lattice)
+    int x2_0;     // x2 of the first row
+    int plane0;   // its plane x0 L1 + x1
+    int slots;    // staged rows
+};
+__device__ inline Tile make_tile(const Lat& lt, long tile, int T)
 {
-    constexpr int TS = 32;              // sites per workgroup
-    constexpr int OCT = 32;             // output channels per workgroup
-    constexpr int WS = OCT + 16;        // LDS row stride of the weights (16 mod 32 banks)
-    constexpr int NST = TS / 16;        // site tiles per workgroup
-    __shared__ float xs[kMC][kXS];
-    __shared__ float ws[3][kMC][WS];
+    Tile t;
+    t.site0 = tile * T;
+    t.n = (int)(lt.V - t.site0 < T ? lt.V - t.site0 : T);
+    const long r0 = t.site0 / lt.L[3], r1 = (t.site0 + t.n - 1) / lt.L[3];
+    t.plane0 = (int)(r0 / lt.L[2]);
+    t.x2_0 = (int)(r0 - (long)t.plane0 * lt.L[2]);
+    const int pl1 = (int)(r1 / lt.L[2]);
+    const int x2_1 = (int)(r1 - (long)pl1 * lt.L[2]);
+    t.slots = (pl1 - t.plane0) * (lt.L[2] + 2) + x2_1 - t.x2_0 + 3;
+    return t;
+}
+// staged position of site i of the tile
+__device__ inline int tile_pos(const Lat& lt, const Tile& t, int i)
+{
+    const long s = t.site0 + i;
+    const long r = s / lt.L[3];
+    const int x3 = (int)(s - r * lt.L[3]);
+    const int pl = (int)(r / lt.L[2]);
+    const int x2 = (int)(r - (long)pl * lt.L[2]);
+    return ((pl - t.plane0) * (lt.L[2] + 2) + x2 + 1 - t.x2_0) * (lt.L[3] + 2) + x3 + 1;
+}
+// a staged position's source: x0, x1 of its plane and the index in the plane
+struct Src {
+    int x0, x1, in_plane;
+};
+__device__ inline Src pos_source(const Lat& lt, const Tile& t, int p)
+{
+    const int w3 = lt.L[3] + 2, w2 = lt.L[2] + 2;
+    const int slot = p / w3;
+    int x3 = p - slot * w3 - 1;
+    x3 = x3 < 0 ? x3 + lt.L[3] : (x3 >= lt.L[3] ? x3 - lt.L[3] : x3);
+    const int u = slot + t.x2_0;
+    const int seg = u / w2;
+    int x2 = u - seg * w2 - 1;
+    x2 = x2 < 0 ? x2 + lt.L[2] : (x2 >= lt.L[2] ? x2 - lt.L[2] : x2);
+    const int pl = t.plane0 + seg;
+    Src r;
+    r.x0 = pl / lt.L[1];
+    r.x1 = pl - r.x0 * lt.L[1];
+    r.in_plane = x2 * lt.L[3] + x3;
+    return r;
+}
+// canonical index of the source in the plane (x0 + d0, x1 + d1)
+__device__ inline long src_site(const Lat& lt, const Src& r, int d0, int d1)
+{
+    int y0 = r.x0 + d0, y1 = r.x1 + d1;
+    y0 = y0 < 0 ? y0 + lt.L[0] : (y0 >= lt.L[0] ? y0 - lt.L[0] : y0);
+    y1 = y1 < 0 ? y1 + lt.L[1] : (y1 >= lt.L[1] ? y1 - lt.L[1] : y1);
+    return (long)y0 * lt.str[0] + (long)y1 * lt.str[1] + r.in_plane;
+}
+
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+// k_conv's map on the matrix cores (v_mfma_f32_32x32x2f32, FP32 products and
+// sums), one GEMM per tap: out[oc][x] += sum_ic Wt(t, ic, oc) in[ic][x + s o_t].
+// Workgroup: a tile of 128 sites and 32 OT output channels, wavefront w the
+// sites 32 w .. 32 w + 31 of all of them. For each (o0, o1) and each chunk of
+// 32 input channels the tile is staged as [position][channel], and the weights
+// of three taps at a time as [tap][output channel][channel], both with a row of
+// 36 floats: a lane's four consecutive channels are one 16-byte LDS read that
+// feeds four instructions, and eight neighbouring rows cover all banks. Of the
+// instruction's two contraction steps the lower lanes take the first and the
+// upper lanes the second four of eight channels, for both operands alike.
+// Lane l supplies A[l % 32][l / 32] and B[l / 32][l % 32] and holds
+// C[8 (i / 4) + 4 (l / 32) + i % 4][l % 32], i < 16.
+// Bound by the matrix cores: a workgroup step of nine taps is 9216 OT matrix
+// cycles against some 60 staged values per thread, and two or three workgroups
+// per CU cover each other's staging. The next three taps' weights are loaded
+// into registers while three are multiplied (32 -> 32 channels 10% faster).
+// MI355X, 16^4: 32 -> 576 channels 1.88 ms = 104 TFLOP/s (vector kernel 4.14
+// ms), 576 -> 32 (input gradient) 2.06 ms = 95 TFLOP/s (8.97 ms), 32 -> 32
+// 0.12 ms (0.31 ms); a large FP32 matrix product reaches 154 TFLOP/s.
+constexpr int kCT = 128;  // sites per tile
+constexpr int kCK = 32;   // input channels per LDS chunk
+constexpr int kCP = 36;   // LDS row stride in floats
+template <bool TRANS, int OT>
+__global__ __launch_bounds__(256, 2) void k_conv_mfma(Lat lt, int ntiles, const float* __restrict__ in, int nic,
+                                                      const float* __restrict__ W, int w_cin, int w_cout,
+                                                      const float* __restrict__ bias, int noc, int npos,
+                                                      float* __restrict__ out, float* __restrict__ act,
+                                                      const float* __restrict__ zprev)
+{
+    constexpr int OCT = 32 * OT;
+    extern __shared__ float4 conv_lds[];
+    float* xs = reinterpret_cast<float*>(conv_lds);  // [npos][kCP]
+    float* ws = xs + npos * kCP;                     // [3][OCT][kCP]
+    const int tile_id = xcd_remap(blockIdx.x, gridDim.x);
+    if (tile_id >= ntiles)
+        return;
     const int sgn = TRANS ? -1 : 1;
-    const long V = lt.V;
-    const int L3 = lt.L[3];
-    const long seg = blockIdx.x;                          // segment of TS sites of one x3 line
-    const long line = seg / (L3 / TS);
-    const int x3_0 = (int)(seg - line * (L3 / TS)) * TS;
-    int x[3];
-    {
-        long r = line;
-        x[2] = (int)(r % lt.L[2]);
-        r /= lt.L[2];
-        x[1] = (int)(r % lt.L[1]);
-        x[0] = (int)(r / lt.L[1]);
-    }
+    const Tile tl = make_tile(lt, tile_id, kCT);
+    const int w3 = lt.L[3] + 2;
+    const int np = tl.slots * w3;
     const int oc0 = blockIdx.y * OCT;
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    const int ot = w / NST, st = w % NST;
-    const int kr = lane >> 4, kc = lane & 15;             // k row and column of this lane's operands
-    typedef float f4 __attribute__((ext_vector_type(4)));
-    f4 acc = {0.f, 0.f, 0.f, 0.f};
-    for (int l = 0; l < 27; ++l) {
-        const int o[3] = {l / 9 - 1, (l / 3) % 3 - 1, l % 3 - 1};
-        long base = 0;  // canonical index of (y0, y1, y2, 0)
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int col = lane & 31, kh = lane >> 5;
+    // this thread's staged positions (npos <= 512)
+    Src src[2];
 #pragma unroll
-        for (int mu = 0; mu < 3; ++mu) {
-            int y = x[mu] + sgn * o[mu];
-            y = y < 0 ? y + lt.L[mu] : (y >= lt.L[mu] ? y - lt.L[mu] : y);
-            base += (long)y * lt.str[mu];
+    for (int k = 0; k < 2; ++k)
+        src[k] = pos_source(lt, tl, tid + 256 * k < np ? tid + 256 * k : 0);
+    const int my = w * 32 + col;  // this lane's site in the tile
+    const float* xb = xs + tile_pos(lt, tl, my < tl.n ? my : 0) * kCP + 4 * kh;
+    const float* wb = ws + col * kCP + 4 * kh;
+    f32x16 acc[OT];
+#pragma unroll
+    for (int ot = 0; ot < OT; ++ot)
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+            acc[ot][i] = 0.f;
+    // the weights of three taps (from tap t0 on) and a channel chunk, four channels a piece: loaded into
+    // registers while the previous taps are multiplied, then stored to LDS
+    constexpr int NW = 3 * OT;
+    f32x4 wr[NW];
+    auto w_place = [&](int k, int& c, int& j, int& q) {  // first channel, output channel, tap of piece k
+        const int e = tid + 256 * k;
+        if (TRANS) {  // channels are contiguous in W
+            c = (e % (kCK / 4)) * 4;
+            j = (e / (kCK / 4)) % OCT;
+            q = e / (kCK / 4 * OCT);
+        } else {  // output channels are
+            j = e % OCT;
+            c = (e / OCT) % (kCK / 4) * 4;
+            q = e / (OCT * (kCK / 4));
         }
-        for (int c0 = 0; c0 < nic; c0 += kMC) {
-            __syncthreads();  // the previous chunk's operands are consumed
-            for (int e = threadIdx.x; e < kMC * (TS + 2); e += 256) {
-                const int ic = e / (TS + 2), j = e - ic * (TS + 2);
-                int y3 = x3_0 - 1 + j;
-                y3 = y3 < 0 ? y3 + L3 : (y3 >= L3 ? y3 - L3 : y3);
-                xs[ic][j] = c0 + ic < nic ? in[(long)(c0 + ic) * V + base + y3] : 0.f;
-            }
-            for (int e = threadIdx.x; e < 3 * kMC * OCT; e += 256) {
-                const int q = e / (kMC * OCT), r = e - q * (kMC * OCT);
-                const int ic = r / OCT, c = r - ic * OCT;
-                const int t = l * 3 + q;  // tap of (o0, o1, o2, o3 = q - 1)
-                const int ci = c0 + ic, co = oc0 + c;
-                float v = 0.f;
-                if (ci < nic && co < noc)
-                    v = TRANS ? W[((long)t * w_cin + co) * w_cout + ci] : W[((long)t * w_cin + ci) * w_cout + co];
-                ws[q][ic][c] = v;
-            }
-            __syncthreads();
+    };
+    int woff[NW];  // of its first channel, from the chunk's first entry
 #pragma unroll
-            for (int q = 0; q < 3; ++q) {
-                const int sh = 1 + sgn * (q - 1);  // segment column of site 0 for o3 = q - 1
+    for (int k = 0; k < NW; ++k) {
+        int c, j, q;
+        w_place(k, c, j, q);
+        woff[k] = TRANS ? (q * w_cin + j) * w_cout + c : (q * w_cin + c) * w_cout + j;
+    }
+    const int wstep = TRANS ? 1 : w_cout;
+    auto load_weights = [&](int t0, int c0) {
+        const float* wp = W + (TRANS ? ((long)t0 * w_cin + oc0) * w_cout + c0 : ((long)t0 * w_cin + c0) * w_cout + oc0);
+        if (c0 + kCK <= nic && oc0 + OCT <= noc) {
 #pragma unroll
-                for (int k0 = 0; k0 < kMC; k0 += 4) {
-                    const float a = ws[q][k0 + kr][ot * 16 + kc];
-                    const float b = xs[k0 + kr][st * 16 + kc + sh];
-                    acc = __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, acc, 0, 0, 0);
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int k = 0; k < NW; ++k)
+                    wr[k][i] = (wp + i * wstep)[woff[k]];
+        } else {
+#pragma unroll
+            for (int k = 0; k < NW; ++k) {
+                int c, j, q;
+                w_place(k, c, j, q);
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    wr[k][i] = c0 + c + i < nic && oc0 + j < noc ? (wp + i * wstep)[woff[k]] : 0.f;
+            }
+        }
+    };
+    load_weights(0, 0);
+    for (int l01 = 0; l01 < 9; ++l01) {
+        const int o0 = l01 / 3 - 1, o1 = l01 % 3 - 1;
+        for (int c0 = 0; c0 < nic; c0 += kCK) {
+            const int nc = nic - c0 < kCK ? nic - c0 : kCK;
+            const int nj = (nc + 7) / 8;  // groups of eight channels
+            __syncthreads();              // the previous chunk's operands are consumed
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                const int p = tid + 256 * k;
+                if (p < np) {
+                    const float* q = in + (long)c0 * lt.V + src_site(lt, src[k], sgn * o0, sgn * o1);
+                    if (nc == kCK) {
+#pragma unroll
+                        for (int c = 0; c < kCK; c += 4) {
+                            const f32x4 v = {q[(long)c * lt.V], q[(long)(c + 1) * lt.V], q[(long)(c + 2) * lt.V],
+                                             q[(long)(c + 3) * lt.V]};
+                            *reinterpret_cast<f32x4*>(xs + p * kCP + c) = v;
+                        }
+                    } else {
+                        for (int c = 0; c < 8 * nj; c += 4) {
+                            f32x4 v;
+#pragma unroll
+                            for (int e = 0; e < 4; ++e)
+                                v[e] = c + e < nc ? q[(long)(c + e) * lt.V] : 0.f;
+                            *reinterpret_cast<f32x4*>(xs + p * kCP + c) = v;
+                        }
+                    }
+                }
+            }
+            for (int o2 = -1; o2 <= 1; ++o2) {
+                if (o2 > -1)
+                    __syncthreads();  // the previous taps' weights are consumed
+#pragma unroll
+                for (int k = 0; k < NW; ++k) {
+                    int c, j, q;
+                    w_place(k, c, j, q);
+                    *reinterpret_cast<f32x4*>(ws + (q * OCT + j) * kCP + c) = wr[k];
+                }
+                __syncthreads();
+                const int t0 = l01 * 9 + (o2 + 1) * 3;
+                if (o2 < 1)
+                    load_weights(t0 + 3, c0);
+                else if (c0 + kCK < nic)
+                    load_weights(l01 * 9, c0 + kCK);
+                else if (l01 < 8)
+                    load_weights(t0 + 3, 0);
+#pragma unroll
+                for (int q = 0; q < 3; ++q) {
+                    const float* xt = xb + sgn * (o2 * w3 + q - 1) * kCP;
+                    const float* wt = wb + q * OCT * kCP;
+                    auto step = [&](int j) {
+                        const f32x4 b = *reinterpret_cast<const f32x4*>(xt + 8 * j);
+                        f32x4 a[OT];
+#pragma unroll
+                        for (int ot = 0; ot < OT; ++ot)
+                            a[ot] = *reinterpret_cast<const f32x4*>(wt + ot * 32 * kCP + 8 * j);
+#pragma unroll
+                        for (int k = 0; k < 4; ++k)
+#pragma unroll
+                            for (int ot = 0; ot < OT; ++ot)
+                                acc[ot] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[ot][k], b[k], acc[ot], 0, 0, 0);
+                    };
+                    if (nj == kCK / 8) {
+#pragma unroll
+                        for (int j = 0; j < kCK / 8; ++j)
+                            step(j);
+                    } else {
+                        for (int j = 0; j < nj; ++j)
+                            step(j);
+                    }
                 }
             }
         }
     }
-    const long site = base_site(lt, line, x3_0 + st * 16 + kc);
+    if (my >= tl.n)
+        return;
+    const long site = tl.site0 + my;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int oc = oc0 + ot * 16 + 4 * kr + i;
-        if (oc >= noc)
-            continue;
-        float v = acc[i] + (bias ? bias[oc] : 0.f);
-        if (TRANS && zprev)
-            v *= silu_grad_f(zprev[(long)oc * V + site]);
-        out[(long)oc * V + site] = v;
-        if (!TRANS && act)
-            act[(long)oc * V + site] = silu_f(v);
-    }
+    for (int ot = 0; ot < OT; ++ot)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            const int oc = oc0 + ot * 32 + 8 * (i / 4) + 4 * kh + i % 4;
+            if (oc >= noc)
+                continue;
+            float v = acc[ot][i] + (bias ? bias[oc] : 0.f);
+            if (TRANS && zprev)
+                v *= silu_grad_f(zprev[(long)oc * lt.V + site]);
+            out[(long)oc * lt.V + site] = v;
+            if (!TRANS && act)
+                act[(long)oc * lt.V + site] = silu_f(v);
+        }
 }
 
 // Forward map with BF16 operands on the matrix cores: inputs and weights
@@ -373,7 +539,126 @@ __global__ __launch_bounds__(256) void k_weights_bf16(const float* __restrict__ 
     Wb[e] = (uint16_t)bf16_bits(v);
 }
 
-// Weight gradient, partial over a chunk of sites:
+// Weight gradient on the matrix cores (v_mfma_f32_32x32x2f32), partial over a
+// range of tiles: part[r][t][ci][co] = sum_y in[ci][y + o_t] g[co][y].
+// Workgroup (o0, o1; 32 input channels; 32 or, PAIR, 64 output channels; range
+// of tiles): per tile the input is staged with its halo as for the forward map
+// and g as [site][output channel]. Six wavefronts: o2 = w % 3 - 1, each with
+// the accumulators of the three taps o3; w / 3 selects the output channels
+// 32 (w / 3) .. or, without PAIR, half of the sites of every tile, whose sums
+// are a partial of their own (r = 2 range + w / 3). The contraction runs over
+// the sites, two per instruction; lanes are channels, so every LDS read is a
+// run of 32 consecutive floats. Sums run over at most kWF tiles before they are
+// added to the range's, which keeps the rounding error below that of one long
+// chain (32 -> 576 channels on 16^4: 1.9e-6 of the gradient with one chain).
+// Bound by the matrix cores: five LDS reads of two cycles feed three
+// instructions of 64. MI355X, 16^4: 32 -> 576 channels 2.50 ms = 78 TFLOP/s
+// where the vector kernel took 42.9 ms, 96 -> 32 0.48 ms (14.4 ms). At most 128
+// registers, so that twelve wavefronts share a CU (136: 25% slower).
+constexpr int kWF = 8;
+template <bool PAIR>
+__global__ __launch_bounds__(384, 4) void k_conv_wgrad_mfma(Lat lt, const float* __restrict__ in, int cin,
+                                                            const float* __restrict__ g, int cout, int tiles,
+                                                            int npos, float* __restrict__ part)
+{
+    constexpr int CO = PAIR ? 64 : 32;
+    constexpr int GP = CO + 4;                       // LDS row stride of g
+    constexpr int NK = (PAIR ? kCT : kCT / 2) / 2;   // instructions per tap and tile
+    extern __shared__ float4 conv_lds[];
+    float* xs = reinterpret_cast<float*>(conv_lds);  // [npos][kCP]
+    float* gs = xs + npos * kCP;                     // [kCT][GP]
+    int* ptab = reinterpret_cast<int*>(gs + kCT * GP);  // [kCT] staged offset of every site
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int col = lane & 31, kh = lane >> 5;
+    const int nct = (cin + 31) / 32;
+    const int l01 = blockIdx.x % 9, ci0 = blockIdx.x / 9 % nct * 32, co0 = blockIdx.x / 9 / nct * CO;
+    const int o0 = l01 / 3 - 1, o1 = l01 % 3 - 1;
+    const int o2 = w % 3 - 1, half = w / 3;
+    const int w3 = lt.L[3] + 2;
+    const int nc = cin - ci0 < 32 ? cin - ci0 : 32;
+    const int ntiles = (int)((lt.V + kCT - 1) / kCT);
+    const int tile1 = min(ntiles, (int)(blockIdx.y + 1) * tiles);
+    f32x16 acc[3], sum[3];
+#pragma unroll
+    for (int q = 0; q < 3; ++q)
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+            acc[q][i] = sum[q][i] = 0.f;
+    const int it0 = blockIdx.y * tiles;
+    for (int it = it0; it < tile1; ++it) {
+        if (it > it0 && (it - it0) % kWF == 0) {
+#pragma unroll
+            for (int q = 0; q < 3; ++q) {
+                sum[q] += acc[q];
+#pragma unroll
+                for (int i = 0; i < 16; ++i)
+                    acc[q][i] = 0.f;
+            }
+        }
+        const Tile tl = make_tile(lt, it, kCT);
+        const int np = tl.slots * w3;
+        __syncthreads();  // the previous tile's operands are consumed
+        for (int p = tid; p < np; p += 384) {
+            const float* q = in + (long)ci0 * lt.V + src_site(lt, pos_source(lt, tl, p), o0, o1);
+            if (nc == 32) {
+#pragma unroll
+                for (int c = 0; c < 32; c += 4) {
+                    const f32x4 v = {q[(long)c * lt.V], q[(long)(c + 1) * lt.V], q[(long)(c + 2) * lt.V],
+                                     q[(long)(c + 3) * lt.V]};
+                    *reinterpret_cast<f32x4*>(xs + p * kCP + c) = v;
+                }
+            } else {
+                for (int c = 0; c < 32; c += 4) {
+                    f32x4 v;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        v[e] = c + e < nc ? q[(long)(c + e) * lt.V] : 0.f;
+                    *reinterpret_cast<f32x4*>(xs + p * kCP + c) = v;
+                }
+            }
+        }
+        for (int e = tid; e < kCT * (CO / 4); e += 384) {
+            const int i = e % kCT, c = e / kCT * 4;
+            f32x4 v;
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                v[k] = i < tl.n && co0 + c + k < cout ? g[(long)(co0 + c + k) * lt.V + tl.site0 + i] : 0.f;
+            *reinterpret_cast<f32x4*>(gs + i * GP + c) = v;
+        }
+        if (tid < kCT)
+            ptab[tid] = tile_pos(lt, tl, tid < tl.n ? tid : 0) * kCP;
+        __syncthreads();
+        const float* xb = xs + o2 * w3 * kCP + col;
+        const float* gb = gs + (PAIR ? half * 32 : 0) + col;
+        const int k0 = (PAIR ? 0 : half * (kCT / 2)) + kh;  // first site of this lane
+#pragma unroll 4
+        for (int k = 0; k < NK; ++k) {
+            const int i = k0 + 2 * k;
+            const float* xp = xb + ptab[i];
+            const float b = gb[i * GP];
+#pragma unroll
+            for (int q = 0; q < 3; ++q)
+                acc[q] = __builtin_amdgcn_mfma_f32_32x32x2f32(xp[(q - 1) * kCP], b, acc[q], 0, 0, 0);
+        }
+    }
+    const int co = co0 + (PAIR ? half * 32 : 0) + col;
+    if (co >= cout)
+        return;
+    const long r = PAIR ? blockIdx.y : 2 * blockIdx.y + half;
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+        float* dst = part + (r * 81 + l01 * 9 + (o2 + 1) * 3 + q) * cin * cout;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            const int c = 8 * (i / 4) + 4 * kh + i % 4;
+            if (c < nc)
+                dst[(long)(ci0 + c) * cout + co] = sum[q][i] + acc[q][i];
+        }
+    }
+}
+
+// The same with vector instructions, for the lattices of k_conv, partial over a
+// chunk of sites:
 // part[chunk][t][ci][co] = sum_{y in chunk} in[ci][y + o_t] g[co][y].
 // Workgroup (t, co tile of kWT, site chunk); thread (ci group, co), the
 // tiles of g and of the shifted input staged in LDS kWS sites at a time.
@@ -446,14 +731,28 @@ __global__ __launch_bounds__(256) void k_sum_chunks(const float* __restrict__ pa
     dW[e] = s;
 }
 
-// db[co] = sum_y g[co][y], one workgroup per channel
-__global__ __launch_bounds__(256) void k_bias_grad(const float* __restrict__ g, long V, float* __restrict__ db)
+// db[co] = sum_y g[co][y], one workgroup per channel; sixteen loads in flight
+// per thread (V is a multiple of 64), summed in pairs in a fixed order
+__global__ __launch_bounds__(1024) void k_bias_grad(const float* __restrict__ g, long V, float* __restrict__ db)
 {
     __shared__ float sh[16];
     const float* gc = g + (long)blockIdx.x * V;
-    float s = 0.f;
-    for (long y = threadIdx.x; y < V; y += blockDim.x)
-        s += gc[y];
+    float a[16];
+#pragma unroll
+    for (int k = 0; k < 16; ++k)
+        a[k] = 0.f;
+    for (long y = threadIdx.x; y < V; y += 16 * 1024) {
+#pragma unroll
+        for (int k = 0; k < 16; ++k)
+            if (y + 1024 * k < V)
+                a[k] += gc[y + 1024 * k];
+    }
+#pragma unroll
+    for (int h = 8; h > 0; h >>= 1)
+#pragma unroll
+        for (int k = 0; k < h; ++k)
+            a[k] += a[k + h];
+    float s = a[0];
     s = block_sum(s, sh);
     if (threadIdx.x == 0)
         db[blockIdx.x] = s;
@@ -766,16 +1065,68 @@ inline unsigned site_blocks(long n) { return (unsigned)((n + 255) / 256); }
 
 }  // namespace
 
-size_t conv_wgrad_chunk_floats(const Geom& g, int cin, int cout, long* chunk, int* nchunk)
+// Positions staged for a tile of T sites, the largest over all tiles: a tile
+// covers at most rows = (T - 1) / L3 + 2 rows (exactly T / L3 when tiles start
+// at row boundaries) and each run of rows of one plane adds two.
+int conv_tile_positions(const Geom& g, int T)
 {
-    // about 64 workgroups' worth of sites per chunk, at most 32 chunks
-    long c = (g.V + 31) / 32;
-    c = ((c + kWS - 1) / kWS) * kWS;
-    if (c < 4096)
-        c = 4096;
-    *chunk = c;
-    *nchunk = (int)((g.V + c - 1) / c);
-    return (size_t)(*nchunk) * 81 * cin * cout;
+    const int L3 = g.L[3], L2 = g.L[2];
+    int rows = T % L3 == 0 ? T / L3 : L3 % T == 0 ? 1 : (T - 1) / L3 + 2;
+    const long total = g.V / L3;
+    if (rows > total)
+        rows = (int)total;
+    int planes = rows % L2 == 0 && T % L3 == 0 ? rows / L2 : L2 % rows == 0 && T % L3 == 0 ? 1 : (rows - 1) / L2 + 2;
+    if (L3 % T == 0)
+        planes = 1;
+    return (rows + 2 * planes) * (L3 + 2);
+}
+
+// LDS of the FP32 tile kernels, in bytes; 0 if the lattice's rows are too long
+// for them (more than 512 staged positions): the vector kernels serve those.
+size_t conv_lds_bytes(const Geom& g, int ot)
+{
+    const int np = conv_tile_positions(g, kCT);
+    return np > 512 ? 0 : sizeof(float) * ((size_t)np * kCP + (size_t)3 * 32 * ot * kCP);
+}
+size_t wgrad_lds_bytes(const Geom& g, bool pair)
+{
+    const int np = conv_tile_positions(g, kCT);
+    return np > 512 ? 0 : sizeof(float) * ((size_t)np * kCP + (size_t)kCT * ((pair ? 64 : 32) + 4) + kCT);
+}
+
+// Two workgroups of the matrix-core weight gradient fit a CU, so the ranges of
+// tiles are cut to give at most 512 workgroups (one full round of 256 CUs; a
+// few more would run alone afterwards). cap: most floats of partial sums.
+bool conv_wgrad_plan(const Geom& g, int cin, int cout, size_t cap, WgradPlan* p)
+{
+    const size_t per = (size_t)81 * cin * cout;
+    p->mfma = wgrad_lds_bytes(g, true) != 0;
+    if (p->mfma) {
+        p->pair = cout > 32;
+        const int tiles = (int)((g.V + kCT - 1) / kCT);
+        const int groups = 9 * ((cin + 31) / 32) * ((cout + (p->pair ? 63 : 31)) / (p->pair ? 64 : 32));
+        const int per_range = p->pair ? 1 : 2;  // partials written per range
+        long n = std::max(1, std::min(tiles, 512 / groups));
+        n = std::min<long>(n, (long)(cap / per) / per_range);
+        if (n < 1)
+            return false;
+        p->chunk = (tiles + n - 1) / n;
+        p->nchunk = (int)((tiles + p->chunk - 1) / p->chunk);
+        p->nparts = p->nchunk * per_range;
+    } else {
+        // at most 32 ranges of at least 4096 sites
+        long c = std::max<long>(4096, (g.V + 31) / 32);
+        const long most = (long)(cap / per);
+        if (most < 1)
+            return false;
+        c = std::max(c, (g.V + most - 1) / most);
+        c = ((c + kWS - 1) / kWS) * kWS;
+        p->chunk = c;
+        p->pair = false;
+        p->nparts = p->nchunk = (int)((g.V + c - 1) / c);
+    }
+    p->floats = (size_t)p->nparts * per;
+    return p->floats <= cap;
 }
 
 // ------------------------------------- allocation-free weight gradient
@@ -808,36 +1159,44 @@ float* noalloc_scratch()
     return ptr[dev];
 }
 
-bool conv_wgrad_chunk_fit(const Geom& g, int cin, int cout, size_t cap, long* chunk, int* nchunk)
-{
-    const size_t per = (size_t)81 * cin * cout;
-    if (conv_wgrad_chunk_floats(g, cin, cout, chunk, nchunk) <= cap)
-        return true;
-    const long most = (long)(cap / per);
-    if (most < 1)
-        return false;
-    long c = (g.V + most - 1) / most;
-    c = ((c + kWS - 1) / kWS) * kWS;
-    *chunk = c;
-    *nchunk = (int)((g.V + c - 1) / c);
-    return (size_t)(*nchunk) * per <= cap;
-}
-
 void launch_net_features(const Geom& g, const c64* U64, const float* noise, float* x, hipStream_t s)
 {
     hipLaunchKernelGGL(k_features, dim3(site_blocks(g.V)), dim3(256), 0, s, g, U64, noise, x);
 }
 
+namespace {
+
+template <bool TRANS>
+void launch_conv(const Geom& g, const float* in, int nic, const float* W, int w_cin, int w_cout, const float* bias,
+                 int noc, float* out, float* act, const float* zprev, hipStream_t s)
+{
+    const Lat lt = make_lat(g);
+    const int ot = noc <= 32 ? 1 : 2;
+    const size_t lds = conv_lds_bytes(g, ot);
+    const int np = conv_tile_positions(g, kCT);
+    const int ntiles = (int)((g.V + kCT - 1) / kCT);
+    const dim3 grid((unsigned)pad_grid(ntiles), (noc + 32 * ot - 1) / (32 * ot));
+    static std::once_flag attr[2];  // per instantiation
+    if (lds && ot == 1) {
+        set_max_lds_once(attr[0], reinterpret_cast<const void*>(&k_conv_mfma<TRANS, 1>), 128 * 1024);
+        hipLaunchKernelGGL((k_conv_mfma<TRANS, 1>), grid, dim3(256), lds, s, lt, ntiles, in, nic, W, w_cin, w_cout,
+                           bias, noc, np, out, act, zprev);
+    } else if (lds) {
+        set_max_lds_once(attr[1], reinterpret_cast<const void*>(&k_conv_mfma<TRANS, 2>), 128 * 1024);
+        hipLaunchKernelGGL((k_conv_mfma<TRANS, 2>), grid, dim3(256), lds, s, lt, ntiles, in, nic, W, w_cin, w_cout,
+                           bias, noc, np, out, act, zprev);
+    } else {
+        hipLaunchKernelGGL(k_conv<TRANS>, dim3(site_blocks(g.V), (noc + kCO - 1) / kCO), dim3(256), 0, s, lt, in, nic,
+                           W, w_cin, w_cout, bias, noc, out, act, zprev);
+    }
+}
+
+}  // namespace
+
 void launch_conv_forward(const Geom& g, const float* in, int cin, const float* W, const float* b, int cout, float* z,
                          float* a, hipStream_t s)
 {
-    const Lat lt = make_lat(g);
-    if (g.L[3] % 32 == 0)
-        hipLaunchKernelGGL(k_conv_mfma<false>, dim3((unsigned)(g.V / 32), (cout + 31) / 32), dim3(256), 0, s, lt, in,
-                           cin, W, cin, cout, b, cout, z, a, nullptr);
-    else
-        hipLaunchKernelGGL(k_conv<false>, dim3(site_blocks(g.V), (cout + kCO - 1) / kCO), dim3(256), 0, s, lt, in,
-                           cin, W, cin, cout, b, cout, z, a, nullptr);
+    launch_conv<false>(g, in, cin, W, cin, cout, b, cout, z, a, nullptr, s);
 }
 
 bool conv_bf16_fits(const Geom& g) { return g.L[3] % kBTS == 0 && g.L[2] % kBNL == 0; }
@@ -867,23 +1226,30 @@ void launch_conv_forward_bf16(const Geom& g, const float* in, int cin, const flo
 }
 
 void launch_conv_backward(const Geom& g, const float* in, int cin, const float* W, int cout, const float* gr,
-                          float* dW, float* db, float* din, const float* zprev, float* part, long chunk, int nchunk,
+                          float* dW, float* db, float* din, const float* zprev, float* part, const WgradPlan& p,
                           hipStream_t s)
 {
     const Lat lt = make_lat(g);
-    hipLaunchKernelGGL(k_conv_wgrad, dim3(81, (cout + kWT - 1) / kWT, nchunk), dim3(256), 0, s, lt, in, cin, gr,
-                       cout, chunk, part);
+    static std::once_flag attr[2];
+    const int np = conv_tile_positions(g, kCT);
+    const unsigned nct = (cin + 31) / 32;
+    if (p.mfma && p.pair) {
+        set_max_lds_once(attr[0], reinterpret_cast<const void*>(&k_conv_wgrad_mfma<true>), 128 * 1024);
+        hipLaunchKernelGGL(k_conv_wgrad_mfma<true>, dim3(9 * nct * ((cout + 63) / 64), p.nchunk), dim3(384),
+                           wgrad_lds_bytes(g, true), s, lt, in, cin, gr, cout, (int)p.chunk, np, part);
+    } else if (p.mfma) {
+        set_max_lds_once(attr[1], reinterpret_cast<const void*>(&k_conv_wgrad_mfma<false>), 128 * 1024);
+        hipLaunchKernelGGL(k_conv_wgrad_mfma<false>, dim3(9 * nct * ((cout + 31) / 32), p.nchunk), dim3(384),
+                           wgrad_lds_bytes(g, false), s, lt, in, cin, gr, cout, (int)p.chunk, np, part);
+    } else {
+        hipLaunchKernelGGL(k_conv_wgrad, dim3(81, (cout + kWT - 1) / kWT, p.nchunk), dim3(256), 0, s, lt, in, cin,
+                           gr, cout, p.chunk, part);
+    }
     const long n = 81L * cin * cout;
-    hipLaunchKernelGGL(k_sum_chunks, dim3(site_blocks(n)), dim3(256), 0, s, part, n, nchunk, dW);
-    hipLaunchKernelGGL(k_bias_grad, dim3(cout), dim3(256), 0, s, gr, g.V, db);
-    if (!din)
-        return;
-    if (g.L[3] % 32 == 0)
-        hipLaunchKernelGGL(k_conv_mfma<true>, dim3((unsigned)(g.V / 32), (cin + 31) / 32), dim3(256), 0, s, lt, gr,
-                           cout, W, cin, cout, nullptr, cin, din, nullptr, zprev);
-    else
-        hipLaunchKernelGGL(k_conv<true>, dim3(site_blocks(g.V), (cin + kCO - 1) / kCO), dim3(256), 0, s, lt, gr,
-                           cout, W, cin, cout, nullptr, cin, din, nullptr, zprev);
+    hipLaunchKernelGGL(k_sum_chunks, dim3(site_blocks(n)), dim3(256), 0, s, part, n, p.nparts, dW);
+    hipLaunchKernelGGL(k_bias_grad, dim3(cout), dim3(1024), 0, s, gr, g.V, db);
+    if (din)
+        launch_conv<true>(g, gr, cout, W, cin, cout, nullptr, cin, din, nullptr, zprev, s);
 }
 
 void launch_out_to_fields(const Geom& g, const float* out, int Ns, c64* f, hipStream_t s)
