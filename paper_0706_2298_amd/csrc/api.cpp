@@ -67,7 +67,7 @@ void free_all(dfl_ctx* c)
                     c->At64, c->At32, c->lpart, c->lstats, c->lbar_count, c->lbar_gen, c->tN,
                     c->lfin, c->lacoef, c->dact, c->net_part, c->loss_Y, c->loss_buf, c->dtol, c->Mt64, c->Mt32, c->lw1, c->lw2,
                     c->gsR, c->gU, c->gW, c->gQ, c->gZ, c->gQ32, c->gZ32, c->gC, c->Cl64, c->Cl32,
-                    c->gAinv, c->gGw, c->bootF, c->bootT, c->net_wbf, c->PhiT};
+                    c->gAinv, c->gGw, c->bootF, c->bootT, c->net_wbf, c->net_xbf, c->PhiT};
     for (void* p : ptrs)
         if (p)
             (void)hipFree(p);
@@ -1894,7 +1894,15 @@ int conv4d_forward_bf16(dfl_ctx* c, const float* in, int cin, const float* W, co
     if (!conv_bf16_fits(c->g))
         fail(DFL_EINVAL, "the BF16 convolution needs L3 % 32 == 0 and L2 % 4 == 0");
     c->net_wbf = grow<uint16_t>(c, c->net_wbf, c->net_wbf_n, conv_bf16_weight_elems(cin, cout));
-    launch_conv_forward_bf16(c->g, in, cin, W, b, cout, z, a, c->net_wbf, c->stream);
+    try {
+        c->net_xbf = grow<uint16_t>(c, c->net_xbf, c->net_xbf_n, conv_bf16_input_elems(c->g, cin, cout));
+    } catch (const dfl::Error& e) {
+        if (e.code != DFL_ENOMEM)
+            throw;
+        (void)hipGetLastError();  // no room for the rounded input: the kernel that rounds as it reads
+        c->net_xbf = nullptr;
+    }
+    launch_conv_forward_bf16(c->g, in, cin, W, b, cout, z, a, c->net_wbf, c->net_xbf, c->stream);
     HIPCHECK(hipGetLastError());
     API_END
 }

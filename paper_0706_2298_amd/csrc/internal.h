@@ -166,6 +166,8 @@ struct dfl_ctx {
     size_t net_part_n = 0;
     uint16_t* net_wbf = nullptr; // BF16 weights of the BF16 forward
     size_t net_wbf_n = 0;
+    uint16_t* net_xbf = nullptr; // and its input, site-major in BF16
+    size_t net_xbf_n = 0;
     dfl::c64* PhiT = nullptr;    // the basis in the transposed in-block order (assembly of the
     size_t PhiT_n = 0;           // face columns along x2 and x3)
     dfl::c64* loss_Y = nullptr;  // deficit loss: per-block G^-1 Psi^+ T
@@ -372,11 +374,13 @@ struct WgradPlan {
 };
 bool conv_wgrad_plan(const Geom& g, int cin, int cout, size_t cap, WgradPlan* p);
 // BF16-operand forward (FP32 sums) for lattices with L3 % 32 == 0 and L2 % 4 == 0
-// (conv_bf16_fits); Wb holds conv_bf16_weight_elems(cin, cout) BF16 entries
+// (conv_bf16_fits); Wb holds conv_bf16_weight_elems(cin, cout) BF16 entries,
+// Xb (the rounded input, site-major; may be null) conv_bf16_input_elems
 bool conv_bf16_fits(const Geom& g);
 size_t conv_bf16_weight_elems(int cin, int cout);
+size_t conv_bf16_input_elems(const Geom& g, int cin, int cout);
 void launch_conv_forward_bf16(const Geom& g, const float* in, int cin, const float* W, const float* b, int cout,
-                              float* z, float* a, uint16_t* Wb, hipStream_t s);
+                              float* z, float* a, uint16_t* Wb, uint16_t* Xb, hipStream_t s);
 void launch_conv_backward(const Geom& g, const float* in, int cin, const float* W, int cout, const float* gr,
                           float* dW, float* db, float* din, const float* zprev, float* part, const WgradPlan& p,
                           hipStream_t s);

@@ -400,7 +400,9 @@ __global__ __launch_bounds__(256, 2) void k_conv_mfma(Lat lt, int ntiles, const 
         }
 }
 
-// Forward map with BF16 operands on the matrix cores: inputs and weights
+// Forward map with BF16 operands on the matrix cores, for lattices whose rows are
+// too long for the staged tiles of k_conv_bf16_tile or where its rounded input
+// finds no room: inputs and weights
 // rounded to BF16 (nearest even), products summed in FP32
 // (v_mfma_f32_16x16x32_bf16), bias and activation in FP32. The weights come
 // pre-converted as Wb[t][oc][ic] (ic padded to a multiple of 32 and oc to
@@ -522,6 +524,163 @@ __global__ __launch_bounds__(256) void k_conv_bf16(Lat lt, const float* __restri
                     act[(long)oc * V + site] = silu_f(v);
             }
         }
+}
+
+// The BF16 forward map on staged site tiles (see make_tile), with
+// v_mfma_f32_32x32x16_bf16. The input comes rounded and site-major, Xb[site][ic]
+// (k_planes_bf16), the weights rounded and in operand order (k_weights_frag):
+// 64 lanes of eight channels per (tap, sixteen input channels, 32 output
+// channels), which the wavefronts read straight into registers, one tap ahead
+// of their use. Workgroup: a tile of 128 NS sites and 32 OT output channels,
+// wavefront w the sites 32 NS w .. of all of them, so that an operand read
+// feeds OT or NS instructions. Staged rows have 40 entries (80 bytes): eight
+// neighbouring positions' 16-byte reads cover all banks.
+// With NS = 4 and OT = 2 a tap and 32 channels are 16 instructions of 32 cycles
+// per wavefront against 8 KB of LDS reads, half of the LDS's time. MI355X, 32 ->
+// 576 channels on 64 x 32^3: 7.9 ms = 790 TFLOP/s with the rounding pass
+// (k_conv_bf16: 23.4 ms); a large BF16 matrix product reaches 1180.
+template <int OT, int NS>
+__global__ __launch_bounds__(256, 2) void k_conv_bf16_tile(Lat lt, int ntiles, const uint16_t* __restrict__ Xb,
+                                                           int cinP, const u16x8* __restrict__ Wf, int noct,
+                                                           const float* __restrict__ bias, int cout, int npos,
+                                                           float* __restrict__ out, float* __restrict__ act)
+{
+    constexpr int T = 128 * NS;
+    extern __shared__ float4 conv_lds[];
+    uint16_t* xs = reinterpret_cast<uint16_t*>(conv_lds);        // [npos][kBRow]
+    int2* tab = reinterpret_cast<int2*>(xs + (size_t)npos * kBRow);  // source of every position
+    const int tile_id = xcd_remap(blockIdx.x, gridDim.x);
+    if (tile_id >= ntiles)
+        return;
+    const Tile tl = make_tile(lt, tile_id, T);
+    const int w3 = lt.L[3] + 2;
+    const int np = tl.slots * w3;
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int col = lane & 31, kh = lane >> 5;
+    const int oct0 = blockIdx.y * OT;
+    for (int p = tid; p < np; p += 256) {
+        const Src r = pos_source(lt, tl, p);
+        tab[p] = make_int2(r.x0 << 16 | r.x1, r.in_plane);
+    }
+    const uint16_t* xb[NS];
+#pragma unroll
+    for (int st = 0; st < NS; ++st) {
+        const int i = (w * NS + st) * 32 + col;
+        xb[st] = xs + tile_pos(lt, tl, i < tl.n ? i : 0) * kBRow + 8 * kh;
+    }
+    const int nk = cinP / 16;
+    u16x8 a[2][OT], an[2][OT];  // weights of this tap and of the next one
+    auto load_a = [&](int t, int c0) {
+        const u16x8* q = Wf + (((long)t * nk + c0 / 16) * noct + oct0) * 64 + lane;
+#pragma unroll
+        for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+            for (int ot = 0; ot < OT; ++ot)
+                an[kk][ot] = q[(kk * noct + ot) * 64];
+    };
+    load_a(0, 0);
+    f32x16 acc[OT][NS];
+#pragma unroll
+    for (int ot = 0; ot < OT; ++ot)
+#pragma unroll
+        for (int st = 0; st < NS; ++st)
+#pragma unroll
+            for (int i = 0; i < 16; ++i)
+                acc[ot][st][i] = 0.f;
+    for (int c0 = 0; c0 < cinP; c0 += kBK)
+        for (int l01 = 0; l01 < 9; ++l01) {
+            const int o0 = l01 / 3 - 1, o1 = l01 % 3 - 1;
+            __syncthreads();  // the table is written, the previous operands are consumed
+            for (int e = tid; e < np * 4; e += 256) {
+                const int2 s = tab[e >> 2];
+                const Src r{s.x >> 16, s.x & 0xffff, s.y};
+                *reinterpret_cast<u16x8*>(xs + (e >> 2) * kBRow + (e & 3) * 8) =
+                    *reinterpret_cast<const u16x8*>(Xb + src_site(lt, r, o0, o1) * cinP + c0 + (e & 3) * 8);
+            }
+            __syncthreads();
+            for (int o2 = -1; o2 <= 1; ++o2) {
+#pragma unroll
+                for (int q = 0; q < 3; ++q) {
+                    const int t = l01 * 9 + (o2 + 1) * 3 + q;
+#pragma unroll
+                    for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+                        for (int ot = 0; ot < OT; ++ot)
+                            a[kk][ot] = an[kk][ot];
+                    if (t < 80)
+                        load_a(t + 1, c0);
+                    else if (c0 + kBK < cinP)
+                        load_a(0, c0 + kBK);
+#pragma unroll
+                    for (int kk = 0; kk < 2; ++kk)
+#pragma unroll
+                        for (int st = 0; st < NS; ++st) {
+                            const bf16x8 b = __builtin_bit_cast(
+                                bf16x8, *reinterpret_cast<const u16x8*>(xb[st] + (o2 * w3 + q - 1) * kBRow + 16 * kk));
+#pragma unroll
+                            for (int ot = 0; ot < OT; ++ot)
+                                acc[ot][st] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(
+                                    __builtin_bit_cast(bf16x8, a[kk][ot]), b, acc[ot][st], 0, 0, 0);
+                        }
+                }
+            }
+        }
+#pragma unroll
+    for (int ot = 0; ot < OT; ++ot)
+#pragma unroll
+        for (int st = 0; st < NS; ++st) {
+            const int k = (w * NS + st) * 32 + col;
+            if (k >= tl.n)
+                continue;
+            const long site = tl.site0 + k;
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                const int oc = (oct0 + ot) * 32 + 8 * (i / 4) + 4 * kh + i % 4;
+                if (oc >= cout)
+                    continue;
+                const float v = acc[ot][st][i] + (bias ? bias[oc] : 0.f);
+                out[(long)oc * lt.V + site] = v;
+                if (act)
+                    act[(long)oc * lt.V + site] = silu_f(v);
+            }
+        }
+}
+
+// Xb[site][ic] = bf16(in[ic][site]), ic padded to cinP with zeros: one thread
+// per site and eight channels (grid: 64 sites x cinP / 32)
+__global__ __launch_bounds__(256) void k_planes_bf16(const float* __restrict__ in, int cin, int cinP, long V,
+                                                     uint16_t* __restrict__ Xb)
+{
+    const long site = (long)blockIdx.x * 64 + (threadIdx.x & 63);
+    const int c0 = blockIdx.y * 32 + (threadIdx.x >> 6) * 8;
+    if (site >= V)
+        return;
+    u16x8 v;
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+        v[j] = (uint16_t)bf16_bits(c0 + j < cin ? in[(long)(c0 + j) * V + site] : 0.f);
+    *reinterpret_cast<u16x8*>(Xb + site * cinP + c0) = v;
+}
+
+// Wf[((t nk + k) noct + o) 64 + lane][j] = bf16(W[t][16 k + 8 (lane / 32) + j][32 o + lane % 32]),
+// zero beyond the channels: the weights in the operand order of k_conv_bf16_tile
+__global__ __launch_bounds__(256) void k_weights_frag(const float* __restrict__ W, int cin, int cout, int nk, int noct,
+                                                      u16x8* __restrict__ Wf)
+{
+    const long e = (long)blockIdx.x * 256 + threadIdx.x;
+    if (e >= 81L * nk * noct * 64)
+        return;
+    const int lane = (int)(e & 63);
+    long r = e >> 6;
+    const int oc = (int)(r % noct) * 32 + (lane & 31);
+    r /= noct;
+    const int ic = (int)(r % nk) * 16 + 8 * (lane >> 5);
+    const long t = r / nk;
+    u16x8 v;
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+        v[j] = (uint16_t)bf16_bits(ic + j < cin && oc < cout ? W[(t * cin + ic + j) * cout + oc] : 0.f);
+    Wf[e] = v;
 }
 
 // Wb[t][oc][ic] = bf16(W[t][ic][oc]) on the padded [81][coutP][cinP] grid (zeros outside)
@@ -1201,6 +1360,29 @@ void launch_conv_forward(const Geom& g, const float* in, int cin, const float* W
 
 bool conv_bf16_fits(const Geom& g) { return g.L[3] % kBTS == 0 && g.L[2] % kBNL == 0; }
 
+namespace {
+
+size_t bf16_lds_bytes(const Geom& g, int ns)
+{
+    return (size_t)conv_tile_positions(g, 128 * ns) * (kBRow * sizeof(uint16_t) + sizeof(int2));
+}
+
+// Sites per tile of the BF16 map: 512 where that gives two workgroups per CU
+// and two of them share a CU's LDS (32 -> 576 on 16^2 x 24 x 64: 1.55 ms, the
+// segment kernel 4.41), 128 where the lattice is too small for that (32 -> 32
+// on 4 x 8^2 x 32: 34 us against 136), 0 (segment kernel) where the rows are
+// too long for a tile. Returned in units of 128 sites.
+int bf16_tile_ns(const Geom& g, int cout)
+{
+    constexpr size_t half = 80 * 1024;
+    const long nco = (cout + 63) / 64;
+    if (bf16_lds_bytes(g, 4) <= half && g.V / 512 * nco >= 512)
+        return 4;
+    return bf16_lds_bytes(g, 1) <= half ? 1 : 0;
+}
+
+}  // namespace
+
 size_t conv_bf16_weight_elems(int cin, int cout)
 {
     const int ot = cout <= 32 ? 2 : 4;
@@ -1208,12 +1390,42 @@ size_t conv_bf16_weight_elems(int cin, int cout)
     return 81ul * (size_t)cinP * (size_t)coutP;
 }
 
+size_t conv_bf16_input_elems(const Geom& g, int cin, int cout)
+{
+    return bf16_tile_ns(g, cout) ? (size_t)((cin + kBK - 1) / kBK * kBK) * (size_t)g.V : 0;
+}
+
 void launch_conv_forward_bf16(const Geom& g, const float* in, int cin, const float* W, const float* b, int cout,
-                              float* z, float* a, uint16_t* Wb, hipStream_t s)
+                              float* z, float* a, uint16_t* Wb, uint16_t* Xb, hipStream_t s)
 {
     const Lat lt = make_lat(g);
+    const int cinP = (cin + kBK - 1) / kBK * kBK;
+    const int ns = bf16_tile_ns(g, cout);
+    if (ns && Xb) {
+        const int ot = cout <= 32 ? 1 : 2;
+        const int noct = (cout + 32 * ot - 1) / (32 * ot) * ot, nk = cinP / 16;
+        u16x8* Wf = reinterpret_cast<u16x8*>(Wb);
+        hipLaunchKernelGGL(k_weights_frag, dim3(site_blocks(81L * nk * noct * 64)), dim3(256), 0, s, W, cin, cout, nk,
+                           noct, Wf);
+        hipLaunchKernelGGL(k_planes_bf16, dim3((unsigned)(g.V / 64), cinP / 32), dim3(256), 0, s, in, cin, cinP, g.V,
+                           Xb);
+        const int ntiles = (int)((g.V + 128 * ns - 1) / (128 * ns));
+        const int np = conv_tile_positions(g, 128 * ns);
+        const size_t lds = bf16_lds_bytes(g, ns);
+        const dim3 grid((unsigned)pad_grid(ntiles), noct / ot);
+        static std::once_flag attr[4];
+        auto launch = [&](std::once_flag& f, auto* kernel) {
+            set_max_lds_once(f, reinterpret_cast<const void*>(kernel), 80 * 1024);
+            hipLaunchKernelGGL(kernel, grid, dim3(256), lds, s, lt, ntiles, Xb, cinP, Wf, noct, b, cout, np, z, a);
+        };
+        if (ot == 1)
+            ns == 1 ? launch(attr[0], &k_conv_bf16_tile<1, 1>) : launch(attr[1], &k_conv_bf16_tile<1, 4>);
+        else
+            ns == 1 ? launch(attr[2], &k_conv_bf16_tile<2, 1>) : launch(attr[3], &k_conv_bf16_tile<2, 4>);
+        return;
+    }
     const int ot = cout <= 32 ? 2 : 4;
-    const int cinP = (cin + kBK - 1) / kBK * kBK, coutP = (cout + 16 * ot - 1) / (16 * ot) * (16 * ot);
+    const int coutP = (cout + 16 * ot - 1) / (16 * ot) * (16 * ot);
     const long nw = 81L * cinP * coutP;
     hipLaunchKernelGGL(k_weights_bf16, dim3(site_blocks(nw)), dim3(256), 0, s, W, cin, cout, cinP, coutP, Wb);
     const unsigned ngrp = (unsigned)(g.V / (kBTS * kBNL));

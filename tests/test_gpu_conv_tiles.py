@@ -65,3 +65,42 @@ def test_conv_tiles(dims, blk, cin, cout):
             assert np.all(np.abs(db.cpu().numpy() - dbr) <= n * EPS / (1 - n * EPS) * dbs)
     finally:
         S.close()
+
+
+def bf16_round(a):
+    """Round to BF16 (nearest even)."""
+    u = np.ascontiguousarray(a, dtype=np.float32).view(np.uint32).astype(np.uint64)
+    u = ((u + 0x7FFF + ((u >> 16) & 1)) >> 16) << 16
+    return u.astype(np.uint32).view(np.float32).astype(np.float64)
+
+
+@pytest.mark.parametrize("dims,blk,cin,cout", [
+    ((16, 8, 8, 32), (4, 4, 4, 4), 5, 576),      # tiles of 512 sites over two planes, two channel tiles
+    ((4, 8, 12, 64), (2, 4, 6, 4), 33, 576),   # tiles that start inside a plane, two input chunks
+    ((16, 16, 32, 32), (4, 4, 4, 4), 3, 8),      # tiles of 512 sites, one channel tile
+    ((2, 4, 12, 32), (1, 2, 6, 4), 4, 33),       # tiles of 128 sites across planes
+    ((2, 2, 4, 1024), (1, 1, 2, 64), 4, 33),     # rows too long for the tiles
+])
+def test_conv_bf16_tiles(dims, blk, cin, cout):
+    # against the FP64 map of the BF16-rounded operands: the products are exact in FP32, so only the
+    # FP32 sum of n = 81 cin products and the bias add round
+    print(f"[case] conv bf16 tiles {dims} {cin}->{cout}", flush=True)
+    S = Solver(dims, dfl_block=blk, sap_block=blk, Ns=1, nkv=1, little_nkv=1, m0=-0.2)
+    try:
+        torch = S.torch
+        V = S.V
+        rng = np.random.default_rng(cin * 17 + cout + dims[3])
+        x = bf16_round(rng.standard_normal((V, cin)))
+        W = bf16_round(rng.standard_normal((3, 3, 3, 3, cin, cout)) / np.sqrt(81 * cin))
+        b = rng.standard_normal(cout).astype(np.float32).astype(np.float64)
+        xd = torch.tensor(np.ascontiguousarray(x.T), dtype=torch.float32, device="cuda")
+        Wd = torch.tensor(W.reshape(81, cin, cout), dtype=torch.float32, device="cuda")
+        bd = torch.tensor(b, dtype=torch.float32, device="cuda")
+        z = torch.empty(cout * V, dtype=torch.float32, device="cuda")
+        binding.conv4d_forward_bf16(S.ctx, xd, cin, Wd, bd, cout, z, None)
+        zg = z.cpu().numpy().astype(np.float64).reshape(cout, V).T
+        n = 81 * cin + 2
+        bound = n * EPS / (1 - n * EPS) * onet.conv4d(np.abs(x), np.abs(W), np.abs(b), dims)
+        assert np.all(np.abs(zg - onet.conv4d(x, W, b, dims)) <= bound)
+    finally:
+        S.close()
