@@ -328,6 +328,15 @@ template <int CTRL, int ROWS> __device__ inline float dpp(float v)
 {
     return __int_as_float(dpp<CTRL, ROWS>(__float_as_int(v)));
 }
+// moves inside a row of 16 lanes, where every lane has a source
+template <int CTRL> __device__ inline int row(int v) { return __builtin_amdgcn_mov_dpp(v, CTRL, 0xF, 0xF, true); }
+template <int CTRL> __device__ inline float row(float v) { return __int_as_float(row<CTRL>(__float_as_int(v))); }
+template <int CTRL> __device__ inline double row(double v)
+{
+    const long long b = __double_as_longlong(v);
+    const int lo = row<CTRL>((int)b), hi = row<CTRL>((int)(b >> 32));
+    return __longlong_as_double(((long long)hi << 32) | (unsigned)lo);
+}
 __device__ inline double lane63(double v)
 {
     const long long b = __double_as_longlong(v);
@@ -340,10 +349,10 @@ __device__ inline float lane63(float v) { return __int_as_float(__builtin_amdgcn
 template <typename T> __device__ inline T wave_sum(T v)
 {
     using namespace wave_detail;
-    v += dpp<0xB1, 0xF>(v);   // quad_perm [1, 0, 3, 2]
-    v += dpp<0x4E, 0xF>(v);   // quad_perm [2, 3, 0, 1]
-    v += dpp<0x141, 0xF>(v);  // row_half_mirror
-    v += dpp<0x140, 0xF>(v);  // row_mirror
+    v += row<0xB1>(v);        // quad_perm [1, 0, 3, 2]
+    v += row<0x4E>(v);        // quad_perm [2, 3, 0, 1]
+    v += row<0x141>(v);       // row_half_mirror
+    v += row<0x140>(v);       // row_mirror
     v += dpp<0x142, 0xA>(v);  // row_bcast:15 into rows 1 and 3
     v += dpp<0x143, 0xC>(v);  // row_bcast:31 into rows 2 and 3
     return lane63(v);

@@ -361,35 +361,51 @@ template <typename T> struct Clover {
     const cpx<T>* c;
 };
 
-// o += C(x) p for site s
-template <typename T> __device__ inline void clover_add(const Clover<T>& C, long s, const spinor<T>& p, spinor<T>& o)
+// the packed entries of the chirality block h (spins 2h, 2h + 1) of site s
+template <typename T> __device__ inline void clover_load(const Clover<T>& C, long s, int h, cpx<T> (&e)[18])
+{
+#pragma unroll
+    for (int q = 0; q < 18; ++q)
+        e[q] = ld(C.c, toff<cpx<T>>(s, 18 * h + q, kCloverComp));
+}
+// w += C_h v from the packed entries
+template <typename T>
+__device__ inline void clover_mul(const cpx<T> (&e)[18], const cpx<T> (&v)[6], cpx<T> (&w)[6])
+{
+#pragma unroll
+    for (int i = 0; i < 6; ++i) {
+        const T d = (i & 1) ? e[i / 2].im : e[i / 2].re;
+        w[i] = cpx<T>{fmadd(d, v[i].re, w[i].re), fmadd(d, v[i].im, w[i].im)};
+    }
+    int q = 3;
+#pragma unroll
+    for (int i = 0; i < 6; ++i)
+#pragma unroll
+        for (int j = i + 1; j < 6; ++j, ++q) {
+            w[i] = cfma(e[q], v[j], w[i]);         // C_ij v_j
+            w[j] = cfma(conjg(e[q]), v[i], w[j]);  // C_ji v_i = conj(C_ij) v_i
+        }
+}
+
+// o += f C(x) p for site s
+template <typename T>
+__device__ inline void clover_add(const Clover<T>& C, long s, const spinor<T>& p, spinor<T>& o, T f = T(1))
 {
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-        cpx<T> e[18];
-#pragma unroll
-        for (int q = 0; q < 18; ++q)
-            e[q] = ld(C.c, toff<cpx<T>>(s, 18 * h + q, kCloverComp));
         cpx<T> v[6], w[6];
 #pragma unroll
-        for (int i = 0; i < 6; ++i)
-            v[i] = p.s[2 * h + i / 3].c[i % 3];
-#pragma unroll
         for (int i = 0; i < 6; ++i) {
-            const T d = (i & 1) ? e[i / 2].im : e[i / 2].re;
-            w[i] = cpx<T>{d * v[i].re, d * v[i].im};
+            const cpx<T> x = p.s[2 * h + i / 3].c[i % 3];
+            v[i] = f == T(1) ? x : f * x;
+            w[i] = o.s[2 * h + i / 3].c[i % 3];
         }
-        int q = 3;
+        cpx<T> e[18];
+        clover_load(C, s, h, e);
+        clover_mul(e, v, w);
 #pragma unroll
         for (int i = 0; i < 6; ++i)
-#pragma unroll
-            for (int j = i + 1; j < 6; ++j, ++q) {
-                w[i] += e[q] * v[j];               // C_ij v_j
-                w[j] += cmul_conj(e[q], v[i]);     // C_ji v_i = conj(C_ij) v_i
-            }
-#pragma unroll
-        for (int i = 0; i < 6; ++i)
-            o.s[2 * h + i / 3].c[i % 3] += w[i];
+            o.s[2 * h + i / 3].c[i % 3] = w[i];
     }
 }
 

@@ -3,24 +3,27 @@
 // full operator, runs nmr minimal-residual steps on the block operator
 // D_Lambda (Dirichlet walls) and adds the block solution to psi.
 //
-// Mapping: one workgroup per Schwarz block. The generic kernel (k_sap, any
-// block size, FP64 or FP32) and the several-field kernel (k_sap_rl, blocks of
-// at most 256 sites) run one thread per site (blockDim = |block| rounded up to
-// a wavefront; spare lanes only join the reductions); the one-field kernel
-// (k_sap_pair) runs two lanes per site. The residual reads the neighbour
+// Mapping: one workgroup per Schwarz block. The residual reads the neighbour
 // spinors across the block faces directly from global memory; those sites
 // belong to blocks of the other colour, which no workgroup of this launch
 // writes, so there is no race. Inside the MR loop the current residue r is
-// exchanged through LDS (12 planes x |block|), and the two block reductions
-// per step use DPP wavefront sums plus one LDS pass. k_sap reads the links
-// through L1/L2 at every MR step; k_sap_rl and k_sap_pair keep them from the
-// residual on.
+// exchanged through LDS (12 planes x |block|), and the block reductions of a
+// step use DPP wavefront sums plus one LDS pass. Every kernel reads the links
+// once per sweep and keeps them on the chip for the MR steps (spare lanes of
+// the last wavefront only join the reductions):
+//   k_sap_rl    FP32, one lane per site
+//   k_sap_cl    the same with the clover term or antiperiodic time
+//   k_sap_pair  two lanes per site: FP64 blocks of up to 256 sites, and FP32
+//               single fields on lattices with few blocks
+//   k_sap_big   FP64 blocks of 257..512 sites, one lane per site and link
 //
 // init (first cycle, where psi starts at zero): 2 = psi is zero everywhere
 // (colour 0: the residue is rho, no hops, no reads of psi), 1 = psi is zero on
 // the sweep's own blocks (colour 1: only the neighbours' values are read).
 // out64 (optional, last cycle of an FP32 sweep): the block's new psi is also
 // written in FP64 there, so no conversion pass follows.
+#include <type_traits>
+
 #include "hop.h"
 
 namespace dfl {
@@ -45,6 +48,37 @@ template <typename T> __device__ inline void scale_spinor(spinor<T>& p, T f)
             p.s[al].c[a] = cpx<T>{p.s[al].c[a].re * f, p.s[al].c[a].im * f};
 }
 
+// (q, r) and ||q||^2 of the block from every lane's shares, in a fixed order;
+// NW: wavefronts of the workgroup (0: nw, at run time). red: LDS.
+template <int NW>
+__device__ inline void block_products(double& re, double& im, double& qq, double (*red)[8], int lane, int wid, int nw)
+{
+    re = wave_sum(re);
+    im = wave_sum(im);
+    qq = wave_sum(qq);
+    if (lane == 0) {
+        red[0][wid] = re;
+        red[1][wid] = im;
+        red[2][wid] = qq;
+    }
+    __syncthreads();
+    re = im = qq = 0.0;
+    if (NW > 0) {
+#pragma unroll
+        for (int w = 0; w < NW; ++w) {
+            re += red[0][w];
+            im += red[1][w];
+            qq += red[2][w];
+        }
+    } else {
+        for (int w = 0; w < nw; ++w) {
+            re += red[0][w];
+            im += red[1][w];
+            qq += red[2][w];
+        }
+    }
+}
+
 template <typename T> __device__ inline void store_spinor_f64(c64* __restrict__ f, long V, long s, const spinor<T>& p)
 {
     spinor<double> d;
@@ -54,33 +88,6 @@ template <typename T> __device__ inline void store_spinor_f64(c64* __restrict__ 
         for (int a = 0; a < 3; ++a)
             d.s[al].c[a] = c64{(double)p.s[al].c[a].re, (double)p.s[al].c[a].im};
     store_spinor(f, V, s, d);
-}
-
-// D_Lambda hops of one site: neighbours inside the Schwarz block come from
-// the LDS copy of the residue; hops leaving the block are dropped.
-template <typename T, typename L>
-__device__ inline void block_hops(const Geom& g, const SapGeom& sg, const L& U, const cpx<T>* lr, int t,
-                                  const int yl[4], long s, const int n[4], const int y[4], spinor<T>& acc)
-{
-    const int V = sg.Vsb;
-#pragma unroll 1
-    for (int h = 0; h < 8; ++h) {
-        const int mu = h >> 1;
-        const int step = (h & 1) ? -1 : +1;
-        if (step > 0 ? yl[mu] + 1 >= sg.sb[mu] : yl[mu] == 0)
-            continue;
-        const int tn = t + step * sg.lstr[mu];
-        spinor<T> p;
-#pragma unroll
-        for (int al = 0; al < 4; ++al)
-#pragma unroll
-            for (int a = 0; a < 3; ++a)
-                p.s[al].c[a] = lr[(3 * al + a) * V + tn];
-        if (step > 0)
-            hop_fwd_rt(mu, load_link(U, mu, s), p, acc);
-        else
-            hop_bwd_rt(mu, load_link(U, mu, site_step(g, s, n, y, mu, -1)), p, acc);
-    }
 }
 
 // the eight hops of the full operator at one site, neighbours from global
@@ -104,152 +111,6 @@ __device__ inline void full_hops(const Geom& g, const SapGeom& sg, const L& U, c
             hop_fwd_rt(mu, load_link(U, mu, s), p, acc);
         else
             hop_bwd_rt(mu, load_link(U, mu, tn), p, acc);
-    }
-}
-
-template <typename T, typename L, bool CLV>
-__global__ __launch_bounds__(512) void k_sap(Geom g, SapGeom sg, L U, const cpx<T>* __restrict__ rho,
-                                             const double* __restrict__ rho_nrm2, cpx<T>* __restrict__ psi, T diag,
-                                             int nmr, int colour, int nrhs, int init, c64* __restrict__ out64,
-                                             Clover<T> C)
-{
-    // workgroup -> (block of this colour, right-hand side), right-hand sides fastest
-    const T rs = rho_scale<T>(rho_nrm2, blockIdx.x % nrhs);
-    rho += (long)(blockIdx.x % nrhs) * 12 * g.V;
-    psi += (long)(blockIdx.x % nrhs) * 12 * g.V;
-    if (out64)
-        out64 += (long)(blockIdx.x % nrhs) * 12 * g.V;
-    extern __shared__ char smem_raw[];
-    cpx<T>* lr = reinterpret_cast<cpx<T>*>(smem_raw);
-    __shared__ double red[3][8];
-
-    const int t = threadIdx.x;
-    const bool active = t < sg.Vsb;
-    const int lane = t & 63, wid = t >> 6, nw = blockDim.x >> 6;
-
-    // k-th block of this colour -> block coordinates m
-    int k = blockIdx.x / nrhs;
-    int half = sg.nsb[3] / 2;
-    int m[4];
-    int j = k % half;
-    int rest = k / half;
-    m[2] = rest % sg.nsb[2];
-    rest /= sg.nsb[2];
-    m[1] = rest % sg.nsb[1];
-    m[0] = rest / sg.nsb[1];
-    m[3] = 2 * j + ((colour + m[0] + m[1] + m[2]) & 1);
-
-    int yl[4] = {0, 0, 0, 0};
-    int n[4] = {0, 0, 0, 0}, y[4] = {0, 0, 0, 0};
-    long s = 0;
-    if (active) {
-        int tt = t;
-        yl[3] = tt % sg.sb[3];
-        tt /= sg.sb[3];
-        yl[2] = tt % sg.sb[2];
-        tt /= sg.sb[2];
-        yl[1] = tt % sg.sb[1];
-        yl[0] = tt / sg.sb[1];
-        for (int mu = 0; mu < 4; ++mu) {
-            int x = m[mu] * sg.sb[mu] + yl[mu];
-            n[mu] = x / g.b[mu];
-            y[mu] = x - n[mu] * g.b[mu];
-        }
-        s = site_compose(g, n, y);
-    }
-
-    // residual with the full operator
-    spinor<T> r, xs;
-    zero(r);
-    zero(xs);
-    if (active) {
-        spinor<T> acc, self;
-        zero(acc);
-        zero(self);
-        if (init < 2)
-            full_hops(g, sg, U, psi, s, n, y, yl, init == 1, acc);
-        if (init == 0)
-            self = load_spinor(psi, g.V, s);
-        spinor<T> d = finish(self, acc, diag);
-        if constexpr (CLV)
-            if (init == 0)
-                clover_add(C, s, self, d);
-        spinor<T> b = load_spinor(rho, g.V, s);
-        if (rho_nrm2)
-            scale_spinor(b, rs);
-#pragma unroll
-        for (int al = 0; al < 4; ++al)
-            r.s[al] = b.s[al] - d.s[al];
-    }
-
-    for (int step = 0; step < nmr; ++step) {
-        if (active) {
-#pragma unroll
-            for (int al = 0; al < 4; ++al)
-#pragma unroll
-                for (int a = 0; a < 3; ++a)
-                    lr[(3 * al + a) * sg.Vsb + t] = r.s[al].c[a];
-        }
-        __syncthreads();
-        spinor<T> q;
-        zero(q);
-        double qr_re = 0.0, qr_im = 0.0, qq = 0.0;
-        if (active) {
-            spinor<T> acc;
-            zero(acc);
-            block_hops(g, sg, U, lr, t, yl, s, n, y, acc);
-            q = finish(r, acc, diag);
-            if constexpr (CLV)
-                clover_add(C, s, r, q);
-#pragma unroll
-            for (int al = 0; al < 4; ++al)
-#pragma unroll
-                for (int a = 0; a < 3; ++a) {
-                    double qa = (double)q.s[al].c[a].re, qb = (double)q.s[al].c[a].im;
-                    double ra = (double)r.s[al].c[a].re, rb = (double)r.s[al].c[a].im;
-                    qr_re += qa * ra + qb * rb;
-                    qr_im += qa * rb - qb * ra;
-                    qq += qa * qa + qb * qb;
-                }
-        }
-        qr_re = wave_sum(qr_re);
-        qr_im = wave_sum(qr_im);
-        qq = wave_sum(qq);
-        if (lane == 0) {
-            red[0][wid] = qr_re;
-            red[1][wid] = qr_im;
-            red[2][wid] = qq;
-        }
-        __syncthreads();
-        double sre = 0.0, sim = 0.0, sqq = 0.0;
-        for (int w = 0; w < nw; ++w) {
-            sre += red[0][w];
-            sim += red[1][w];
-            sqq += red[2][w];
-        }
-        if (!(sqq > 0.0))
-            break;  // zero residue on this block: uniform across the workgroup
-        cpx<T> alpha{(T)(sre / sqq), (T)(sim / sqq)};
-#pragma unroll
-        for (int al = 0; al < 4; ++al)
-#pragma unroll
-            for (int a = 0; a < 3; ++a) {
-                xs.s[al].c[a] += alpha * r.s[al].c[a];
-                r.s[al].c[a] -= alpha * q.s[al].c[a];
-            }
-    }
-
-    if (active) {
-        spinor<T> p;
-        zero(p);
-        if (init == 0)
-            p = load_spinor(psi, g.V, s);
-#pragma unroll
-        for (int al = 0; al < 4; ++al)
-            p.s[al] += xs.s[al];
-        store_spinor(psi, g.V, s, p);
-        if (out64)
-            store_spinor_f64(out64, g.V, s, p);
     }
 }
 
@@ -292,6 +153,10 @@ template <typename L> __device__ inline su3<float> expand(const Link2<L>& l)
     return u;
 }
 
+// Makes v's value unknown to the compiler at this point, so that what is computed
+// from it inside a loop is not moved out of the loop (and then spilled).
+template <typename T> __device__ inline void pin(cpx<T>& v) { asm volatile("" : "+v"(v.re), "+v"(v.im)); }
+
 // the link from its two register rows and its third row in LDS (entry b at l3[b * stride])
 template <typename L> __device__ inline su3<float> expand_lds(const Link2<L>& l, const c32* l3, int stride)
 {
@@ -309,9 +174,10 @@ template <typename L> __device__ inline su3<float> expand_lds(const Link2<L>& l,
 
 // B4: 4^4 blocks, whose extents, in-block strides and LDS plane size are
 // compile-time constants (every LDS access of a hop is then an immediate
-// offset from the thread's own address).
+// offset from the thread's own address). Blocks of 257..512 sites run one per
+// CU.
 template <typename L, bool B4>
-__global__ __launch_bounds__(256, 2) void k_sap_rl(Geom g, SapGeom sg, L U, const c32* __restrict__ rho,
+__global__ __launch_bounds__(B4 ? 256 : 512, 2) void k_sap_rl(Geom g, SapGeom sg, L U, const c32* __restrict__ rho,
                                                const double* __restrict__ rho_nrm2, c32* __restrict__ psi,
                                                float diag, int nmr, int colour, int nrhs, int init,
                                                c64* __restrict__ out64)
@@ -417,18 +283,20 @@ __global__ __launch_bounds__(256, 2) void k_sap_rl(Geom g, SapGeom sg, L U, cons
                 for (int a = 0; a < 3; ++a)
                     lr[(3 * al + a) * Vsb + t] = r.s[al].c[a];
         }
-        __syncthreads();
         // acc = -2 D_Lambda r: it starts at -2 diag r and collects the inside
         // hops, so the MR coefficient follows from it without forming D_Lambda r
         spinor<float> acc;
-        // the lane's products summed in FP32, the block sums in FP64
-        float fr_re = 0.0f, fr_im = 0.0f, fqq = 0.0f;
         if (active) {
 #pragma unroll
             for (int al = 0; al < 4; ++al)
 #pragma unroll
                 for (int a = 0; a < 3; ++a)
                     acc.s[al].c[a] = cpx<float>{-2.0f * diag * r.s[al].c[a].re, -2.0f * diag * r.s[al].c[a].im};
+        }
+        __syncthreads();
+        // the lane's products summed in FP32, the block sums in FP64
+        float fr_re = 0.0f, fr_im = 0.0f, fqq = 0.0f;
+        if (active) {
 #pragma unroll
             for (int h = 0; h < 8; ++h) {
                 const int mu = h >> 1;
@@ -461,26 +329,14 @@ __global__ __launch_bounds__(256, 2) void k_sap_rl(Geom g, SapGeom sg, L U, cons
                     fqq = fmadd(qb, qb, fmadd(qa, qa, fqq));
                 }
         }
-        const double qr_re = wave_sum((double)fr_re);
-        const double qr_im = wave_sum((double)fr_im);
-        const double qq = wave_sum((double)fqq);
-        if (lane == 0) {
-            red[0][wid] = qr_re;
-            red[1][wid] = qr_im;
-            red[2][wid] = qq;
-        }
-        __syncthreads();
-        double sre = 0.0, sim = 0.0, sqq = 0.0;
-        for (int w = 0; w < nw; ++w) {
-            sre += red[0][w];
-            sim += red[1][w];
-            sqq += red[2][w];
-        }
+        double sre = fr_re, sim = fr_im, sqq = fqq;
+        block_products<B4 ? 4 : 0>(sre, sim, sqq, red, lane, wid, nw);
         if (!(sqq > 0.0))
             break;  // zero residue on this block: uniform across the workgroup
+        const double inv = -2.0 / sqq;
         // with q = D_Lambda r = -acc / 2: alpha = (q, r) / ||q||^2 = -2 (acc, r) / ||acc||^2,
         // x += alpha r, r -= alpha q = r + (alpha / 2) acc
-        const c32 alpha{(float)(-2.0 * sre / sqq), (float)(-2.0 * sim / sqq)};
+        const c32 alpha{(float)(inv * sre), (float)(inv * sim)};
         const c32 half{0.5f * alpha.re, 0.5f * alpha.im};
 #pragma unroll
         for (int al = 0; al < 4; ++al)
@@ -505,111 +361,401 @@ __global__ __launch_bounds__(256, 2) void k_sap_rl(Geom g, SapGeom sg, L U, cons
     }
 }
 
-// ---------------------------------------------------------------- lane pairs
-//
-// FP32 sweep with two lanes per site (adjacent lanes 2i, 2i+1). The even lane
-// takes the four forward hops, (1 - g_mu) U_mu(x) psi(x + mu), the odd lane
-// the four backward ones, (1 + g_mu) U_mu(x - mu)^+ psi(x - mu). The odd lane
-// holds the adjoint of its link, and its spin projection and reconstruction
-// equal the forward ones with the sign of every e_mu term flipped (see the
-// projector identities in hop.h), so both lanes run one instruction stream
-// with the sign as an FMA operand. The pair's partial sums are combined by
-// one cross-lane add per real, and each lane owns two of the site's four spin
-// components of the residue, the MR direction and the block solution
-// (even: spins 0 and 1, odd: 2 and 3). Four links of 3x3 per lane (72 VGPRs)
-// leave room for two wavefronts per SIMD.
-
-// x + s*y, x + s*i*y and x - s*i*y with the lane's sign s
-__device__ inline c32 add_s(c32 x, float sg, c32 y) { return {fmaf(sg, y.re, x.re), fmaf(sg, y.im, x.im)}; }
-__device__ inline c32 add_si(c32 x, float sg, c32 y) { return {fmaf(-sg, y.im, x.re), fmaf(sg, y.re, x.im)}; }
-__device__ inline c32 add_smi(c32 x, float sg, c32 y) { return {fmaf(sg, y.im, x.re), fmaf(-sg, y.re, x.im)}; }
-
-// acc += forward (sg = +1, w = U_mu(x)) or backward (sg = -1, w = U_mu(x-mu)^+) hop of p
-template <int MU>
-__device__ inline void hop_pair(const su3<float>& w, const spinor<float>& p, float sg, spinor<float>& acc)
+// The same for the clover term and antiperiodic time. Beside the links the 36
+// clover entries of a site fit neither registers nor LDS, and re-reading them
+// at every MR step is paid in exposed latency (192 us per sweep of one field on
+// 48 x 24^3, 95 without the term). So the residue lives in LDS alone, the block
+// solution too, the third link rows are rebuilt for every use, and of every
+// chirality block's entries kLC are in LDS, the others in registers: one read
+// of everything per sweep, two blocks of 256 sites per CU: 139 us.
+constexpr int kLC = 5;  // LDS entries of a chirality block (of 18)
+template <typename L, bool B4>
+__global__ __launch_bounds__(B4 ? 256 : 512, 2) void k_sap_cl(Geom g, SapGeom sg, L U, const c32* __restrict__ rho,
+                                                              const double* __restrict__ rho_nrm2,
+                                                              c32* __restrict__ psi, float diag, int nmr, int colour,
+                                                              int nrhs, int init, c64* __restrict__ out64,
+                                                              Clover<float> C)
 {
-    cvec3<float> h0, h1;
+    const int Vsb = B4 ? 256 : sg.Vsb;
+    int sbl[4], lst[4];
 #pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        if (MU == 0) {
-            h0.c[a] = add_s(p.s[0].c[a], sg, p.s[2].c[a]);
-            h1.c[a] = add_s(p.s[1].c[a], sg, p.s[3].c[a]);
-        } else if (MU == 1) {
-            h0.c[a] = add_si(p.s[0].c[a], sg, p.s[3].c[a]);
-            h1.c[a] = add_si(p.s[1].c[a], sg, p.s[2].c[a]);
-        } else if (MU == 2) {
-            h0.c[a] = add_s(p.s[0].c[a], sg, p.s[3].c[a]);
-            h1.c[a] = add_s(p.s[1].c[a], -sg, p.s[2].c[a]);
-        } else {
-            h0.c[a] = add_si(p.s[0].c[a], sg, p.s[2].c[a]);
-            h1.c[a] = add_smi(p.s[1].c[a], sg, p.s[3].c[a]);
-        }
+    for (int mu = 0; mu < 4; ++mu) {
+        sbl[mu] = B4 ? 4 : sg.sb[mu];
+        lst[mu] = B4 ? (64 >> (2 * mu)) : sg.lstr[mu];
     }
-    cvec3<float> w0 = mul(w, h0);
-    cvec3<float> w1 = mul(w, h1);
-    acc.s[0] += w0;
-    acc.s[1] += w1;
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        if (MU == 0) {
-            acc.s[2].c[a] = add_s(acc.s[2].c[a], sg, w0.c[a]);
-            acc.s[3].c[a] = add_s(acc.s[3].c[a], sg, w1.c[a]);
-        } else if (MU == 1) {
-            acc.s[2].c[a] = add_smi(acc.s[2].c[a], sg, w1.c[a]);
-            acc.s[3].c[a] = add_smi(acc.s[3].c[a], sg, w0.c[a]);
-        } else if (MU == 2) {
-            acc.s[2].c[a] = add_s(acc.s[2].c[a], -sg, w1.c[a]);
-            acc.s[3].c[a] = add_s(acc.s[3].c[a], sg, w0.c[a]);
-        } else {
-            acc.s[2].c[a] = add_smi(acc.s[2].c[a], sg, w0.c[a]);
-            acc.s[3].c[a] = add_si(acc.s[3].c[a], sg, w1.c[a]);
-        }
-    }
-}
-
-// v + (v of the other lane of the pair); every lane of the wavefront must take part
-__device__ inline float pair_sum(float v)
-{
-    // DPP quad_perm [1, 0, 3, 2]: swap adjacent lanes
-    int o = __builtin_amdgcn_update_dpp(0, __float_as_int(v), 0xB1, 0xF, 0xF, false);
-    return v + __int_as_float(o);
-}
-
-// the lane's link for direction mu: U_mu(x) (forward lane) or U_mu(x - mu)^+ (backward lane)
-template <typename L> __device__ inline su3<float> pair_link(const L& U, int mu, long site, bool bwd)
-{
-    su3<float> u = expand(load_link2(U, mu, site));
-    su3<float> w;
-#pragma unroll
-    for (int a = 0; a < 3; ++a)
-#pragma unroll
-        for (int b = 0; b < 3; ++b) {
-            const c32 x = u.m[a][b], y = u.m[b][a];
-            w.m[a][b] = bwd ? c32{y.re, -y.im} : x;
-        }
-    return w;
-}
-
-template <typename L>
-__global__ __launch_bounds__(512, 1) void k_sap_pair(Geom g, SapGeom sg, L U, const c32* __restrict__ rho,
-                                                     const double* __restrict__ rho_nrm2, c32* __restrict__ psi,
-                                                     float diag, int nmr, int colour, int nrhs, int init,
-                                                     c64* __restrict__ out64)
-{
+    // workgroup -> (block of this colour, right-hand side), right-hand sides fastest
     const float rs = rho_scale<float>(rho_nrm2, blockIdx.x % nrhs);
     rho += (long)(blockIdx.x % nrhs) * 12 * g.V;
     psi += (long)(blockIdx.x % nrhs) * 12 * g.V;
     if (out64)
         out64 += (long)(blockIdx.x % nrhs) * 12 * g.V;
     extern __shared__ char smem_raw[];
-    c32* lr = reinterpret_cast<c32*>(smem_raw);
+    c32* lr = reinterpret_cast<c32*>(smem_raw);  // residue
+    c32* lx = lr + 12 * Vsb;                     // block solution
+    c32* lc = lx + 12 * Vsb;                     // clover entries, (kLC h + q) * Vsb + site
     __shared__ double red[3][8];
 
     const int t = threadIdx.x;
-    const int ts = t >> 1;           // site in the block
-    const int hb = t & 1;            // 0: forward hops, spins 0-1; 1: backward hops, spins 2-3
-    const float sgn = hb ? -1.0f : 1.0f;
-    const bool active = ts < sg.Vsb;  // both lanes of a pair agree
+    const bool active = t < Vsb;
+    const int lane = t & 63, wid = t >> 6, nw = blockDim.x >> 6;
+
+    int k = blockIdx.x / nrhs;
+    int half = sg.nsb[3] / 2;
+    int m[4];
+    int j = k % half;
+    int rest = k / half;
+    m[2] = rest % sg.nsb[2];
+    rest /= sg.nsb[2];
+    m[1] = rest % sg.nsb[1];
+    m[0] = rest / sg.nsb[1];
+    m[3] = 2 * j + ((colour + m[0] + m[1] + m[2]) & 1);
+
+    int yl[4] = {0, 0, 0, 0};
+    int n[4] = {0, 0, 0, 0}, y[4] = {0, 0, 0, 0};
+    long s = 0;
+    if (active) {
+        int tt = t;
+        yl[3] = tt % sbl[3];
+        tt /= sbl[3];
+        yl[2] = tt % sbl[2];
+        tt /= sbl[2];
+        yl[1] = tt % sbl[1];
+        yl[0] = tt / sbl[1];
+        for (int mu = 0; mu < 4; ++mu) {
+            int x = m[mu] * sbl[mu] + yl[mu];
+            n[mu] = x / g.b[mu];
+            y[mu] = x - n[mu] * g.b[mu];
+        }
+        s = site_compose(g, n, y);
+    }
+    const bool clv = C.c != nullptr;
+    c32 cl[2][18 - kLC];
+    // o += f C p at this site
+    auto site_clover = [&](float f, const spinor<float>& p, spinor<float>& o) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            c32 e[18], v[6], w[6];
+#pragma unroll
+            for (int q = 0; q < 18; ++q)
+                e[q] = q < kLC ? lc[(kLC * h + q) * Vsb + t] : cl[h][q < kLC ? 0 : q - kLC];
+#pragma unroll
+            for (int i = 0; i < 6; ++i) {
+                v[i] = f * p.s[2 * h + i / 3].c[i % 3];
+                w[i] = o.s[2 * h + i / 3].c[i % 3];
+            }
+            clover_mul(e, v, w);
+#pragma unroll
+            for (int i = 0; i < 6; ++i)
+                o.s[2 * h + i / 3].c[i % 3] = w[i];
+        }
+    };
+
+    // residual with the full operator; the links are kept for the MR steps
+    Link2<L> lk[8];
+    if (active) {
+        spinor<float> acc, self;
+        zero(acc);
+        zero(self);
+#pragma unroll
+        for (int h = 0; h < 8; ++h) {
+            const int mu = h >> 1;
+            const int step = (h & 1) ? -1 : +1;
+            long tn = site_step(g, s, n, y, mu, step);
+            lk[h] = load_link2(U, mu, step > 0 ? s : tn);
+            const bool inside = step > 0 ? yl[mu] + 1 < sbl[mu] : yl[mu] > 0;
+            if (init == 0 || (init == 1 && !inside)) {
+                spinor<float> p = load_spinor(psi, g.V, tn);
+                if (mu == 0 && crosses_time(g, n, y, mu, step))
+                    negate(p);
+                if (step > 0)
+                    hop_fwd_rt(mu, expand(lk[h]), p, acc);
+                else
+                    hop_bwd_rt(mu, expand(lk[h]), p, acc);
+            }
+            if (h & 1)
+                asm volatile("" ::: "memory");  // two hops' loads in flight at a time
+        }
+        if (clv) {
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                for (int q = 0; q < 18; ++q) {
+                    const c32 e = ld(C.c, toff<c32>(s, 18 * h + q, kCloverComp));
+                    if (q < kLC)
+                        lc[(kLC * h + q) * Vsb + t] = e;
+                    else
+                        cl[h][q < kLC ? 0 : q - kLC] = e;
+                }
+        }
+        if (init == 0)
+            self = load_spinor(psi, g.V, s);
+        spinor<float> d = finish(self, acc, diag);
+        if (clv && init == 0)
+            site_clover(1.0f, self, d);
+        spinor<float> b = load_spinor(rho, g.V, s);
+        if (rho_nrm2)
+            scale_spinor(b, rs);
+#pragma unroll
+        for (int al = 0; al < 4; ++al)
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+                lr[(3 * al + a) * Vsb + t] = b.s[al].c[a] - d.s[al].c[a];
+                lx[(3 * al + a) * Vsb + t] = c32{0.0f, 0.0f};
+            }
+    }
+
+    for (int stp = 0; stp < nmr; ++stp) {
+        // acc = -2 D_Lambda r: it starts at -2 (diag + C) r and collects the inside
+        // hops, so the MR coefficient follows from it without forming D_Lambda r
+        spinor<float> acc;
+        if (active) {
+            spinor<float> r;
+#pragma unroll
+            for (int al = 0; al < 4; ++al)
+#pragma unroll
+                for (int a = 0; a < 3; ++a) {
+                    r.s[al].c[a] = lr[(3 * al + a) * Vsb + t];
+                    acc.s[al].c[a] = -2.0f * diag * r.s[al].c[a];
+                }
+            if (clv)
+                site_clover(-2.0f, r, acc);
+        }
+        __syncthreads();
+        // the lane's products summed in FP32, the block sums in FP64
+        float fr_re = 0.0f, fr_im = 0.0f, fqq = 0.0f;
+        if (active) {
+#pragma unroll
+            for (int h = 0; h < 8; ++h) {
+                const int mu = h >> 1;
+                const int step = (h & 1) ? -1 : +1;
+                if (step > 0 ? yl[mu] + 1 < sbl[mu] : yl[mu] > 0) {
+                    const int tn = t + step * lst[mu];
+                    spinor<float> p;
+#pragma unroll
+                    for (int al = 0; al < 4; ++al)
+#pragma unroll
+                        for (int a = 0; a < 3; ++a)
+                            p.s[al].c[a] = lr[(3 * al + a) * Vsb + tn];
+                    pin(lk[h].e[0]);
+                    pin(lk[h].e[1]);
+                    pin(lk[h].e[2]);
+                    if (step > 0)
+                        hop_fwd_rt(mu, expand(lk[h]), p, acc);
+                    else
+                        hop_bwd_rt(mu, expand(lk[h]), p, acc);
+                }
+                asm volatile("" ::: "memory");
+            }
+#pragma unroll
+            for (int al = 0; al < 4; ++al)
+#pragma unroll
+                for (int a = 0; a < 3; ++a) {
+                    const float qa = acc.s[al].c[a].re, qb = acc.s[al].c[a].im;
+                    const c32 r = lr[(3 * al + a) * Vsb + t];
+                    fr_re = fmadd(qb, r.im, fmadd(qa, r.re, fr_re));
+                    fr_im = fmadd(-qb, r.re, fmadd(qa, r.im, fr_im));
+                    fqq = fmadd(qb, qb, fmadd(qa, qa, fqq));
+                }
+        }
+        double sre = fr_re, sim = fr_im, sqq = fqq;
+        block_products<B4 ? 4 : 0>(sre, sim, sqq, red, lane, wid, nw);
+        if (!(sqq > 0.0))
+            break;  // zero residue on this block: uniform across the workgroup
+        // with q = D_Lambda r = -acc / 2: alpha = (q, r) / ||q||^2 = -2 (acc, r) / ||acc||^2,
+        // x += alpha r, r -= alpha q = r + (alpha / 2) acc
+        const double inv = -2.0 / sqq;
+        const c32 alpha{(float)(inv * sre), (float)(inv * sim)};
+        const c32 half{0.5f * alpha.re, 0.5f * alpha.im};
+        if (active) {
+#pragma unroll
+            for (int al = 0; al < 4; ++al)
+#pragma unroll
+                for (int a = 0; a < 3; ++a) {
+                    const int e = (3 * al + a) * Vsb + t;
+                    const c32 r = lr[e];
+                    lx[e] = cfma(alpha, r, lx[e]);
+                    lr[e] = cfma(half, acc.s[al].c[a], r);
+                }
+        }
+    }
+
+    if (active) {
+#pragma unroll
+        for (int al = 0; al < 4; ++al)
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+                const uint32_t at = toff<c32>(s, 3 * al + a, 12);
+                c32 p = lx[(3 * al + a) * Vsb + t];
+                if (init == 0)
+                    p += ld(psi, at);
+                st(psi, at, p);
+                if (out64)
+                    st(out64, 2 * at, c64{(double)p.re, (double)p.im});
+            }
+    }
+}
+
+// ---------------------------------------------------------------- lane pairs
+//
+// Sweep with two lanes per site (lanes i and i + 32 of a wavefront). The lower
+// lane takes the four forward hops, (1 - g_mu) U_mu(x) psi(x + mu), the upper
+// lane the four backward ones, (1 + g_mu) U_mu(x - mu)^+ psi(x - mu). The upper
+// lane holds the adjoint of its link, and its spin projection and reconstruction
+// equal the forward ones with the sign of every e_mu term flipped (see the
+// projector identities in hop.h), so both lanes run one instruction stream with
+// the sign as an FMA operand. The pair's partial sums are combined by one swap
+// of wavefront halves and one add per real, which leaves each lane the two spin
+// components that it owns of the residue, the MR direction and the block
+// solution (lower: spins 0 and 1, upper: 2 and 3, which is also one chirality
+// block of the clover term each). Neighbouring lanes are neighbouring sites of
+// one kind of hop, so the LDS reads have no bank conflicts.
+// FP32: four links of 3x3 per lane (72 VGPRs). FP64: the links' first two rows
+// (96 VGPRs), the third ones rebuilt for every use; the residue and the block
+// solution live in LDS alone, and so do kPC of the lane's 18 clover entries.
+// Both leave room for two wavefronts per SIMD, one block of 256 sites per CU.
+// FP64, 4^4 blocks: 20 fields on 16^4 360 us per sweep (links re-read at every
+// step: 579), one field on 8^4 29 us (61), with the clover term on 32 x 16^3
+// 58 us. The vector units are busy half of the time, the rest is the latency of
+// the LDS reads, barriers and first loads at two wavefronts per SIMD.
+
+// x + s*y, x + s*i*y and x - s*i*y with the lane's sign s
+template <typename T> __device__ inline cpx<T> add_s(cpx<T> x, T sg, cpx<T> y)
+{
+    return {fmadd(sg, y.re, x.re), fmadd(sg, y.im, x.im)};
+}
+template <typename T> __device__ inline cpx<T> add_si(cpx<T> x, T sg, cpx<T> y)
+{
+    return {fmadd(-sg, y.im, x.re), fmadd(sg, y.re, x.im)};
+}
+template <typename T> __device__ inline cpx<T> add_smi(cpx<T> x, T sg, cpx<T> y)
+{
+    return {fmadd(sg, y.im, x.re), fmadd(-sg, y.re, x.im)};
+}
+
+// the projected colour vector K (h_K of hop.h with the lane's sign) of the
+// neighbour whose component (spin, colour) is p(3 * spin + colour)
+template <int MU, int K, typename T, typename P> __device__ inline cvec3<T> pair_project(const P& p, T sg)
+{
+    cvec3<T> h;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        const cpx<T> x = p(3 * K + a);
+        if (MU == 0)
+            h.c[a] = add_s(x, sg, p(3 * (2 + K) + a));
+        else if (MU == 1)
+            h.c[a] = add_si(x, sg, p(3 * (3 - K) + a));
+        else if (MU == 2)
+            h.c[a] = add_s(x, K == 0 ? sg : -sg, p(3 * (3 - K) + a));
+        else
+            h.c[a] = K == 0 ? add_si(x, sg, p(3 * 2 + a)) : add_smi(x, sg, p(3 * 3 + a));
+    }
+    return h;
+}
+// acc += the contribution of w = W h_K to all four spins
+template <int MU, int K, typename T> __device__ inline void pair_add(const cvec3<T>& w, T sg, spinor<T>& acc)
+{
+    acc.s[K] += w;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        if (MU == 0)
+            acc.s[2 + K].c[a] = add_s(acc.s[2 + K].c[a], sg, w.c[a]);
+        else if (MU == 1)
+            acc.s[3 - K].c[a] = add_smi(acc.s[3 - K].c[a], sg, w.c[a]);
+        else if (MU == 2)
+            acc.s[3 - K].c[a] = add_s(acc.s[3 - K].c[a], K == 0 ? sg : -sg, w.c[a]);
+        else
+            acc.s[2 + K].c[a] = K == 0 ? add_smi(acc.s[2].c[a], sg, w.c[a]) : add_si(acc.s[3].c[a], sg, w.c[a]);
+    }
+}
+// acc += forward (sg = +1, w = U_mu(x)) or backward (sg = -1, w = U_mu(x-mu)^+)
+// hop. FP64 takes the two colour vectors one after the other, which keeps the
+// live registers below 256.
+template <int MU, typename T, typename P>
+__device__ inline void hop_pair(const su3<T>& w, const P& p, T sg, spinor<T>& acc)
+{
+    if constexpr (sizeof(T) == 8) {
+        pair_add<MU, 0>(mul(w, pair_project<MU, 0, T>(p, sg)), sg, acc);
+        asm volatile("" ::: "memory");
+        pair_add<MU, 1>(mul(w, pair_project<MU, 1, T>(p, sg)), sg, acc);
+        return;
+    }
+    const cvec3<T> h0 = pair_project<MU, 0, T>(p, sg), h1 = pair_project<MU, 1, T>(p, sg);
+    const cvec3<T> w0 = mul(w, h0), w1 = mul(w, h1);
+    pair_add<MU, 0>(w0, sg, acc);
+    pair_add<MU, 1>(w1, sg, acc);
+}
+template <typename T, typename P>
+__device__ inline void hop_pair_rt(int mu, const su3<T>& w, const P& p, T sg, spinor<T>& acc)
+{
+    if (mu == 0) hop_pair<0>(w, p, sg, acc);
+    else if (mu == 1) hop_pair<1>(w, p, sg, acc);
+    else if (mu == 2) hop_pair<2>(w, p, sg, acc);
+    else hop_pair<3>(w, p, sg, acc);
+}
+
+// lo + (lo of the upper lane of the pair) in the lower lanes, hi + (hi of the
+// lower lane) in the upper ones; every lane of the wavefront must take part
+__device__ inline float pair_sum(float lo, float hi)
+{
+    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(lo), __float_as_uint(hi), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+__device__ inline double pair_sum(double lo, double hi)
+{
+    const unsigned long long a = (unsigned long long)__double_as_longlong(lo), b = (unsigned long long)__double_as_longlong(hi);
+    const auto l = __builtin_amdgcn_permlane32_swap((unsigned)a, (unsigned)b, false, false);
+    const auto h = __builtin_amdgcn_permlane32_swap((unsigned)(a >> 32), (unsigned)(b >> 32), false, false);
+    return __longlong_as_double((long long)(((unsigned long long)h[0] << 32) | l[0])) +
+           __longlong_as_double((long long)(((unsigned long long)h[1] << 32) | l[1]));
+}
+
+// the lane's link for direction mu: U_mu(x) (forward lane) or U_mu(x - mu)^+ (backward lane)
+template <typename L> __device__ inline auto pair_link(const L& U, int mu, long site, bool bwd)
+{
+    auto u = to_link(load_rows(U, mu, site));
+    decltype(u) w;
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+#pragma unroll
+        for (int b = 0; b < 3; ++b) {
+            const auto x = u.m[a][b], y = u.m[b][a];
+            w.m[a][b] = bwd ? conjg(y) : x;
+        }
+    return w;
+}
+
+// IMP: clover term (C.c non-null) and antiperiodic time
+constexpr int kPC = 7;
+template <typename T, typename L, bool B4, bool IMP>
+__global__ __launch_bounds__(512, 1) void k_sap_pair(Geom g, SapGeom sg, L U, const cpx<T>* __restrict__ rho,
+                                                     const double* __restrict__ rho_nrm2, cpx<T>* __restrict__ psi,
+                                                     T diag, int nmr, int colour, int nrhs, int init,
+                                                     c64* __restrict__ out64, Clover<T> C)
+{
+    constexpr bool F64 = sizeof(T) == 8;
+    const int Vsb = B4 ? 256 : sg.Vsb, NT = B4 ? 512 : (int)blockDim.x;
+    int sbl[4], lst[4];
+#pragma unroll
+    for (int mu = 0; mu < 4; ++mu) {
+        sbl[mu] = B4 ? 4 : sg.sb[mu];
+        lst[mu] = B4 ? (64 >> (2 * mu)) : sg.lstr[mu];
+    }
+    const T rs = rho_scale<T>(rho_nrm2, blockIdx.x % nrhs);
+    rho += (long)(blockIdx.x % nrhs) * 12 * g.V;
+    psi += (long)(blockIdx.x % nrhs) * 12 * g.V;
+    if (out64)
+        out64 += (long)(blockIdx.x % nrhs) * 12 * g.V;
+    extern __shared__ char smem_raw[];
+    cpx<T>* lr = reinterpret_cast<cpx<T>*>(smem_raw);
+    cpx<T>* lx = lr + 12 * Vsb;  // FP64: block solution
+    cpx<T>* lc = lx + 12 * Vsb;  // FP64: clover entries, q * blockDim.x + thread
+    __shared__ double red[3][8];
+
+    const int t = threadIdx.x;
+    const int ts = (t >> 6) * 32 + (t & 31);  // site in the block
+    const int hb = (t >> 5) & 1;     // 0: forward hops, spins 0-1; 1: backward hops, spins 2-3
+    const T sgn = hb ? T(-1) : T(1);
+    const bool active = ts < Vsb;  // both lanes of a pair agree
     const int lane = t & 63, wid = t >> 6, nw = blockDim.x >> 6;
 
     int k = blockIdx.x / nrhs;
@@ -628,6 +774,291 @@ __global__ __launch_bounds__(512, 1) void k_sap_pair(Geom g, SapGeom sg, L U, co
     long s = 0;
     if (active) {
         int tt = ts;
+        yl[3] = tt % sbl[3];
+        tt /= sbl[3];
+        yl[2] = tt % sbl[2];
+        tt /= sbl[2];
+        yl[1] = tt % sbl[1];
+        yl[0] = tt / sbl[1];
+        for (int mu = 0; mu < 4; ++mu) {
+            int x = m[mu] * sbl[mu] + yl[mu];
+            n[mu] = x / g.b[mu];
+            y[mu] = x - n[mu] * g.b[mu];
+        }
+        s = site_compose(g, n, y);
+    }
+    // neighbour of this lane's hop inside the block
+    bool inside[4];
+#pragma unroll
+    for (int mu = 0; mu < 4; ++mu)
+        inside[mu] = hb ? yl[mu] > 0 : yl[mu] + 1 < sbl[mu];
+    const int c0 = 6 * hb;  // first owned component (3 * spin + colour)
+
+    // residual with the full operator; the links are kept for the MR steps
+    cpx<T> lk[4][F64 ? 6 : 9];
+    auto link = [&](int mu) {
+        su3<T> w;
+#pragma unroll
+        for (int q = 0; q < (F64 ? 6 : 9); ++q)
+            w.m[q / 3][q % 3] = lk[mu][q];
+        if constexpr (F64) {
+            pin(w.m[0][0]);
+            pin(w.m[0][1]);
+            pin(w.m[0][2]);
+            complete_third_row(w);
+        }
+        return w;
+    };
+    spinor<T> acc;
+    zero(acc);
+    if (active) {
+#pragma unroll
+        for (int mu = 0; mu < 4; ++mu) {
+            long tn = site_step(g, s, n, y, mu, hb ? -1 : +1);
+            const su3<T> w = pair_link(U, mu, hb ? tn : s, hb != 0);
+#pragma unroll
+            for (int q = 0; q < (F64 ? 6 : 9); ++q)
+                lk[mu][q] = w.m[q / 3][q % 3];
+            if (init == 0 || (init == 1 && !inside[mu])) {
+                spinor<T> p = load_spinor(psi, g.V, tn);
+                if (IMP && mu == 0 && crosses_time(g, n, y, mu, hb ? -1 : +1))
+                    negate(p);
+                hop_pair_rt(mu, w, [&](int c) { return p.s[c / 3].c[c % 3]; }, sgn, acc);
+            }
+            if (F64 || (mu & 1))
+                asm volatile("" ::: "memory");  // two hops' loads in flight at a time (FP64: one)
+        }
+    }
+    // this lane's components of the residue and of the block solution
+    cpx<T> rr[F64 ? 1 : 6], xx[F64 ? 1 : 6], q[6];
+    auto r_of = [&](int i) { return F64 ? lr[(c0 + i) * Vsb + ts] : rr[F64 ? 0 : i]; };
+    // the lane's clover block
+    cpx<T> cl[18];
+    const bool clv = IMP && C.c && active;
+    if (clv) {
+        clover_load(C, s, hb, cl);
+        if (F64)
+#pragma unroll
+            for (int e = 0; e < kPC; ++e)
+                lc[e * NT + t] = cl[e];
+    }
+    auto clover = [&](const cpx<T> (&v)[6], cpx<T> (&w)[6]) {
+        cpx<T> e[18];
+#pragma unroll
+        for (int i = 0; i < 18; ++i)
+            e[i] = F64 && i < kPC ? lc[i * NT + t] : cl[i];
+        clover_mul(e, v, w);
+    };
+#pragma unroll
+    for (int i = 0; i < 6; ++i)
+        q[i] = cpx<T>{0, 0};
+    if (clv && init == 0) {
+        cpx<T> self[6];
+#pragma unroll
+        for (int i = 0; i < 6; ++i)
+            self[i] = ld(psi, toff<cpx<T>>(s, c0 + i, 12));
+        clover(self, q);
+    }
+#pragma unroll
+    for (int i = 0; i < 6; ++i) {
+        // pair sum, then the owned half (spins 0-1 or 2-3)
+        const int al = i / 3, a = i % 3;
+        const cpx<T> ao{pair_sum(acc.s[al].c[a].re, acc.s[al + 2].c[a].re),
+                        pair_sum(acc.s[al].c[a].im, acc.s[al + 2].c[a].im)};
+        cpx<T> r = cpx<T>{0, 0};
+        if (active) {
+            cpx<T> self = cpx<T>{0, 0};
+            if (init == 0)
+                self = ld(psi, toff<cpx<T>>(s, c0 + i, 12));
+            cpx<T> b = ld(rho, toff<cpx<T>>(s, c0 + i, 12));
+            if (rho_nrm2)
+                b = cpx<T>{b.re * rs, b.im * rs};
+            if (IMP)
+                b -= q[i];
+            r = cpx<T>{b.re - (diag * self.re - T(0.5) * ao.re), b.im - (diag * self.im - T(0.5) * ao.im)};
+            if (F64) {
+                lr[(c0 + i) * Vsb + ts] = r;
+                lx[(c0 + i) * Vsb + ts] = cpx<T>{0, 0};
+            }
+        }
+        if (!F64) {
+            rr[F64 ? 0 : i] = r;
+            xx[F64 ? 0 : i] = cpx<T>{0, 0};
+        }
+    }
+
+    for (int stp = 0; stp < nmr; ++stp) {
+        // q = (diag + C) r, then - 1/2 of the inside hops
+        if (active) {
+            cpx<T> r[6];
+#pragma unroll
+            for (int i = 0; i < 6; ++i) {
+                r[i] = r_of(i);
+                if (!F64)
+                    lr[(c0 + i) * Vsb + ts] = r[i];
+                q[i] = cpx<T>{diag * r[i].re, diag * r[i].im};
+            }
+            if (clv)
+                clover(r, q);
+        }
+        __syncthreads();
+        zero(acc);
+        if (active) {
+#pragma unroll
+            for (int mu = 0; mu < 4; ++mu) {
+                if (inside[mu]) {
+                    const cpx<T>* pn = lr + ts + (hb ? -lst[mu] : lst[mu]);
+                    hop_pair_rt(mu, link(mu), [&](int c) { return pn[c * Vsb]; }, sgn, acc);
+                }
+                if (F64 || (mu & 1))
+                    asm volatile("" ::: "memory");
+            }
+        }
+        // (spare lanes only join the reductions)
+        if (!active)
+#pragma unroll
+            for (int i = 0; i < 6; ++i)
+                q[i] = cpx<T>{0, 0};
+        // the lane's products summed in its precision, the block sums in FP64
+        T fr_re = 0, fr_im = 0, fqq = 0;
+#pragma unroll
+        for (int i = 0; i < 6; ++i) {
+            const int al = i / 3, a = i % 3;
+            const cpx<T> ao{pair_sum(acc.s[al].c[a].re, acc.s[al + 2].c[a].re),
+                            pair_sum(acc.s[al].c[a].im, acc.s[al + 2].c[a].im)};
+            q[i] = cpx<T>{q[i].re - T(0.5) * ao.re, q[i].im - T(0.5) * ao.im};
+            const T qa = q[i].re, qb = q[i].im;
+            const cpx<T> r = active ? r_of(i) : cpx<T>{0, 0};
+            const T ra = r.re, rb = r.im;
+            fr_re = fmadd(qb, rb, fmadd(qa, ra, fr_re));
+            fr_im = fmadd(-qb, ra, fmadd(qa, rb, fr_im));
+            fqq = fmadd(qb, qb, fmadd(qa, qa, fqq));
+        }
+        double sre = fr_re, sim = fr_im, sqq = fqq;
+        block_products<B4 ? 8 : 0>(sre, sim, sqq, red, lane, wid, nw);
+        if (!(sqq > 0.0))
+            break;  // zero residue on this block: uniform across the workgroup
+        const double inv = 1.0 / sqq;
+        const cpx<T> alpha{(T)(inv * sre), (T)(inv * sim)};
+        if (F64 ? active : true) {
+#pragma unroll
+            for (int i = 0; i < 6; ++i) {
+                const int e = (c0 + i) * Vsb + ts, v = F64 ? 0 : i;
+                const cpx<T> r = r_of(i);
+                if (F64) {
+                    lx[e] = cfma(alpha, r, lx[e]);
+                    lr[e] = cfma(-alpha, q[i], r);
+                } else {
+                    xx[v] = cfma(alpha, r, xx[v]);
+                    rr[v] = cfma(-alpha, q[i], r);
+                }
+            }
+        }
+    }
+
+    if (active) {
+#pragma unroll
+        for (int i = 0; i < 6; ++i) {
+            cpx<T> p = F64 ? lx[(c0 + i) * Vsb + ts] : xx[F64 ? 0 : i];
+            if (init == 0)
+                p += ld(psi, toff<cpx<T>>(s, c0 + i, 12));
+            st(psi, toff<cpx<T>>(s, c0 + i, 12), p);
+            if (out64)
+                st(out64, toff<c64>(s, c0 + i, 12), c64{(double)p.re, (double)p.im});
+        }
+    }
+}
+
+template <typename T, typename L>
+void launch(const Geom& g, const SapGeom& sg, L U, const cpx<T>* rho, const double* rho_nrm2, cpx<T>* psi, T m0,
+            int nmr, int colour, int nrhs, int init, c64* out64, hipStream_t s, const cpx<T>* clov);
+
+// o += f C(x) p, or o = f (dg + C(x)) p with SET, the entries read nine at a time
+// and the chirality blocks one after the other (few live registers)
+template <bool SET, typename T>
+__device__ inline void clover_add_low(const Clover<T>& C, int s, T f, T dg, const spinor<T>& p, spinor<T>& o)
+{
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        cpx<T> e[9], w[6];
+        auto v = [&](int i) { return f * p.s[2 * h + i / 3].c[i % 3]; };
+#pragma unroll
+        for (int i = 0; i < 6; ++i)
+            w[i] = SET ? dg * v(i) : o.s[2 * h + i / 3].c[i % 3];
+#pragma unroll
+        for (int part = 0; part < 2; ++part) {
+#pragma unroll
+            for (int q = 0; q < 9; ++q)
+                e[q] = ld(C.c, toff<cpx<T>>(s, 18 * h + 9 * part + q, kCloverComp));
+            if (part == 0) {
+#pragma unroll
+                for (int i = 0; i < 6; ++i) {
+                    const T d = (i & 1) ? e[i / 2].im : e[i / 2].re;
+                    w[i] = cpx<T>{fmadd(d, v(i).re, w[i].re), fmadd(d, v(i).im, w[i].im)};
+                }
+            }
+            int q = 3;
+#pragma unroll
+            for (int i = 0; i < 6; ++i)
+#pragma unroll
+                for (int j = i + 1; j < 6; ++j, ++q)
+                    if (q / 9 == part) {
+                        w[i] = cfma(e[q % 9], v(j), w[i]);
+                        w[j] = cfma(conjg(e[q % 9]), v(i), w[j]);
+                    }
+            // the next entries' address waits for these products
+            asm volatile("" : "+v"(s), "+v"(w[0].re), "+v"(w[3].re), "+v"(w[5].im));
+        }
+#pragma unroll
+        for (int i = 0; i < 6; ++i)
+            o.s[2 * h + i / 3].c[i % 3] = w[i];
+    }
+}
+
+// FP64 sweep for blocks of more than 256 sites, one lane per site, one block
+// per CU. A site holds its four forward links only (two rows, 96 registers) and
+// works on both ends of each: U_mu(x) times the projected neighbour x + mu for
+// itself, and U_mu(x)^+ times its own projected residue for x + mu, which takes
+// it from LDS; so every link is read once per sweep. The residue is held in
+// registers and mirrored in LDS for the neighbours; the block solution is added
+// to psi step by step, each site's own values only. Bound by latency: one block
+// fills a CU's registers, and its eight wavefronts meet at ten barriers a step.
+// 8 x 4^3 blocks on 32 x 16^3: with the clover term 125 us per sweep where the
+// links re-read at every step took 171; three fields without it 150 (239).
+template <bool IMP>
+__global__ __launch_bounds__(512, 2) void k_sap_big(Geom g, SapGeom sg, Links64 U, const c64* __restrict__ rho,
+                                                    c64* __restrict__ psi, double diag, int nmr, int colour, int nrhs,
+                                                    int init, Clover<double> C)
+{
+    // workgroup -> (block of this colour, right-hand side), right-hand sides fastest
+    rho += (long)(blockIdx.x % nrhs) * 12 * g.V;
+    psi += (long)(blockIdx.x % nrhs) * 12 * g.V;
+    extern __shared__ char smem_raw[];
+    c64* lr = reinterpret_cast<c64*>(smem_raw);  // [12][Vsb] residue
+    c64* ex = lr + 12 * sg.Vsb;                  // [6][Vsb] backward hops on their way to x + mu
+    __shared__ double red[3][8];
+
+    const int t = threadIdx.x;
+    const bool active = t < sg.Vsb;
+    const int lane = t & 63, wid = t >> 6, nw = blockDim.x >> 6;
+
+    // k-th block of this colour -> block coordinates m
+    int k = blockIdx.x / nrhs;
+    int half = sg.nsb[3] / 2;
+    int m[4];
+    int j = k % half;
+    int rest = k / half;
+    m[2] = rest % sg.nsb[2];
+    rest /= sg.nsb[2];
+    m[1] = rest % sg.nsb[1];
+    m[0] = rest / sg.nsb[1];
+    m[3] = 2 * j + ((colour + m[0] + m[1] + m[2]) & 1);
+
+    int yl[4] = {0, 0, 0, 0};
+    int n[4] = {0, 0, 0, 0}, y[4] = {0, 0, 0, 0};
+    long s = 0;
+    if (active) {
+        int tt = t;
         yl[3] = tt % sg.sb[3];
         tt /= sg.sb[3];
         yl[2] = tt % sg.sb[2];
@@ -641,198 +1072,237 @@ __global__ __launch_bounds__(512, 1) void k_sap_pair(Geom g, SapGeom sg, L U, co
         }
         s = site_compose(g, n, y);
     }
-    // neighbour of this lane's hop inside the block
-    bool inside[4];
-#pragma unroll
-    for (int mu = 0; mu < 4; ++mu)
-        inside[mu] = hb ? yl[mu] > 0 : yl[mu] + 1 < sg.sb[mu];
-    const int c0 = 6 * hb;  // first owned component (3 * spin + colour)
+    const bool clv = IMP && C.c != nullptr;
 
-    // residual with the full operator; the links are kept for the MR steps
-    su3<float> lk[4];
-    spinor<float> acc;
-    zero(acc);
+    // residual with the full operator
+    spinor<double> r;
+    zero(r);
     if (active) {
-#pragma unroll
-        for (int mu = 0; mu < 4; ++mu) {
-            long tn = site_step(g, s, n, y, mu, hb ? -1 : +1);
-            lk[mu] = pair_link(U, mu, hb ? tn : s, hb != 0);
-            if (init == 0 || (init == 1 && !inside[mu])) {
-                spinor<float> p = load_spinor(psi, g.V, tn);
-                if (mu == 0) hop_pair<0>(lk[0], p, sgn, acc);
-                else if (mu == 1) hop_pair<1>(lk[1], p, sgn, acc);
-                else if (mu == 2) hop_pair<2>(lk[2], p, sgn, acc);
-                else hop_pair<3>(lk[3], p, sgn, acc);
-            }
-            if (mu & 1)
-                asm volatile("" ::: "memory");  // two hops' loads in flight at a time
-        }
-    }
-    c32 r[6], xs[6];
-#pragma unroll
-    for (int i = 0; i < 6; ++i) {
-        // pair sum, then the owned half (spins 0-1 or 2-3)
-        const int al = i / 3, a = i % 3;
-        c32 lo{pair_sum(acc.s[al].c[a].re), pair_sum(acc.s[al].c[a].im)};
-        c32 hi{pair_sum(acc.s[al + 2].c[a].re), pair_sum(acc.s[al + 2].c[a].im)};
-        c32 ao = hb ? hi : lo;
-        r[i] = c32{0.0f, 0.0f};
-        xs[i] = c32{0.0f, 0.0f};
-        if (active) {
-            c32 self = c32{0.0f, 0.0f};
-            if (init == 0)
-                self = ld(psi, toff<c32>(s, c0 + i, 12));
-            c32 b = ld(rho, toff<c32>(s, c0 + i, 12));
-            if (rho_nrm2)
-                b = c32{b.re * rs, b.im * rs};
-            r[i] = c32{b.re - (diag * self.re - 0.5f * ao.re), b.im - (diag * self.im - 0.5f * ao.im)};
-        }
-    }
-
-    for (int stp = 0; stp < nmr; ++stp) {
-        if (active) {
-#pragma unroll
-            for (int i = 0; i < 6; ++i)
-                lr[(c0 + i) * sg.Vsb + ts] = r[i];
-        }
-        __syncthreads();
+        spinor<double> acc, self;
         zero(acc);
+        zero(self);
+        if (init < 2)
+            full_hops(g, sg, U, psi, s, n, y, yl, init == 1, acc);
+        if (init == 0)
+            self = load_spinor(psi, g.V, s);
+        spinor<double> d = finish(self, acc, diag);
+        if (clv && init == 0)
+            clover_add_low<false>(C, (int)s, 1.0, 0.0, self, d);
+        const spinor<double> b = load_spinor(rho, g.V, s);
+#pragma unroll
+        for (int al = 0; al < 4; ++al)
+            r.s[al] = b.s[al] - d.s[al];
+    }
+    LinkRows<Links64> lk[4];
+    if (active)
+#pragma unroll
+        for (int mu = 0; mu < 4; ++mu)
+            lk[mu] = load_rows(U, mu, s);
+
+    int step = 0;
+    for (; step < nmr; ++step) {
+        // (unknown to the compiler here: addresses are formed in the step, not kept over all of them)
+        int Vsb = sg.Vsb, sc = (int)s;
+        asm volatile("" : "+s"(Vsb), "+v"(sc));
+        // acc = -2 D_Lambda r: it starts at -2 (diag + C) r and collects the inside
+        // hops, so the MR coefficient follows from it without forming D_Lambda r
+        spinor<double> acc;
         if (active) {
 #pragma unroll
-            for (int mu = 0; mu < 4; ++mu) {
-                if (inside[mu]) {
-                    const int tn = ts + (hb ? -sg.lstr[mu] : sg.lstr[mu]);
-                    spinor<float> p;
+            for (int al = 0; al < 4; ++al)
 #pragma unroll
-                    for (int al = 0; al < 4; ++al)
+                for (int a = 0; a < 3; ++a)
+                    lr[(3 * al + a) * Vsb + t] = r.s[al].c[a];
+            if (clv) {
+                clover_add_low<true>(C, sc, -2.0, diag, r, acc);
+            } else {
 #pragma unroll
-                        for (int a = 0; a < 3; ++a)
-                            p.s[al].c[a] = lr[(3 * al + a) * sg.Vsb + tn];
-                    if (mu == 0) hop_pair<0>(lk[0], p, sgn, acc);
-                    else if (mu == 1) hop_pair<1>(lk[1], p, sgn, acc);
-                    else if (mu == 2) hop_pair<2>(lk[2], p, sgn, acc);
-                    else hop_pair<3>(lk[3], p, sgn, acc);
-                }
-                if (mu & 1)
-                    asm volatile("" ::: "memory");
+                for (int al = 0; al < 4; ++al)
+#pragma unroll
+                    for (int a = 0; a < 3; ++a)
+                        acc.s[al].c[a] = -2.0 * diag * r.s[al].c[a];
             }
-        }
-        c32 q[6];
-        // the lane's products summed in FP32, the block sums in FP64
-        float fr_re = 0.0f, fr_im = 0.0f, fqq = 0.0f;
-#pragma unroll
-        for (int i = 0; i < 6; ++i) {
-            const int al = i / 3, a = i % 3;
-            c32 lo{pair_sum(acc.s[al].c[a].re), pair_sum(acc.s[al].c[a].im)};
-            c32 hi{pair_sum(acc.s[al + 2].c[a].re), pair_sum(acc.s[al + 2].c[a].im)};
-            c32 ao = hb ? hi : lo;
-            q[i] = c32{diag * r[i].re - 0.5f * ao.re, diag * r[i].im - 0.5f * ao.im};
-            const float qa = q[i].re, qb = q[i].im;
-            const float ra = r[i].re, rb = r[i].im;
-            fr_re = fmadd(qb, rb, fmadd(qa, ra, fr_re));
-            fr_im = fmadd(-qb, ra, fmadd(qa, rb, fr_im));
-            fqq = fmadd(qb, qb, fmadd(qa, qa, fqq));
-        }
-        const double qr_re = wave_sum((double)fr_re);
-        const double qr_im = wave_sum((double)fr_im);
-        const double qq = wave_sum((double)fqq);
-        if (lane == 0) {
-            red[0][wid] = qr_re;
-            red[1][wid] = qr_im;
-            red[2][wid] = qq;
+        } else {
+            zero(acc);
         }
         __syncthreads();
+        auto direction = [&](auto mu_c) {
+            constexpr int MU = decltype(mu_c)::value;
+            const int lst = sg.lstr[MU];
+            if (active && yl[MU] + 1 < sg.sb[MU]) {
+                pin(lk[MU].e[0]);
+                pin(lk[MU].e[1]);
+                pin(lk[MU].e[2]);
+                const su3<double> u = to_link(lk[MU]);
+#pragma unroll
+                for (int K = 0; K < 2; ++K) {
+                    // (1 + g_mu) r(x) and (1 - g_mu) r(x + mu), their colour vector K
+                    const c64* pn = lr + t + lst;
+                    const cvec3<double> v =
+                        mul_dag(u, K == 0 ? pair_project<MU, 0, double>([&](int c) { return r.s[c / 3].c[c % 3]; }, -1.0)
+                                          : pair_project<MU, 1, double>([&](int c) { return r.s[c / 3].c[c % 3]; }, -1.0));
+#pragma unroll
+                    for (int a = 0; a < 3; ++a)
+                        ex[(3 * K + a) * Vsb + t] = v.c[a];
+                    const auto p = [&](int c) { return pn[c * Vsb]; };
+                    if (K == 0)
+                        pair_add<MU, 0>(mul(u, pair_project<MU, 0, double>(p, 1.0)), 1.0, acc);
+                    else
+                        pair_add<MU, 1>(mul(u, pair_project<MU, 1, double>(p, 1.0)), 1.0, acc);
+                    asm volatile("" ::: "memory");
+                }
+            }
+            __syncthreads();
+            if (active && yl[MU] > 0) {
+                cvec3<double> v0, v1;
+#pragma unroll
+                for (int a = 0; a < 3; ++a) {
+                    v0.c[a] = ex[a * Vsb + t - lst];
+                    v1.c[a] = ex[(3 + a) * Vsb + t - lst];
+                }
+                bwd_add<MU>(v0, v1, acc);
+            }
+            if (MU < 3)
+                __syncthreads();
+        };
+        direction(std::integral_constant<int, 0>());
+        direction(std::integral_constant<int, 1>());
+        direction(std::integral_constant<int, 2>());
+        direction(std::integral_constant<int, 3>());
         double sre = 0.0, sim = 0.0, sqq = 0.0;
-        for (int w = 0; w < nw; ++w) {
-            sre += red[0][w];
-            sim += red[1][w];
-            sqq += red[2][w];
+        if (active) {
+#pragma unroll
+            for (int al = 0; al < 4; ++al)
+#pragma unroll
+                for (int a = 0; a < 3; ++a) {
+                    const double qa = acc.s[al].c[a].re, qb = acc.s[al].c[a].im;
+                    const double ra = r.s[al].c[a].re, rb = r.s[al].c[a].im;
+                    sre = fmadd(qb, rb, fmadd(qa, ra, sre));
+                    sim = fmadd(-qb, ra, fmadd(qa, rb, sim));
+                    sqq = fmadd(qb, qb, fmadd(qa, qa, sqq));
+                }
         }
+        block_products<0>(sre, sim, sqq, red, lane, wid, nw);
         if (!(sqq > 0.0))
             break;  // zero residue on this block: uniform across the workgroup
-        c32 alpha{(float)(sre / sqq), (float)(sim / sqq)};
+        // with q = D_Lambda r = -acc / 2: alpha = (q, r) / ||q||^2 = -2 (acc, r) / ||acc||^2,
+        // psi += alpha r, r -= alpha q = r + (alpha / 2) acc
+        const double inv = -2.0 / sqq;
+        const c64 alpha{inv * sre, inv * sim};
+        const c64 ha{0.5 * alpha.re, 0.5 * alpha.im};
+        if (active) {
 #pragma unroll
-        for (int i = 0; i < 6; ++i) {
-            xs[i] = cfma(alpha, r[i], xs[i]);
-            r[i] = cfma(-alpha, q[i], r[i]);
+            for (int al = 0; al < 4; ++al)
+#pragma unroll
+                for (int a = 0; a < 3; ++a) {
+                    const uint32_t at = toff<c64>(sc, 3 * al + a, 12);
+                    const c64 x = init == 0 || step > 0 ? ld(psi, at) : c64{0.0, 0.0};
+                    st(psi, at, cfma(alpha, r.s[al].c[a], x));
+                    r.s[al].c[a] = cfma(ha, acc.s[al].c[a], r.s[al].c[a]);
+                }
         }
     }
-
-    if (active) {
-#pragma unroll
-        for (int i = 0; i < 6; ++i) {
-            c32 p = xs[i];
-            if (init == 0)
-                p += ld(psi, toff<c32>(s, c0 + i, 12));
-            st(psi, toff<c32>(s, c0 + i, 12), p);
-            if (out64)
-                st(out64, toff<c64>(s, c0 + i, 12), c64{(double)p.re, (double)p.im});
-        }
+    if (active && init > 0 && step == 0) {  // psi was not written before
+        zero(r);
+        store_spinor(psi, g.V, s, r);
     }
 }
 
-template <typename T, typename L>
-void launch(const Geom& g, const SapGeom& sg, L U, const cpx<T>* rho, const double* rho_nrm2, cpx<T>* psi, T m0,
-            int nmr, int colour, int nrhs, int init, c64* out64, hipStream_t s, const cpx<T>* clov);
+inline bool is_b4(const SapGeom& sg) { return sg.sb[0] == 4 && sg.sb[1] == 4 && sg.sb[2] == 4 && sg.sb[3] == 4; }
 
-// Blocks of up to 256 sites: links in registers. One field on lattices whose
-// colours hold few blocks per CU (sg.one_rl == 0): lane pairs, one block per
-// CU at two wavefronts per SIMD (16^4 and 32 x 16^3 with 4^4 blocks: 11%
-// faster than one lane per site); several fields, or one field with many
-// blocks per colour: one lane per site, two blocks per CU (16 fields on 16^4:
-// 12% faster than the generic kernel at three blocks per CU, which re-reads
-// the links every MR step, and 28% faster than lane pairs; one field on
-// 64 x 32^3: 346 against 475 us per sweep with lane pairs).
-// Larger blocks, the clover term and antiperiodic time: the generic kernel.
-template <typename L>
+template <typename T, typename L, bool IMP>
+void launch_pair(const Geom& g, const SapGeom& sg, L U, const cpx<T>* rho, const double* rho_nrm2, cpx<T>* psi, T m0,
+                 int nmr, int colour, int nrhs, int init, c64* out64, hipStream_t s, const cpx<T>* clov)
+{
+    const int threads = (sg.Vsb + 31) / 32 * 64;
+    size_t lds = (size_t)12 * sg.Vsb * sizeof(cpx<T>);
+    if (sizeof(T) == 8)
+        lds += lds + (IMP ? (size_t)kPC * threads * sizeof(cpx<T>) : 0);
+    static std::once_flag attr[2];  // per kernel instantiation
+    auto go = [&](std::once_flag& f, auto* kernel) {
+        set_max_lds_once(f, reinterpret_cast<const void*>(kernel), 160 * 1024 - 1024);
+        hipLaunchKernelGGL(kernel, dim3(sg.n_per_colour * nrhs), dim3(threads), lds, s, g, sg, U, rho, rho_nrm2, psi,
+                           T(4) + m0, nmr, colour, nrhs, init, out64, Clover<T>{clov});
+    };
+    if (is_b4(sg))
+        go(attr[0], &k_sap_pair<T, L, true, IMP>);
+    else
+        go(attr[1], &k_sap_pair<T, L, false, IMP>);
+}
+
+template <typename L, bool B4, bool IMP>
+void launch_rl_kernel(const Geom& g, const SapGeom& sg, L U, const c32* rho, const double* rho_nrm2, c32* psi,
+                      float m0, int nmr, int colour, int nrhs, int init, c64* out64, hipStream_t s, const c32* clov)
+{
+    const dim3 grid(sg.n_per_colour * nrhs), threads(((sg.Vsb + 63) / 64) * 64);
+    static std::once_flag attr;  // one per kernel instantiation
+    if constexpr (IMP) {
+        set_max_lds_once(attr, reinterpret_cast<const void*>(&k_sap_cl<L, B4>), 160 * 1024 - 1024);
+        hipLaunchKernelGGL((k_sap_cl<L, B4>), grid, threads, (size_t)(24 + 2 * kLC) * sg.Vsb * sizeof(c32), s, g, sg,
+                           U, rho, rho_nrm2, psi, 4.0f + m0, nmr, colour, nrhs, init, out64, Clover<float>{clov});
+    } else {
+        set_max_lds_once(attr, reinterpret_cast<const void*>(&k_sap_rl<L, B4>), 160 * 1024 - 1024);
+        hipLaunchKernelGGL((k_sap_rl<L, B4>), grid, threads, (size_t)36 * sg.Vsb * sizeof(c32), s, g, sg, U, rho,
+                           rho_nrm2, psi, 4.0f + m0, nmr, colour, nrhs, init, out64);
+    }
+}
+
+// FP32: links in registers. One field on lattices whose colours hold few blocks
+// per CU (sg.one_rl == 0), blocks of up to 256 sites: lane pairs, one block per
+// CU at two wavefronts per SIMD (16^4 and 32 x 16^3 with 4^4 blocks: 11% faster
+// than one lane per site). Several fields, one field with many blocks per
+// colour, or larger blocks: one lane per site, two blocks of up to 256 sites
+// per CU (16 fields on 16^4: 12% faster than the generic kernel at three blocks
+// per CU, which re-reads the links every MR step, and 28% faster than lane
+// pairs; one field on 64 x 32^3: 346 against 475 us per sweep with lane pairs).
+template <typename L, bool IMP>
 void launch_rl(const Geom& g, const SapGeom& sg, L U, const c32* rho, const double* rho_nrm2, c32* psi, float m0,
                int nmr, int colour, int nrhs, int init, c64* out64, hipStream_t s, const c32* clov)
 {
-    if (sg.Vsb > 256 || clov || g.tsign < 0) {
-        launch<float, L>(g, sg, U, rho, rho_nrm2, psi, m0, nmr, colour, nrhs, init, out64, s, clov);
-        return;
-    }
-    size_t lds = (size_t)12 * sg.Vsb * sizeof(c32);
-    if (nrhs == 1 && !sg.one_rl) {
-        int threads = ((2 * sg.Vsb + 63) / 64) * 64;
-        hipLaunchKernelGGL((k_sap_pair<L>), dim3(sg.n_per_colour * nrhs), dim3(threads), lds, s, g, sg, U, rho,
-                           rho_nrm2, psi, 4.0f + m0, nmr, colour, nrhs, init, out64);
-        return;
-    }
-    int threads = ((sg.Vsb + 63) / 64) * 64;
-    size_t lds_rl = (size_t)36 * sg.Vsb * sizeof(c32);
-    static std::once_flag attr;  // one per link type
-    static std::once_flag attr4;
-    const bool b4 = sg.sb[0] == 4 && sg.sb[1] == 4 && sg.sb[2] == 4 && sg.sb[3] == 4;
-    if (b4) {
-        set_max_lds_once(attr4, reinterpret_cast<const void*>(&k_sap_rl<L, true>), 80 * 1024);
-        hipLaunchKernelGGL((k_sap_rl<L, true>), dim3(sg.n_per_colour * nrhs), dim3(threads), lds_rl, s, g, sg, U,
-                           rho, rho_nrm2, psi, 4.0f + m0, nmr, colour, nrhs, init, out64);
-    } else {
-        set_max_lds_once(attr, reinterpret_cast<const void*>(&k_sap_rl<L, false>), 80 * 1024);
-        hipLaunchKernelGGL((k_sap_rl<L, false>), dim3(sg.n_per_colour * nrhs), dim3(threads), lds_rl, s, g, sg, U,
-                           rho, rho_nrm2, psi, 4.0f + m0, nmr, colour, nrhs, init, out64);
-    }
+    if (nrhs == 1 && !sg.one_rl && sg.Vsb <= 256)
+        launch_pair<float, L, IMP>(g, sg, U, rho, rho_nrm2, psi, m0, nmr, colour, nrhs, init, out64, s, clov);
+    else if (is_b4(sg))
+        launch_rl_kernel<L, true, IMP>(g, sg, U, rho, rho_nrm2, psi, m0, nmr, colour, nrhs, init, out64, s, clov);
+    else
+        launch_rl_kernel<L, false, IMP>(g, sg, U, rho, rho_nrm2, psi, m0, nmr, colour, nrhs, init, out64, s, clov);
 }
 
-template <typename T, typename L>
-void launch(const Geom& g, const SapGeom& sg, L U, const cpx<T>* rho, const double* rho_nrm2, cpx<T>* psi, T m0,
-            int nmr, int colour, int nrhs, int init, c64* out64, hipStream_t s, const cpx<T>* clov)
+template <typename L>
+void launch32(const Geom& g, const SapGeom& sg, L U, const c32* rho, const double* rho_nrm2, c32* psi, float m0,
+              int nmr, int colour, int nrhs, int init, c64* out64, hipStream_t s, const c32* clov)
 {
-    int threads = ((sg.Vsb + 63) / 64) * 64;
-    size_t lds = (size_t)12 * sg.Vsb * sizeof(cpx<T>);
-    const Clover<T> C{clov};
-    if (clov) {
-        static std::once_flag attr;  // one per kernel instantiation
-        set_max_lds_once(attr, reinterpret_cast<const void*>(&k_sap<T, L, true>), 160 * 1024 - 1024);
-        hipLaunchKernelGGL((k_sap<T, L, true>), dim3(sg.n_per_colour * nrhs), dim3(threads), lds, s, g, sg, U, rho,
-                           rho_nrm2, psi, T(4) + m0, nmr, colour, nrhs, init, out64, C);
-    } else {
-        static std::once_flag attr;
-        set_max_lds_once(attr, reinterpret_cast<const void*>(&k_sap<T, L, false>), 160 * 1024 - 1024);
-        hipLaunchKernelGGL((k_sap<T, L, false>), dim3(sg.n_per_colour * nrhs), dim3(threads), lds, s, g, sg, U, rho,
-                           rho_nrm2, psi, T(4) + m0, nmr, colour, nrhs, init, out64, C);
+    if (clov || g.tsign < 0)
+        launch_rl<L, true>(g, sg, U, rho, rho_nrm2, psi, m0, nmr, colour, nrhs, init, out64, s, clov);
+    else
+        launch_rl<L, false>(g, sg, U, rho, rho_nrm2, psi, m0, nmr, colour, nrhs, init, out64, s, clov);
+}
+
+// FP64: lane pairs for blocks of up to 256 sites, one lane per site and link
+// for larger ones.
+void launch64(const Geom& g, const SapGeom& sg, Links64 U, const c64* rho, c64* psi, double m0, int nmr, int colour,
+              int nrhs, int init, hipStream_t s, const c64* clov)
+{
+    if (sg.Vsb <= 256) {
+        if (clov || g.tsign < 0)
+            launch_pair<double, Links64, true>(g, sg, U, rho, nullptr, psi, m0, nmr, colour, nrhs, init, nullptr, s,
+                                               clov);
+        else
+            launch_pair<double, Links64, false>(g, sg, U, rho, nullptr, psi, m0, nmr, colour, nrhs, init, nullptr, s,
+                                                clov);
+        return;
     }
+    const int threads = ((sg.Vsb + 63) / 64) * 64;
+    const size_t lds = (size_t)18 * sg.Vsb * sizeof(c64);
+    static std::once_flag attr[2];
+    auto go = [&](std::once_flag& f, auto* kernel) {
+        set_max_lds_once(f, reinterpret_cast<const void*>(kernel), 160 * 1024 - 1024);
+        hipLaunchKernelGGL(kernel, dim3(sg.n_per_colour * nrhs), dim3(threads), lds, s, g, sg, U, rho, psi, 4.0 + m0,
+                           nmr, colour, nrhs, init, Clover<double>{clov});
+    };
+    if (clov)
+        go(attr[0], &k_sap_big<true>);
+    else
+        go(attr[1], &k_sap_big<false>);
 }
 
 }  // namespace
@@ -840,19 +1310,19 @@ void launch(const Geom& g, const SapGeom& sg, L U, const cpx<T>* rho, const doub
 void launch_sap_colour64(const Geom& g, const SapGeom& sg, Links64 U, const c64* rho, c64* psi, double m0, int nmr,
                          int colour, int nrhs, int init, hipStream_t s, const c64* clov)
 {
-    launch(g, sg, U, rho, (const double*)nullptr, psi, m0, nmr, colour, nrhs, init, (c64*)nullptr, s, clov);
+    launch64(g, sg, U, rho, psi, m0, nmr, colour, nrhs, init, s, clov);
 }
 void launch_sap_colour32(const Geom& g, const SapGeom& sg, Links32 U, const c32* rho, c32* psi, float m0, int nmr,
                          int colour, int nrhs, int init, c64* out64, hipStream_t s, const c32* clov,
                          const double* rho_nrm2)
 {
-    launch_rl(g, sg, U, rho, rho_nrm2, psi, m0, nmr, colour, nrhs, init, out64, s, clov);
+    launch32(g, sg, U, rho, rho_nrm2, psi, m0, nmr, colour, nrhs, init, out64, s, clov);
 }
 void launch_sap_colour_bf16(const Geom& g, const SapGeom& sg, LinksBF16 U, const c32* rho, c32* psi, float m0,
                             int nmr, int colour, int nrhs, int init, c64* out64, hipStream_t s, const c32* clov,
                             const double* rho_nrm2)
 {
-    launch_rl(g, sg, U, rho, rho_nrm2, psi, m0, nmr, colour, nrhs, init, out64, s, clov);
+    launch32(g, sg, U, rho, rho_nrm2, psi, m0, nmr, colour, nrhs, init, out64, s, clov);
 }
 
 }  // namespace dfl
