@@ -402,11 +402,11 @@ constexpr int kNetMaxCout = 576;   // output channels (input-gradient staging bo
 constexpr int kLossMaxN = 32;      // fields and targets of the deficit loss
 
 // ---------------------------------------------------------------- little.hip
-// workgroups of the little GCR: requested (0: Nb / 4), clamped to 1..min(Nb, kLittleMaxGrid)
+// workgroups of the little GCR: requested (0: Nb / 4), clamped to 1..min(Nb / 2, kLittleMaxGrid)
 int little_gcr_grid(const Geom& g, int requested);
 size_t little_gcr_partial_doubles(int grid_size);
 // workgroups of the batched little GCR: twice the requested single-source
-// grid (0: Nb / 4), at most one per compute unit and the block count
+// grid (0: Nb / 4), at most one per compute unit and half the block count
 int little_gcr_multi_grid(const Geom& g, int requested);
 // workgroups of the (batched) little GCR kernels that can be resident at once
 // on the current device (occupancy x compute units); the grid barrier needs

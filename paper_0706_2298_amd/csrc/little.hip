@@ -1,9 +1,12 @@
 // GCR for the little system A v = w (eq. (6.1), appendix A.4) in a single
 // cooperative launch.
 //
-// The little vector has Nb*Ns entries; workgroup g owns the blocks
-// g, g + G, g + 2G, ... (G = grid size) and all entries of those blocks. One
-// GCR step normally needs two grid-wide barriers (one more inside the
+// The little vector has Nb*Ns entries; workgroup g owns the block pairs
+// g, g + G, g + 2G, ... (G = grid size; pair p = blocks 2p and 2p + 1) and all
+// entries of those blocks. A pair are neighbours along x3, one block of either
+// colour, so both halves of the even-odd operator occupy every workgroup (with
+// single blocks g, g + G, ... a workgroup's blocks often had one colour and
+// half of the workgroups idled in either half). One GCR step normally needs two grid-wide barriers (one more inside the
 // even-odd operator):
 //   S1  xi_k = r is complete everywhere: apply chi_k = A xi_k (rows of the
 //       owned blocks; the nine neighbour blocks' entries are read from global
@@ -146,7 +149,11 @@ __device__ inline int nbr_block(const Geom& g, int blk, int d)
     return blk + (nn - n_mu) * g.bstr[mu];
 }
 
-// The workgroup's view: it owns the blocks g + i G (i = owned position); its
+// The i-th owned block of workgroup g of G, and how many it owns (Nb is even)
+__device__ inline int owned_block(int g, int G, int i) { return 2 * (g + (i >> 1) * G) + (i & 1); }
+__device__ inline int owned_count(int Nb, int g, int G) { return 2 * ((Nb / 2 - g + G - 1) / G); }
+
+// The workgroup's view: it owns owned_block(i) (i = owned position); its
 // vector entries are those of the owned positions listed in vb (all of them
 // when vb is null). nbr (LDS, may be null): nbr[8 i + d - 1] = neighbour d of
 // owned position i.
@@ -157,7 +164,7 @@ template <typename T> struct LittleCtx {
     const int* vb;
     int nvb;
     const int* nbr;
-    __device__ int block(int i) const { return g + (vb ? vb[i] : i) * G; }
+    __device__ int block(int i) const { return owned_block(g, G, vb ? vb[i] : i); }
     __device__ long entry(int e) const
     {
         int i = e / a.Ns;
@@ -296,7 +303,7 @@ __device__ inline void apply_blocks(const LittleCtx<T>& c, const int* list, int 
             const int gq = task / rows, row = task - gq * rows;
             const int ib = row / Ns, k = row - ib * Ns;
             const int own = list ? list[ib] : ib;
-            const int blk = c.g + own * c.G;
+            const int blk = owned_block(c.g, c.G, own);
             const int da = d0 + gq * per, dz = min(d1, da + per);
             double re = 0.0, im = 0.0;
             for (int db = da; db < dz; db += kApplyD) {
@@ -353,7 +360,7 @@ __device__ inline void apply_blocks(const LittleCtx<T>& c, const int* list, int 
                 si += lds[2 * (gq * rows + row) + 1];
             }
             const int ib = row / Ns, k = row - ib * Ns;
-            const int blk = c.g + (list ? list[ib] : ib) * c.G;
+            const int blk = owned_block(c.g, c.G, list ? list[ib] : ib);
             const long i = (long)blk * Ns + k;
             double yr = beta * sr, yi = beta * si;
             if (alpha != 0.0) {
@@ -585,15 +592,15 @@ template <typename T, bool EO> __global__ __launch_bounds__(LT1) void k_little_g
     __shared__ int nbr_tab[8 * kMaxOwned];  // neighbours of the owned blocks, computed once
 
     const int G = (int)gridDim.x, gi = (int)blockIdx.x, t = (int)threadIdx.x;
-    const int nbg = (a.g.Nb - gi + G - 1) / G;
+    const int nbg = owned_count(a.g.Nb, gi, G);
     const bool tab = nbg <= kMaxOwned;
     if (tab)
         for (int q = t; q < 8 * nbg; q += LT1)
-            nbr_tab[q] = nbr_block(a.g, gi + (q >> 3) * G, 1 + (q & 7));
+            nbr_tab[q] = nbr_block(a.g, owned_block(gi, G, q >> 3), 1 + (q & 7));
     if (EO && t == 0) {
         int ne = 0, no = 0;
         for (int i = 0; i < nbg; ++i) {
-            if (block_colour(a.g, gi + i * G))
+            if (block_colour(a.g, owned_block(gi, G, i)))
                 l_odd[no++] = i;
             else
                 l_even[ne++] = i;
@@ -1041,7 +1048,7 @@ template <typename T> struct MultiCtx {
     {
         int i = e / a.Ns;
         int k = e - i * a.Ns;
-        return (long)(g + (vb ? vb[i] : i) * G) * a.Ns + k;
+        return (long)owned_block(g, G, vb ? vb[i] : i) * a.Ns + k;
     }
     __device__ double* pslot(int slot, int b) const { return a.part + (((long)slot * a.nrhs + b) * G + g) * 2; }
 };
@@ -1085,7 +1092,7 @@ __device__ inline void apply_multi_mfma(const MultiCtx<T>& c, const cpx<T>* __re
     const int b_n = n < nlist ? list[n] : 0;
     for (int task = wave; task < npos * mt; task += LT / 64) {
         const int ib = task / mt, tt = task - ib * mt;
-        const int blk = c.g + (pos ? pos[ib] : ib) * c.G;
+        const int blk = owned_block(c.g, c.G, pos ? pos[ib] : ib);
         const int rr = 16 * tt + n;
         const int m = rr >> 1, cr = rr & 1;
         typename Mfma<T>::acc_t acc = {0, 0, 0, 0};
@@ -1283,11 +1290,11 @@ template <typename T, bool EO> __global__ __launch_bounds__(LT) void k_little_gc
     unsigned long long bar_target = 0;
     if (c.t == 0)
         bar_target = __hip_atomic_load(a.bar_gen, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    c.nbg = (a.g.Nb - c.g + c.G - 1) / c.G;
+    c.nbg = owned_count(a.g.Nb, c.g, c.G);
     if (EO && c.t == 0) {
         int ne = 0, no = 0;
         for (int i = 0; i < c.nbg; ++i) {
-            if (block_colour(a.g, c.g + i * c.G))
+            if (block_colour(a.g, owned_block(c.g, c.G, i)))
                 l_odd[no++] = i;
             else
                 l_even[ne++] = i;
@@ -1662,8 +1669,8 @@ int little_gcr_grid(const Geom& g, int requested)
     int G = requested > 0 ? requested : g.Nb / 4;
     if (G > kLittleMaxGrid)
         G = kLittleMaxGrid;
-    if (G > g.Nb)
-        G = g.Nb;
+    if (G > g.Nb / 2)
+        G = g.Nb / 2;
     if (G < 1)
         G = 1;
     return G;
@@ -1674,8 +1681,8 @@ int little_gcr_multi_grid(const Geom& g, int requested)
     int G = requested > 0 ? 2 * requested : g.Nb / 4;
     if (G > kLittleMaxGridMulti)
         G = kLittleMaxGridMulti;
-    if (G > g.Nb)
-        G = g.Nb;
+    if (G > g.Nb / 2)
+        G = g.Nb / 2;
     if (G < 1)
         G = 1;
     return G;
@@ -1708,7 +1715,7 @@ int little_gcr_resident_limit(bool multi)
 
 bool little_eo_fits(const Geom& g, int grid)
 {
-    return (g.Nb + grid - 1) / grid <= kMaxOwned;
+    return 2 * ((g.Nb / 2 + grid - 1) / grid) <= kMaxOwned;
 }
 
 size_t little_gcr_partial_doubles(int grid_size) { return (size_t)NSLOT * (grid_size + 1) * 2; }
