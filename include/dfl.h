@@ -109,8 +109,9 @@ typedef struct {
     dfl_prec sap_prec;     /* arithmetic of the SAP block solves: F64 or F32 */
     dfl_prec little_prec;  /* arithmetic of the little solves inside cycles: F64 or F32 */
     int little_grid;       /* workgroups of the little solver (0: a quarter of the block
-                              count); clamped to the block count, to 256 and to the
-                              number of workgroups the device holds at once */
+                              count, or half of it for even-odd solves of up to 512
+                              blocks); clamped to half the block count, to 256 and to
+                              the number of workgroups the device holds at once */
     int little_adapt;      /* 1: inside a cycle, relax the little-solve tolerance in
                               proportion to the fall of the residue (appendix A.5) */
     int little_eo;         /* 1: little solves (single-source and batched) run GCR on the

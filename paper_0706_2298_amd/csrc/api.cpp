@@ -601,9 +601,16 @@ void little_solve_impl(dfl_ctx* c, const c64* w, c64* v, double tol, dfl_prec pr
     const long n = (long)c->g.Nb * c->p.Ns;
     const int Ns = c->p.Ns, nkv = c->p.little_nkv, mi = c->p.little_maxiter;
     const bool eo_multi = nb > 1 && c->eo_ok && little_eo_fits(c->g, c->lgrid_multi);
+    // few blocks: one block pair per workgroup, the sources side by side as far as the device holds them
+    const bool pair = c->lpair > 0 && c->eo_ok;
     if (prec == DFL_F64) {
         ProfScope ps(c, DFL_PROF_LITTLE);
-        if (nb == 1)
+        if (pair)
+            for (int b = 0; b < nb; b += c->lpair)
+                launch_little_gcr_pair<double>(c->g, Ns, nkv, mi, tol, tol_dev, c->Mt64, static_cast<c64*>(c->lw1),
+                                               c->gQ, c->gZ, c->gdefl_n, w + b * n, v + b * n, c->lpart, c->lstats,
+                                               c->lbar_gen, std::min(c->lpair, nb - b), c->stream, !c->capturing);
+        else if (nb == 1)
             launch_little_gcr<double>(c->g, Ns, nkv, mi, tol, tol_dev, c->At64, c->eo_ok ? c->Mt64 : nullptr,
                                       static_cast<c64*>(c->lw1), static_cast<c64*>(c->lw2), c->gQ, c->gZ,
                                       c->eo_ok ? c->gdefl_n : 0, c->gdefl_oblique, c->gAinv, c->gGw, w, v,
@@ -621,7 +628,13 @@ void little_solve_impl(dfl_ctx* c, const c64* w, c64* v, double tol, dfl_prec pr
         launch_f64_to_f32(w, c->lw32, n * nb, c->stream);
         {
             ProfScope ps(c, DFL_PROF_LITTLE);
-            if (nb == 1)
+            if (pair)
+                for (int b = 0; b < nb; b += c->lpair)
+                    launch_little_gcr_pair<float>(c->g, Ns, nkv, mi, tol, tol_dev, c->Mt32, static_cast<c32*>(c->lw1),
+                                                  c->gQ32, c->gZ32, c->gdefl_n, c->lw32 + b * n, c->lx32 + b * n,
+                                                  c->lpart, c->lstats, c->lbar_gen, std::min(c->lpair, nb - b),
+                                                  c->stream, !c->capturing);
+            else if (nb == 1)
                 launch_little_gcr<float>(c->g, Ns, nkv, mi, tol, tol_dev, c->At32, c->eo_ok ? c->Mt32 : nullptr,
                                          static_cast<c32*>(c->lw1), static_cast<c32*>(c->lw2), c->gQ32, c->gZ32,
                                          c->eo_ok ? c->gdefl_n : 0, c->gdefl_oblique, c->gAinv, c->gGw, c->lw32,
@@ -640,6 +653,9 @@ void little_solve_impl(dfl_ctx* c, const c64* w, c64* v, double tol, dfl_prec pr
     }
 }
 
+// words of the little solvers' barriers: the generation, then the flags of every source
+size_t lbar_words(const dfl_ctx* c) { return kLittleFlags + (size_t)kLittleBarWords * std::max(1, c->lpair); }
+
 void reset_little_stats(dfl_ctx* c) { HIPCHECK(hipMemsetAsync(c->lstats, 0, sizeof(int) * 4, c->stream)); }
 
 // [iterations, solves, failed] accumulated since the last reset (synchronises)
@@ -654,9 +670,10 @@ void read_little_stats(dfl_ctx* c, int out[3])
     if (c->prof_on)
         c->prof_little_iters += h[0];
     if (h[2] & 4) {
-        // a timed-out barrier leaves its arrival count behind: clear it so
+        // a timed-out barrier leaves its arrival count and flags behind: clear them so
         // that later solves start from a clean barrier
         HIPCHECK(hipMemsetAsync(c->lbar_count, 0, sizeof(unsigned) * 64, c->stream));
+        HIPCHECK(hipMemsetAsync(c->lbar_gen, 0, sizeof(unsigned long long) * lbar_words(c), c->stream));
         HIPCHECK(hipMemsetAsync(c->lstats, 0, sizeof(int) * 4, c->stream));
         sync(c);
         fail(DFL_EHIP, "little solver: grid barrier timed out");
@@ -1331,15 +1348,18 @@ int dfl_create(dfl_ctx** out, const dfl_params* p, void* hip_stream)
         c->lt = alloc_dev<c64>(c, N);
         c->lw32 = alloc_dev<c32>(c, R * N);
         c->lx32 = alloc_dev<c32>(c, R * N);
-        c->lgrid = little_gcr_grid(c->g, p->little_grid);
+        c->lgrid = little_gcr_grid(c->g, p->little_grid, p->little_eo && p->Ns <= 32 && p->little_gdefl != 2);
         c->lgrid_multi = little_gcr_multi_grid(c->g, p->little_grid);
         // every workgroup of the grid-barrier kernels must be resident at
         // once (graph replays launch them as ordinary kernels)
-        c->lgrid = std::min(c->lgrid, little_gcr_resident_limit(false));
+        const int resident = little_gcr_resident_limit(false);
+        c->lgrid = std::min(c->lgrid, resident);
         c->lgrid_multi = std::min(c->lgrid_multi, little_gcr_resident_limit(true));
         if (c->lgrid < 1 || c->lgrid_multi < 1)
             fail(DFL_EHIP, "the little GCR kernels cannot be resident on this device");
-        size_t part = little_gcr_partial_doubles(c->lgrid);
+        if (p->little_eo && p->little_gdefl != 2)
+            c->lpair = std::min(little_pair_sources(c->g, p->Ns, c->lgrid, resident), (int)R);
+        size_t part = little_gcr_partial_doubles(c->lgrid) * std::max(1, c->lpair);
         if (R > 1) {
             size_t nfin = 0, nac = 0;
             part = std::max(part, little_gcr_multi_doubles(c->lgrid_multi, (int)R, &nfin, &nac));
@@ -1349,7 +1369,7 @@ int dfl_create(dfl_ctx** out, const dfl_params* p, void* hip_stream)
         c->lpart = alloc_dev<double>(c, part);
         c->lstats = alloc_dev<int>(c, 4);
         c->lbar_count = alloc_dev<unsigned>(c, 64);
-        c->lbar_gen = alloc_dev<unsigned long long>(c, 32);
+        c->lbar_gen = alloc_dev<unsigned long long>(c, lbar_words(c));
         const long RM = std::max<long>(R, max_multi_fields(c));  // fields normalised in one launch
         c->red = alloc_dev<double>(c, (size_t)kMaxDot * kRedBlocks * 2 * RM);
         c->dnorm = alloc_dev<double>(c, (size_t)2 * RM);
@@ -1366,7 +1386,7 @@ int dfl_create(dfl_ctx** out, const dfl_params* p, void* hip_stream)
         HIPCHECK(hipMemsetAsync(c->dflag, 0, sizeof(int) * 4, c->stream));
         HIPCHECK(hipMemsetAsync(c->lstats, 0, sizeof(int) * 4, c->stream));
         HIPCHECK(hipMemsetAsync(c->lbar_count, 0, sizeof(unsigned) * 64, c->stream));
-        HIPCHECK(hipMemsetAsync(c->lbar_gen, 0, sizeof(unsigned long long) * 32, c->stream));
+        HIPCHECK(hipMemsetAsync(c->lbar_gen, 0, sizeof(unsigned long long) * lbar_words(c), c->stream));
         sync(c);
     } catch (...) {
         free_all(c);

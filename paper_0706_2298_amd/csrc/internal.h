@@ -65,6 +65,8 @@ constexpr int kRedThreads = 256;
 constexpr int kMaxDot = 64;       // most vectors in one multi-dot
 constexpr int kMaxLittleNkv = 32; // most Krylov vectors of the little GCR
 constexpr int kLittleMaxGrid = 256;  // workgroups of the cooperative little GCR (one per CU)
+constexpr int kLittleFlags = 32;        // barrier words before the per-workgroup flags
+constexpr int kLittleBarWords = kLittleMaxGrid;  // flags of one source (two per workgroup), in 64-bit words
 constexpr int kMaxLittleRhs = 16;    // right-hand sides of one batched little solve
 constexpr int kMaxLittleDefl = 32;   // global deflation directions of the little system
 constexpr int kCloverComp = 36;         // complex entries of the clover term per site (two packed 6 x 6 blocks)
@@ -143,8 +145,9 @@ struct dfl_ctx {
     double* lpart = nullptr;   // partial sums of the cooperative little GCR
     int* lstats = nullptr;     // [iterations, solves, failure flags, spare]
     unsigned* lbar_count = nullptr;         // grid barrier of the little GCR kernel
-    unsigned long long* lbar_gen = nullptr;
+    unsigned long long* lbar_gen = nullptr;  // its generation, then the flags of the pair kernel
     int lgrid = 0;             // its grid size
+    int lpair = 0;             // sources one launch of the block-pair solver takes (0: it does not apply)
     int lgrid_multi = 0;       // grid of the batched little GCR
     double* lfin = nullptr;    // batched little GCR: reduced sums and per-workgroup coefficients
     double* lacoef = nullptr;
@@ -402,8 +405,9 @@ constexpr int kNetMaxCout = 576;   // output channels (input-gradient staging bo
 constexpr int kLossMaxN = 32;      // fields and targets of the deficit loss
 
 // ---------------------------------------------------------------- little.hip
-// workgroups of the little GCR: requested (0: Nb / 4), clamped to 1..min(Nb / 2, kLittleMaxGrid)
-int little_gcr_grid(const Geom& g, int requested);
+// workgroups of the little GCR: requested (0: Nb / 4, or Nb / 2 for up to 512 blocks with
+// `pair`: even-odd solves, Ns <= 32, no oblique deflation), clamped to 1..min(Nb / 2, kLittleMaxGrid)
+int little_gcr_grid(const Geom& g, int requested, bool pair);
 size_t little_gcr_partial_doubles(int grid_size);
 // workgroups of the batched little GCR: twice the requested single-source
 // grid (0: Nb / 4), at most one per compute unit and half the block count
@@ -434,6 +438,18 @@ void launch_little_gcr(const Geom& g, int Ns, int nkv, int maxiter, double tol, 
                        int nq, int oblique, const double* Ainv, const double* Gw, const cpx<T>* w,
                        cpx<T>* x, cpx<T>* r, cpx<T>* xi, cpx<T>* chi, double* part, int* stats, unsigned* bar_count,
                        unsigned long long* bar_gen, int grid, hipStream_t s, bool cooperative = true);
+
+// The even-odd solves with one block pair per workgroup (minimal-residual
+// deflation): sources that one launch takes side by side with `resident`
+// workgroups on the device, 0 if the grid of little_gcr_grid is not one
+// workgroup per pair; part (little_gcr_partial_doubles each) and the flags
+// (kLittleBarWords each, after the kLittleFlags words of bar) are per source.
+int little_pair_sources(const Geom& g, int Ns, int grid, int resident);
+template <typename T>
+void launch_little_gcr_pair(const Geom& g, int Ns, int nkv, int maxiter, double tol, const double* tol_dev,
+                            const cpx<T>* Mt, cpx<T>* w1, const cpx<T>* Q, const cpx<T>* Z, int nq, const cpx<T>* w,
+                            cpx<T>* x, double* part, int* stats, unsigned long long* bar, int nsrc, hipStream_t s,
+                            bool cooperative);
 
 // The same for nrhs systems at once (nrhs <= kMaxLittleRhs): w, x, r hold
 // nrhs little vectors back to back, xi and chi nkv * nrhs. Sizes of part,

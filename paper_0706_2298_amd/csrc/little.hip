@@ -25,6 +25,8 @@
 // is updated from the triangular system and the residue recomputed as
 // w - A x (two more barriers); convergence is decided on that true residue. The barriers are this file's own (see
 // grid_barrier); the launch is cooperative so all workgroups are resident.
+#include <algorithm>
+
 #include "internal.h"
 
 namespace dfl {
@@ -999,6 +1001,534 @@ template <typename T, bool EO> __global__ __launch_bounds__(LT1) void k_little_g
     }
 }
 
+// -------------------------------------------------- one block pair per workgroup
+//
+// The even-odd GCR for lattices of at most 512 blocks, where a step is all
+// latency: one workgroup per block pair, its eight-neighbour matrices in
+// registers (a thread holds one row of one neighbour term), the pair's Krylov
+// and deflation vectors in LDS, and every dot product and combination spread
+// over groups of 8 or 16 lanes, so that a step has three exchanges between
+// workgroups and otherwise no memory access. What workgroups exchange (the
+// operator's argument and intermediate, partial and reduced sums) is written
+// and read with agent-scope relaxed atomics, which are coherent by themselves:
+// the barrier needs no cache write-back or invalidation, only that a thread's
+// stores have completed before its workgroup raises its flag. The flags rise by
+// one per barrier and are never reset; a launch continues from their value.
+// Same algorithm, decisions and precisions as k_little_gcr with the
+// minimal-residual deflation; its comments explain the steps.
+// MI355X: a little solve of P_L on 32 x 16^3 (Ns = 20, FP64 to 1e-12, 27 steps)
+// takes 0.58 ms (k_little_gcr: 1.20), 18 us a step of which 8 are the reduction
+// over 256 workgroups; on 8^4 9 us a step (30). P_L of five fields on 8^4 0.26 ms
+// (one batched solve: 2.5).
+
+template <typename T> __device__ inline cpx<T> ld_agent(const cpx<T>* p)
+{
+    if constexpr (sizeof(T) == 4) {
+        const unsigned long long b = __hip_atomic_load(reinterpret_cast<const unsigned long long*>(p), __ATOMIC_RELAXED,
+                                                       __HIP_MEMORY_SCOPE_AGENT);
+        return cpx<T>{(T)__uint_as_float((unsigned)b), (T)__uint_as_float((unsigned)(b >> 32))};
+    } else {
+        const double* q = reinterpret_cast<const double*>(p);
+        const double re = __hip_atomic_load(q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const double im = __hip_atomic_load(q + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        return cpx<T>{(T)re, (T)im};
+    }
+}
+template <typename T> __device__ inline void st_agent(cpx<T>* p, cpx<T> v)
+{
+    if constexpr (sizeof(T) == 4) {
+        const unsigned long long b = (unsigned long long)__float_as_uint((float)v.re) |
+                                     ((unsigned long long)__float_as_uint((float)v.im) << 32);
+        __hip_atomic_store(reinterpret_cast<unsigned long long*>(p), b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    } else {
+        double* q = reinterpret_cast<double*>(p);
+        __hip_atomic_store(q, (double)v.re, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(q + 1, (double)v.im, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+}
+
+// With `raise`, sets this workgroup's flag to `target` once all its threads'
+// stores have completed; then every thread with wait >= 0 waits until the flag
+// of workgroup `wait` has reached it (the count may wrap). Polling is bounded;
+// on timeout a failure is recorded and the thread goes on.
+__device__ inline void flag_barrier(unsigned* flags, unsigned target, int g, bool raise, int wait, int* stats)
+{
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (threadIdx.x == 0 && raise)
+        __hip_atomic_store(flags + g, target, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (wait >= 0) {
+        long spin = 0;
+        while ((int)(__hip_atomic_load(flags + wait, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) - target) < 0) {
+            __builtin_amdgcn_s_sleep(1);
+            if (++spin > kSpinLimit) {
+                atomicOr(&stats[2], 4);
+                break;
+            }
+        }
+    }
+    __syncthreads();
+}
+
+// sums over aligned groups of 8 and 16 lanes, in every lane
+__device__ inline double sum8(double v)
+{
+    using wave_detail::row;
+    v += row<0xB1>(v);
+    v += row<0x4E>(v);
+    return v + row<0x141>(v);
+}
+__device__ inline double sum16(double v)
+{
+    v = sum8(v);
+    return v + wave_detail::row<0x140>(v);
+}
+
+constexpr int kPairAllRead = 16;  // up to so many workgroups, each sums all partial sums itself
+
+template <typename T, int NL> __global__ __launch_bounds__(LT1) void k_little_gcr_pair(LittleArgs<T> a)
+{
+    constexpr bool kTrackNorm = sizeof(T) == sizeof(double);
+    constexpr double kNormFloor = 1e-12;
+    constexpr double kLooseTol2 = 1e-16;
+    constexpr int NP = NL + 1;  // LDS stride of a staged neighbour vector (odd: the eight neighbours' banks differ)
+    __shared__ cpx<T> chi_s[NK][NL], xi_s[NK][NL], q_s[NQ][NL], z_s[NQ][NL];
+    __shared__ cpx<T> su[8 * NP];
+    __shared__ cpx<T> w1e_s[NL], w1o_s[NL], rhs_s[NL], r_s[NL], x_s[NL], y_s[NL];
+    __shared__ double red[2 * (2 * NK + 2 + NQ)];
+    __shared__ double acoef[NK][NK][2], qcoef[NQ][NK][2];
+    __shared__ double zc[NQ][2], cq_s[NQ][2], ccoef[NK][2], alpha[NK][2], bcoef[NK];
+    __shared__ double rn2_s;
+    __shared__ int second_s;
+
+    // several sources are so many independent solves side by side
+    const int G = a.g.Nb / 2, src = (int)blockIdx.x / G, g = (int)blockIdx.x - src * G, t = (int)threadIdx.x;
+    const int Ns = a.Ns, nq = a.nq;
+    a.w += (long)src * a.g.Nb * Ns;
+    a.x += (long)src * a.g.Nb * Ns;
+    a.w1 += (long)src * a.g.Nb * Ns;
+    a.part += (long)src * NSLOT * (G + 1) * 2;
+    const int lane = t & 63, wv = t >> 6;
+    const int first_even = block_colour(a.g, 2 * g) == 0;
+    const int be = 2 * g + (first_even ? 0 : 1), bo = 2 * g + (first_even ? 1 : 0);
+    const double tol2 = a.tol_dev ? (*a.tol_dev) * (*a.tol_dev) : a.tol2;
+    unsigned* const flags = reinterpret_cast<unsigned*>(a.bar_gen) + (long)src * 2 * kLittleMaxGrid;  // one per workgroup
+    unsigned* const rflags = flags + kLittleMaxGrid;                 // of the reductions
+    unsigned target = __hip_atomic_load(flags + g, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    cpx<T>* const ex = a.w1;  // exchanged vectors: the operator's argument (even) and intermediate (odd blocks)
+    double* const pub = a.part + (long)NSLOT * G * 2;
+
+    // waits for the owners of the odd (even) block's neighbours only: what they read is not overwritten
+    // before the next reduction, which every workgroup takes part in
+    const int wait_o = t < 8 ? nbr_block(a.g, bo, t + 1) >> 1 : -1, wait_e = t < 8 ? nbr_block(a.g, be, t + 1) >> 1 : -1;
+    auto sync_odd = [&]() { flag_barrier(flags, ++target, g, true, wait_o, a.stats); };
+    auto sync_even = [&]() { flag_barrier(flags, ++target, g, true, wait_e, a.stats); };
+
+    // operator rows in registers: threads 0 .. 8 Ns - 1 the odd block, the next 8 Ns the even one;
+    // lane group of eight = one row, lane d of it the term of neighbour d + 1
+    const int half = t < 8 * Ns ? 0 : 1;
+    const int task = t - half * 8 * Ns;
+    const bool has = task < 8 * Ns;
+    const int row = task >> 3, d = task & 7;
+    cpx<T> m[NL];
+    {
+        const cpx<T>* M = a.Mt + ((long)(half ? be : bo) * 9 + 1 + d) * Ns * Ns + row;
+#pragma unroll
+        for (int l = 0; l < NL; ++l)
+            m[l] = has && l < Ns ? M[(long)l * Ns] : cpx<T>{0, 0};
+    }
+    for (int q = t; q < 8 * NP; q += LT1)
+        su[q] = cpx<T>{0, 0};
+    for (int q = t; q < nq * Ns; q += LT1) {
+        q_s[q / Ns][q % Ns] = a.Q[(long)(q / Ns) * a.g.Nb * Ns + (long)be * Ns + q % Ns];
+        z_s[q / Ns][q % Ns] = a.Z[(long)(q / Ns) * a.g.Nb * Ns + (long)be * Ns + q % Ns];
+    }
+    // staging: thread t < 8 Ns fetches entry t % Ns of neighbour t / Ns + 1 of either block
+    const int sd = t / Ns, sl = t - sd * Ns;
+    const long nb_o = t < 8 * Ns ? (long)nbr_block(a.g, bo, sd + 1) * Ns + sl : 0;
+    const long nb_e = t < 8 * Ns ? (long)nbr_block(a.g, be, sd + 1) * Ns + sl : 0;
+    auto stage = [&](long from) {
+        if (t < 8 * Ns)
+            su[sd * NP + sl] = ld_agent(ex + from);
+        __syncthreads();
+    };
+    // sum_d M_d u_d of this thread's row group over the staged vectors, in every lane of the group
+    auto rows = [&](double& re, double& im) {
+        re = im = 0.0;
+        const cpx<T>* u = su + d * NP;
+#pragma unroll
+        for (int l = 0; l < NL; ++l) {
+            const cpx<T> w = u[l];
+            re += (double)m[l].re * (double)w.re - (double)m[l].im * (double)w.im;
+            im += (double)m[l].re * (double)w.im + (double)m[l].im * (double)w.re;
+        }
+        re = sum8(re);
+        im = sum8(im);
+    };
+    // the odd half: ex_o = M_oe ex_e
+    auto odd_half = [&]() {
+        stage(nb_o);
+        double re, im;
+        rows(re, im);
+        if (has && half == 0 && d == 0)
+            st_agent(ex + (long)bo * Ns + row, cpx<T>{(T)re, (T)im});
+    };
+    // the even half: y = u - M_eo ex_o for this block's u
+    auto even_half = [&](const cpx<T>* u, cpx<T>* y) {
+        stage(nb_e);
+        double re, im;
+        rows(re, im);
+        if (has && half == 1 && d == 0)
+            y[row] = cpx<T>{(T)((double)u[row].re - re), (T)((double)u[row].im - im)};
+        __syncthreads();
+    };
+    auto publish = [&](const cpx<T>* v) {
+        if (t < Ns)
+            st_agent(ex + (long)be * Ns + t, v[t]);
+    };
+    // dot product of one slot over this block, the first of eight lanes writes the partial sum
+    auto slot_dot = [&](const cpx<T>* p, const cpx<T>* q, int slot, bool on) {
+        double re = 0.0, im = 0.0;
+        if (on)
+            for (int e = t & 7; e < Ns; e += 8) {
+                const cpx<T> x = p[e], y = q[e];
+                re += (double)x.re * (double)y.re + (double)x.im * (double)y.im;
+                im += (double)x.re * (double)y.im - (double)x.im * (double)y.re;
+            }
+        re = sum8(re);
+        im = sum8(im);
+        if (on && (t & 7) == 0)
+            st_agent(reinterpret_cast<cpx<double>*>(a.part) + (long)slot * G + g, cpx<double>{re, im});
+    };
+    // red[0 .. ns) = the sums of slots s0 .. over the workgroups, the same in all of them
+    auto reduce = [&](int s0, int ns) {
+        const cpx<double>* part = reinterpret_cast<const cpx<double>*>(a.part);
+        const int owners = ns < G ? ns : G;
+        flag_barrier(flags, ++target, g, true, t < G && (g < owners || G <= kPairAllRead) ? t : -1, a.stats);
+        if (G <= kPairAllRead) {
+            constexpr int kRounds = (2 * NK + 2 + NQ + LT1 / 16 - 1) / (LT1 / 16);
+            cpx<double> v[kRounds];
+            const int q = t & 15;
+#pragma unroll
+            for (int i = 0; i < kRounds; ++i) {
+                const int s = (t >> 4) + i * (LT1 / 16);
+                v[i] = s < ns && q < G ? ld_agent(part + (long)(s0 + s) * G + q) : cpx<double>{0.0, 0.0};
+            }
+#pragma unroll
+            for (int i = 0; i < kRounds; ++i) {
+                const int s = (t >> 4) + i * (LT1 / 16);
+                const double re = sum16(v[i].re), im = sum16(v[i].im);
+                if (s < ns && q == 0) {
+                    red[2 * s] = re;
+                    red[2 * s + 1] = im;
+                }
+            }
+            __syncthreads();
+            return;
+        }
+        // workgroup g sums the slots g, g + G, ..., one wavefront each, and publishes them
+        for (int s = g + wv * G; s < ns; s += G * (LT1 / 64)) {
+            cpx<double> v[kLittleMaxGrid / 64];
+#pragma unroll
+            for (int i = 0; i < kLittleMaxGrid / 64; ++i) {
+                const int q = lane + 64 * i;
+                v[i] = q < G ? ld_agent(part + (long)(s0 + s) * G + q) : cpx<double>{0.0, 0.0};
+            }
+            double re = 0.0, im = 0.0;
+#pragma unroll
+            for (int i = 0; i < kLittleMaxGrid / 64; ++i) {
+                re += v[i].re;
+                im += v[i].im;
+            }
+            re = wave_sum(re);
+            im = wave_sum(im);
+            if (lane == 0)
+                st_agent(reinterpret_cast<cpx<double>*>(pub) + s, cpx<double>{re, im});
+        }
+        flag_barrier(rflags, target, g, g < owners, t < owners ? t : -1, a.stats);
+        for (int s = t; s < ns; s += LT1) {
+            const cpx<double> v = ld_agent(reinterpret_cast<const cpx<double>*>(pub) + s);
+            red[2 * s] = v.re;
+            red[2 * s + 1] = v.im;
+        }
+        __syncthreads();
+    };
+    // sum over the terms of entry e = t / 16 in every lane of its group of 16
+    const int ce = t >> 4;
+    auto combine = [&](int nterm, auto term, double& re, double& im) {
+        re = im = 0.0;
+        if (ce < Ns)
+            for (int j = t & 15; j < nterm; j += 16) {
+                cpx<T> v;
+                double2 c;
+                term(j, c, v);
+                re += c.x * (double)v.re - c.y * (double)v.im;
+                im += c.x * (double)v.im + c.y * (double)v.re;
+            }
+        re = sum16(re);
+        im = sum16(im);
+    };
+    const bool writer = ce < Ns && (t & 15) == 0;
+    // (Q_l, v) in red[2 from ..]: c = (Q_l, v); r -= Q c, x += Z c; ||r||^2 afterwards from vn2
+    auto project = [&](int from, double vn2) {
+        if (t < nq) {
+            cq_s[t][0] = red[2 * (from + t)];
+            cq_s[t][1] = red[2 * (from + t) + 1];
+        }
+        __syncthreads();
+        double qr, qi, zr, zi;
+        combine(nq, [&](int j, double2& c, cpx<T>& v) { c = make_double2(cq_s[j][0], cq_s[j][1]); v = q_s[j][ce]; }, qr, qi);
+        combine(nq, [&](int j, double2& c, cpx<T>& v) { c = make_double2(cq_s[j][0], cq_s[j][1]); v = z_s[j][ce]; }, zr, zi);
+        if (writer) {
+            r_s[ce] = cpx<T>{(T)((double)r_s[ce].re - qr), (T)((double)r_s[ce].im - qi)};
+            x_s[ce] = cpx<T>{(T)((double)x_s[ce].re + zr), (T)((double)x_s[ce].im + zi)};
+        }
+        for (int l = 0; l < nq; ++l)
+            vn2 -= cq_s[l][0] * cq_s[l][0] + cq_s[l][1] * cq_s[l][1];
+        __syncthreads();
+        return vn2;
+    };
+
+    // w1 = D^-1 w on both blocks (eight lanes per row), the odd part published; the reduced source on the even block
+    {
+        const int blk = half ? be : bo;
+        double re = 0.0, im = 0.0;
+        if (has)
+            for (int l = d; l < Ns; l += 8) {
+                const cpx<T> p = a.Mt[((long)blk * 9 * Ns + l) * Ns + row], w = a.w[(long)blk * Ns + l];
+                re += (double)p.re * (double)w.re - (double)p.im * (double)w.im;
+                im += (double)p.re * (double)w.im + (double)p.im * (double)w.re;
+            }
+        re = sum8(re);
+        im = sum8(im);
+        if (has && d == 0) {
+            const cpx<T> v{(T)re, (T)im};
+            if (half) {
+                w1e_s[row] = v;
+            } else {
+                w1o_s[row] = v;
+                st_agent(ex + (long)bo * Ns + row, v);
+            }
+        }
+    }
+    sync_even();
+    even_half(w1e_s, rhs_s);
+    if (t < Ns) {
+        x_s[t] = cpx<T>{0, 0};
+        r_s[t] = rhs_s[t];
+    }
+    __syncthreads();
+    // ||rhs||^2 and (Q, rhs); then r leaves span Q
+    slot_dot((t >> 3) == 0 ? rhs_s : q_s[((t >> 3) - 1) & (NQ - 1)], rhs_s, SW + (t >> 3), (t >> 3) < 1 + nq);
+    reduce(SW, 1 + nq);
+    const double wn2 = red[0];
+    double rn2 = project(1, wn2);
+    if (t == 0)
+        rn2_s = rn2;
+    __syncthreads();
+
+    int iters = 0;
+    bool converged = !(wn2 > 0.0), broke = false, hit = false;
+    while (!converged && !broke && iters < a.maxiter) {
+        int k = 0;
+        hit = false;
+        for (; k < a.nkv && iters < a.maxiter; ++k) {
+            if (t < Ns)
+                xi_s[k][t] = r_s[t];
+            publish(r_s);
+            const bool far = k > 0 && kTrackNorm && rn2_s > (tol2 + kNormFloor) * wn2;
+            if (k == 0 || far) {
+                sync_odd();
+            } else {
+                slot_dot(r_s, r_s, SC, t < 8);
+                reduce(SC, 1);
+                if (t == 0)
+                    rn2_s = red[0];
+                const double rr = red[0];
+                __syncthreads();
+                if (rr <= tol2 * wn2) {
+                    hit = true;
+                    break;  // converged with k directions
+                }
+            }
+            odd_half();
+            sync_even();
+            even_half(xi_s[k], y_s);
+            // one Gram-Schmidt pass: (chi_j, y), (chi_j, r), ||y||^2, (y, r), (Q_l, y)
+            auto pass = [&](int slot0) {
+                const int ns = 2 * k + 2 + nq;
+                for (int s = t >> 3; s < (ns + 7) / 8 * 8; s += LT1 / 8) {
+                    const cpx<T>* p = s < k ? chi_s[s] : s < 2 * k ? chi_s[s - k] : s < 2 * k + 2 ? y_s
+                                      : q_s[(s - 2 * k - 2) & (NQ - 1)];
+                    slot_dot(p, (s >= k && s < 2 * k) || s == 2 * k + 1 ? r_s : y_s, slot0 + s, s < ns);
+                }
+                reduce(slot0, ns);
+            };
+            pass(SA);
+            const int q0 = 2 * k + 2;
+            if (t < 64) {
+                const int ri = t < k ? 2 * t : 2 * (q0 + t - k);
+                const double m2 = t < k + nq ? red[ri] * red[ri] + red[ri + 1] * red[ri + 1] : 0.0;
+                const double p2 = wave_sum(m2);
+                if (t == 0) {
+                    const double n2 = red[4 * k];
+                    second_s = ((k > 0 || nq > 0) && !(n2 - p2 >= 0.01 * n2)) ? 1 : 0;
+                }
+            }
+            __syncthreads();
+            auto gs_term = [&](int j, double2& c, cpx<T>& v) {
+                const int ri = j < k ? 2 * j : 2 * (q0 + j - k);
+                c = make_double2(red[ri], red[ri + 1]);
+                v = j < k ? chi_s[j][ce] : q_s[j - k][ce];
+            };
+            const bool second = second_s != 0;
+            if (second) {
+                // heavy cancellation: subtract the first projections, then a second pass
+                double sr, si;
+                combine(k + nq, gs_term, sr, si);
+                if (writer)
+                    y_s[ce] = cpx<T>{(T)((double)y_s[ce].re - sr), (T)((double)y_s[ce].im - si)};
+            }
+            if (t < k) {
+                acoef[t][k][0] = second ? red[2 * t] : 0.0;
+                acoef[t][k][1] = second ? red[2 * t + 1] : 0.0;
+            }
+            if (t < nq) {
+                qcoef[t][k][0] = second ? red[2 * (q0 + t)] : 0.0;
+                qcoef[t][k][1] = second ? red[2 * (q0 + t) + 1] : 0.0;
+            }
+            if (second) {
+                __syncthreads();
+                pass(SB);
+            }
+            // red now holds the (last) pass: a_j, (chi_j, r), ||chi||^2, (chi, r)
+            if (t < 64) {
+                double m2 = 0.0, dr = 0.0, di = 0.0;
+                if (t < k) {
+                    const double ar = red[2 * t], ai = red[2 * t + 1];
+                    const double qr = red[2 * (k + t)], qi = red[2 * (k + t) + 1];
+                    m2 = ar * ar + ai * ai;
+                    dr = ar * qr + ai * qi;
+                    di = ar * qi - ai * qr;
+                    acoef[t][k][0] += ar;
+                    acoef[t][k][1] += ai;
+                } else if (t < k + nq) {
+                    const int l = t - k;
+                    const double qr = red[2 * (q0 + l)], qi = red[2 * (q0 + l) + 1];
+                    m2 = qr * qr + qi * qi;
+                }
+                m2 = wave_sum(m2);
+                dr = wave_sum(dr);
+                di = wave_sum(di);
+                if (t == 0) {
+                    const double b2 = red[4 * k] - m2;
+                    const double crr = red[4 * k + 2] - dr, cri = red[4 * k + 3] - di;
+                    const double b = b2 > 0.0 ? sqrt(b2) : 0.0;
+                    bcoef[k] = b;
+                    ccoef[k][0] = b > 0.0 ? crr / b : 0.0;
+                    ccoef[k][1] = b > 0.0 ? cri / b : 0.0;
+                    if (kTrackNorm)
+                        rn2_s -= ccoef[k][0] * ccoef[k][0] + ccoef[k][1] * ccoef[k][1];
+                }
+            }
+            if (t < nq) {
+                qcoef[t][k][0] += red[2 * (q0 + t)];
+                qcoef[t][k][1] += red[2 * (q0 + t) + 1];
+            }
+            __syncthreads();
+            const double b = bcoef[k];
+            if (!(b > 0.0)) {
+                broke = true;  // the new direction lies in the span: end the cycle without it
+                break;
+            }
+            // chi_k = (y - sum_j a_j chi_j - sum_l q_l Q_l) / b; r -= c_k chi_k
+            double sr, si;
+            combine(k + nq, gs_term, sr, si);
+            if (writer) {
+                const double inv = 1.0 / b, cr0 = ccoef[k][0], ci0 = ccoef[k][1];
+                const double yr = ((double)y_s[ce].re - sr) * inv, yi = ((double)y_s[ce].im - si) * inv;
+                chi_s[k][ce] = cpx<T>{(T)yr, (T)yi};
+                r_s[ce] = cpx<T>{(T)((double)r_s[ce].re - (cr0 * yr - ci0 * yi)),
+                                 (T)((double)r_s[ce].im - (cr0 * yi + ci0 * yr))};
+            }
+            ++iters;
+            __syncthreads();
+        }
+        // x += sum_j alpha_j xi_j - sum_l zc_l Z_l, alpha from the triangular system
+        if (t == 0) {
+            for (int i = k - 1; i >= 0; --i) {
+                double sr = ccoef[i][0], si = ccoef[i][1];
+                for (int j = i + 1; j < k; ++j) {
+                    const double ar = acoef[i][j][0], ai = acoef[i][j][1];
+                    sr -= ar * alpha[j][0] - ai * alpha[j][1];
+                    si -= ar * alpha[j][1] + ai * alpha[j][0];
+                }
+                alpha[i][0] = sr / bcoef[i];
+                alpha[i][1] = si / bcoef[i];
+            }
+        }
+        __syncthreads();
+        if (t < nq) {
+            double zr = 0.0, zi = 0.0;
+            for (int j = 0; j < k; ++j) {
+                zr += qcoef[t][j][0] * alpha[j][0] - qcoef[t][j][1] * alpha[j][1];
+                zi += qcoef[t][j][0] * alpha[j][1] + qcoef[t][j][1] * alpha[j][0];
+            }
+            zc[t][0] = zr;
+            zc[t][1] = zi;
+        }
+        __syncthreads();
+        {
+            double sr, si;
+            combine(k + nq, [&](int j, double2& c, cpx<T>& v) {
+                c = j < k ? make_double2(alpha[j][0], alpha[j][1]) : make_double2(-zc[j - k][0], -zc[j - k][1]);
+                v = j < k ? xi_s[j][ce] : z_s[j - k][ce];
+            }, sr, si);
+            if (writer)
+                x_s[ce] = cpx<T>{(T)((double)x_s[ce].re + sr), (T)((double)x_s[ce].im + si)};
+            __syncthreads();
+        }
+        if (kTrackNorm && hit && tol2 >= kLooseTol2) {
+            converged = true;
+            break;
+        }
+        // recompute r = rhs - op(x)
+        publish(x_s);
+        sync_odd();
+        odd_half();
+        sync_even();
+        even_half(x_s, y_s);
+        if (t < Ns)
+            r_s[t] = cpx<T>{(T)((double)rhs_s[t].re - (double)y_s[t].re), (T)((double)rhs_s[t].im - (double)y_s[t].im)};
+        __syncthreads();
+        slot_dot((t >> 3) == 0 ? r_s : q_s[((t >> 3) - 1) & (NQ - 1)], r_s, SW + (t >> 3), (t >> 3) < 1 + nq);
+        reduce(SW, 1 + nq);
+        rn2 = project(1, red[0]);
+        converged = rn2 <= tol2 * wn2;
+        if (t == 0)
+            rn2_s = rn2;  // start of the next cycle's norm updates
+        __syncthreads();
+    }
+    // x_o = w1_o - M_oe x_e
+    publish(x_s);
+    sync_odd();
+    {
+        stage(nb_o);
+        double re, im;
+        rows(re, im);
+        if (has && half == 0 && d == 0)
+            a.x[(long)bo * Ns + row] = cpx<T>{(T)((double)w1o_s[row].re - re), (T)((double)w1o_s[row].im - im)};
+        if (t < Ns)
+            a.x[(long)be * Ns + t] = x_s[t];
+    }
+    if (g == 0 && t == 0) {
+        atomicAdd(&a.stats[0], iters);
+        atomicAdd(&a.stats[1], 1);
+        if (!converged)
+            atomicOr(&a.stats[2], 1);
+    }
+}
+
 // ------------------------------------------------------------ many sources
 //
 // The same GCR for nrhs little systems A v_b = w_b at once: the right-hand
@@ -1663,10 +2193,12 @@ void launch_impl(const Geom& g, int Ns, int nkv, int maxiter, double tol, const 
 // apply's bandwidth with it. Default four blocks per workgroup: with the
 // even-odd operator each apply covers two blocks, one round of the 512
 // threads for Ns up to 32 (measured on 16^4: 64 workgroups beat 32, 48 and
-// 128). At most kLittleMaxGrid workgroups.
-int little_gcr_grid(const Geom& g, int requested)
+// 128). At most kLittleMaxGrid workgroups. Up to 512 blocks the kernel with one
+// block pair per workgroup takes the even-odd solves (pair): it has no cache
+// maintenance in its barriers and no memory access between them.
+int little_gcr_grid(const Geom& g, int requested, bool pair)
 {
-    int G = requested > 0 ? requested : g.Nb / 4;
+    int G = requested > 0 ? requested : pair && g.Nb <= 2 * kLittleMaxGrid ? g.Nb / 2 : g.Nb / 4;
     if (G > kLittleMaxGrid)
         G = kLittleMaxGrid;
     if (G > g.Nb / 2)
@@ -1709,6 +2241,10 @@ int little_gcr_resident_limit(bool multi)
         occ(reinterpret_cast<const void*>(&k_little_gcr<double, false>), LT1);
         occ(reinterpret_cast<const void*>(&k_little_gcr<float, true>), LT1);
         occ(reinterpret_cast<const void*>(&k_little_gcr<float, false>), LT1);
+        occ(reinterpret_cast<const void*>(&k_little_gcr_pair<double, 24>), LT1);
+        occ(reinterpret_cast<const void*>(&k_little_gcr_pair<double, 32>), LT1);
+        occ(reinterpret_cast<const void*>(&k_little_gcr_pair<float, 24>), LT1);
+        occ(reinterpret_cast<const void*>(&k_little_gcr_pair<float, 32>), LT1);
     }
     return per_cu * cus;
 }
@@ -1730,6 +2266,51 @@ void launch_little_gcr(const Geom& g, int Ns, int nkv, int maxiter, double tol, 
     launch_impl<T>(g, Ns, nkv, maxiter, tol, tol_dev, At, Mt, Q, Z, nq, oblique, Ainv, Gw, w, x, r, xi, chi, w1, w2, part,
                    stats, bar_count, bar_gen, grid, s, cooperative);
 }
+
+int little_pair_sources(const Geom& g, int Ns, int grid, int resident)
+{
+    return 2 * grid == g.Nb && Ns <= 32 ? std::max(1, resident / grid) : 0;
+}
+
+template <typename T>
+void launch_little_gcr_pair(const Geom& g, int Ns, int nkv, int maxiter, double tol, const double* tol_dev,
+                            const cpx<T>* Mt, cpx<T>* w1, const cpx<T>* Q, const cpx<T>* Z, int nq, const cpx<T>* w,
+                            cpx<T>* x, double* part, int* stats, unsigned long long* bar, int nsrc, hipStream_t s,
+                            bool cooperative)
+{
+    LittleArgs<T> a{};
+    a.g = g;
+    a.Ns = Ns;
+    a.nkv = nkv;
+    a.maxiter = maxiter;
+    a.tol2 = tol * tol;
+    a.tol_dev = tol_dev;
+    a.Mt = Mt;
+    a.w = w;
+    a.x = x;
+    a.w1 = w1;
+    a.Q = Q;
+    a.Z = Z;
+    a.nq = Q && Z ? nq : 0;
+    a.part = part;
+    a.stats = stats;
+    a.bar_gen = bar + kLittleFlags;
+    const auto pair = Ns <= 24 ? &k_little_gcr_pair<T, 24> : &k_little_gcr_pair<T, 32>;
+    const dim3 grid(g.Nb / 2 * nsrc);
+    if (!cooperative) {
+        hipLaunchKernelGGL(pair, grid, dim3(LT1), 0, s, a);
+        HIPCHECK(hipGetLastError());
+        return;
+    }
+    void* args[] = {&a};
+    HIPCHECK(hipLaunchCooperativeKernel(reinterpret_cast<const void*>(pair), grid, dim3(LT1), args, 0, s));
+}
+template void launch_little_gcr_pair<double>(const Geom&, int, int, int, double, const double*, const c64*, c64*,
+                                             const c64*, const c64*, int, const c64*, c64*, double*, int*,
+                                             unsigned long long*, int, hipStream_t, bool);
+template void launch_little_gcr_pair<float>(const Geom&, int, int, int, double, const double*, const c32*, c32*,
+                                            const c32*, const c32*, int, const c32*, c32*, double*, int*,
+                                            unsigned long long*, int, hipStream_t, bool);
 
 template <typename T>
 void launch_little_gcr_multi(const Geom& g, int Ns, int nkv, int maxiter, double tol, const double* tol_dev, int nrhs,
