@@ -616,7 +616,7 @@ void little_solve_impl(dfl_ctx* c, const c64* w, c64* v, double tol, dfl_prec pr
                                       c->eo_ok ? c->gdefl_n : 0, c->gdefl_oblique, c->gAinv, c->gGw, w, v,
                                       static_cast<c64*>(c->lr),
                                       static_cast<c64*>(c->lxi), static_cast<c64*>(c->lchi), c->lpart, c->lstats,
-                                      c->lbar_count, c->lbar_gen, c->lgrid, c->stream, !c->capturing);
+                                      c->lbar_gen, c->lgrid, c->stream, !c->capturing);
         else
             launch_little_gcr_multi<double>(c->g, Ns, nkv, mi, tol, tol_dev, nb, c->At64, eo_multi ? c->Mt64 : nullptr,
                                             static_cast<c64*>(c->lw1), static_cast<c64*>(c->lw2), w, v,
@@ -640,7 +640,7 @@ void little_solve_impl(dfl_ctx* c, const c64* w, c64* v, double tol, dfl_prec pr
                                          c->eo_ok ? c->gdefl_n : 0, c->gdefl_oblique, c->gAinv, c->gGw, c->lw32,
                                          c->lx32, static_cast<c32*>(c->lr),
                                          static_cast<c32*>(c->lxi), static_cast<c32*>(c->lchi), c->lpart, c->lstats,
-                                         c->lbar_count, c->lbar_gen, c->lgrid, c->stream, !c->capturing);
+                                         c->lbar_gen, c->lgrid, c->stream, !c->capturing);
             else
                 launch_little_gcr_multi<float>(c->g, Ns, nkv, mi, tol, tol_dev, nb, c->At32,
                                                eo_multi ? c->Mt32 : nullptr, static_cast<c32*>(c->lw1),

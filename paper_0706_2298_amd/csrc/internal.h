@@ -436,7 +436,7 @@ template <typename T>
 void launch_little_gcr(const Geom& g, int Ns, int nkv, int maxiter, double tol, const double* tol_dev,
                        const cpx<T>* At, const cpx<T>* Mt, cpx<T>* w1, cpx<T>* w2, const cpx<T>* Q, const cpx<T>* Z,
                        int nq, int oblique, const double* Ainv, const double* Gw, const cpx<T>* w,
-                       cpx<T>* x, cpx<T>* r, cpx<T>* xi, cpx<T>* chi, double* part, int* stats, unsigned* bar_count,
+                       cpx<T>* x, cpx<T>* r, cpx<T>* xi, cpx<T>* chi, double* part, int* stats,
                        unsigned long long* bar_gen, int grid, hipStream_t s, bool cooperative = true);
 
 // The even-odd solves with one block pair per workgroup (minimal-residual

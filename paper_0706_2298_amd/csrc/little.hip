@@ -19,12 +19,13 @@
 //       ||chi_k||^2 - sum |a_j|^2).
 // If that single pass cancels more than 99% of ||chi_k||^2 (orthogonality
 // would suffer), a second pass with its own barrier S3 repeats it.
-// Partial sums are written per workgroup and every workgroup reduces them in
-// the same fixed order, so all workgroups take identical decisions and the
-// result is bit-reproducible. After nkv steps (or convergence) the solution
-// is updated from the triangular system and the residue recomputed as
-// w - A x (two more barriers); convergence is decided on that true residue. The barriers are this file's own (see
-// grid_barrier); the launch is cooperative so all workgroups are resident.
+// Partial sums are written per workgroup, summed in a fixed order by one
+// workgroup per slot and published, so all workgroups take identical decisions
+// and the result is bit-reproducible. After nkv steps (or convergence) the
+// solution is updated from the triangular system and the residue recomputed as
+// w - A x (two more barriers); convergence is decided on that true residue. The
+// barriers are this file's own (flag_barrier, grid_barrier); the launch is
+// cooperative so all workgroups are resident.
 #include <algorithm>
 
 #include "internal.h"
@@ -72,8 +73,8 @@ template <typename T> struct LittleArgs {
     const double* Gw;      //   Gw = W^+ W (nq x nq complex)
     double* part;          // NSLOT * G complex partial sums, then NSLOT published sums
     int* stats;            // [0] += iterations, [1] += solves, [2] |= 1 not converged, |= 4 barrier timeout
-    unsigned* bar_count;   // grid barrier: arrivals (0 between barriers)
-    unsigned long long* bar_gen;  // grid barrier: generation, increases across launches
+    int ucap, tab;         // blocks whose neighbour vectors fit LDS; whether the neighbour table does
+    unsigned long long* bar_gen;  // flags of the workgroups, two each (flag_barrier)
 };
 
 // Grid-wide barrier for a cooperative launch (all workgroups co-resident).
@@ -113,6 +114,61 @@ __device__ inline void grid_barrier(unsigned* count, unsigned long long* gen, un
     __syncthreads();
 }
 
+// What workgroups of the single-source solvers exchange (the operator's
+// argument and intermediate, partial and reduced sums) is written and read with
+// agent-scope relaxed atomics, which are coherent by themselves: their barriers
+// need no cache write-back or invalidation, only that a thread's stores have
+// completed before its workgroup raises its flag, and what a workgroup keeps to
+// itself (matrices, Krylov vectors) stays in its caches.
+template <typename T> __device__ inline cpx<T> ld_agent(const cpx<T>* p)
+{
+    if constexpr (sizeof(T) == 4) {
+        const unsigned long long b = __hip_atomic_load(reinterpret_cast<const unsigned long long*>(p), __ATOMIC_RELAXED,
+                                                       __HIP_MEMORY_SCOPE_AGENT);
+        return cpx<T>{(T)__uint_as_float((unsigned)b), (T)__uint_as_float((unsigned)(b >> 32))};
+    } else {
+        const double* q = reinterpret_cast<const double*>(p);
+        const double re = __hip_atomic_load(q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        const double im = __hip_atomic_load(q + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        return cpx<T>{(T)re, (T)im};
+    }
+}
+template <typename T> __device__ inline void st_agent(cpx<T>* p, cpx<T> v)
+{
+    if constexpr (sizeof(T) == 4) {
+        const unsigned long long b = (unsigned long long)__float_as_uint((float)v.re) |
+                                     ((unsigned long long)__float_as_uint((float)v.im) << 32);
+        __hip_atomic_store(reinterpret_cast<unsigned long long*>(p), b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    } else {
+        double* q = reinterpret_cast<double*>(p);
+        __hip_atomic_store(q, (double)v.re, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __hip_atomic_store(q + 1, (double)v.im, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+}
+
+// With `raise`, sets this workgroup's flag to `target` once all its threads'
+// stores have completed; then every thread with wait >= 0 waits until the flag
+// of workgroup `wait` has reached it (the count may wrap). Polling is bounded;
+// on timeout a failure is recorded and the thread goes on.
+__device__ inline void flag_barrier(unsigned* flags, unsigned target, int g, bool raise, int wait, int* stats)
+{
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (threadIdx.x == 0 && raise)
+        __hip_atomic_store(flags + g, target, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (wait >= 0) {
+        long spin = 0;
+        while ((int)(__hip_atomic_load(flags + wait, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) - target) < 0) {
+            __builtin_amdgcn_s_sleep(1);
+            if (++spin > kSpinLimit) {
+                atomicOr(&stats[2], 4);
+                break;
+            }
+        }
+    }
+    __syncthreads();
+}
+
 __device__ inline double2 cfma_conj(double2 acc, double ar, double ai, double br, double bi)
 {
     // acc += conj(a) * b
@@ -122,6 +178,8 @@ __device__ inline double2 cfma_conj(double2 acc, double ar, double ai, double br
 }
 
 constexpr int kMaxOwned = 1024;  // blocks one workgroup of the even-odd solver may own
+constexpr int kLittleStage = 52 * 1024;              // LDS for staged neighbour vectors
+constexpr int kLittleDynLds = kLittleStage + 36 * 1024 + 1024;  // and the tables of kMaxOwned blocks
 
 // colour (sum of block coordinates mod 2) of block blk
 __device__ inline int block_colour(const Geom& g, int blk)
@@ -166,6 +224,8 @@ template <typename T> struct LittleCtx {
     const int* vb;
     int nvb;
     const int* nbr;
+    cpx<T>* us;  // LDS: the neighbour vectors of up to ucap blocks
+    int ucap;
     __device__ int block(int i) const { return owned_block(g, G, vb ? vb[i] : i); }
     __device__ long entry(int e) const
     {
@@ -174,118 +234,68 @@ template <typename T> struct LittleCtx {
         return (long)block(i) * a.Ns + k;
     }
     __device__ int R() const { return nvb * a.Ns; }
+    // this workgroup's share of a partial-sum slot
+    __device__ void put(int slot, double re, double im) const
+    {
+        st_agent(reinterpret_cast<cpx<double>*>(a.part) + (long)slot * G + g, cpx<double>{re, im});
+    }
 };
 
-// reduce slots [s0, s0 + ns) over the G workgroups into red (complex), identically everywhere
-// Each wavefront reduces kSlotUnroll slots at a time so that their loads are
-// in flight together (the partial sums were written by other workgroups and
-// come from beyond the local L2).
+// Slots of one Gram-Schmidt pass that a wavefront sums at a time, their loads
+// in flight together
 constexpr int kSlotUnroll = 4;
-__device__ inline void reduce_slots(const double* __restrict__ part, int G, int s0, int ns, double* red)
-{
-    constexpr int NW = LT1 / 64;
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    for (int sb = w; sb < ns; sb += NW * kSlotUnroll) {
-        double re[kSlotUnroll], im[kSlotUnroll];
-#pragma unroll
-        for (int u = 0; u < kSlotUnroll; ++u) {
-            re[u] = 0.0;
-            im[u] = 0.0;
-        }
-        // slots past ns read slot ns - 1 (valid memory, result dropped): no
-        // branch separates the loads of the kSlotUnroll slots
-        for (int q = lane; q < G; q += 64) {
-            double2 v[kSlotUnroll];
-#pragma unroll
-            for (int u = 0; u < kSlotUnroll; ++u) {
-                const int s = min(sb + u * NW, ns - 1);
-                v[u] = *reinterpret_cast<const double2*>(part + ((long)(s0 + s) * G + q) * 2);
-            }
-#pragma unroll
-            for (int u = 0; u < kSlotUnroll; ++u) {
-                re[u] += v[u].x;
-                im[u] += v[u].y;
-            }
-        }
-#pragma unroll
-        for (int u = 0; u < kSlotUnroll; ++u) {
-            const int s = sb + u * NW;
-            const double sr = wave_sum(re[u]), si = wave_sum(im[u]);
-            if (s < ns && lane == 0) {
-                red[2 * s] = sr;
-                red[2 * s + 1] = si;
-            }
-        }
-    }
-    __syncthreads();
-}
 
-// Grid barrier that also reduces the partial-sum slots [s0, s0 + ns) over the
-// G workgroups: the workgroup that arrives last sums them (reduce_slots, the
-// same fixed order whichever workgroup it is, so the result is
-// bit-reproducible), writes the ns complex sums to pub and only then publishes
-// the next generation; the others wait for it and read the ns sums instead of
-// all G ns partial sums. One workgroup thus reads the partials once, instead
-// of every workgroup reading all of them from the other XCDs' L2. red: 2 ns
-// doubles in LDS; last_s: an int in LDS. pub is not overwritten before every
-// workgroup has read it (the next such barrier needs every workgroup's
-// arrival first).
-__device__ inline void grid_barrier_reduce(unsigned* count, unsigned long long* gen, unsigned long long& target,
-                                           int* stats, const double* __restrict__ part, double* pub, int G, int s0,
-                                           int ns, double* red, int* last_s)
+// red[0 .. ns) = the sums over the G workgroups of the partial-sum slots s0 ..,
+// the same in all of them: workgroup g sums the slots g, g + G, ..., one
+// wavefront each, and publishes them in pub, and everyone reads those. Ends a
+// flag_barrier of all workgroups. red: 2 ns doubles in LDS.
+__device__ inline void reduce_slots(unsigned* flags, unsigned* rflags, unsigned& target, int* stats, double* part,
+                                    double* pub, int G, int g, int s0, int ns, double* red)
 {
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        ++target;
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-        const unsigned old = __hip_atomic_fetch_add(count, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        const int last = old == gridDim.x - 1;
-        if (last)
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-        *last_s = last;
-    }
-    __syncthreads();
-    if (*last_s) {
-        reduce_slots(part, G, s0, ns, red);
-        for (int q = threadIdx.x; q < 2 * ns; q += blockDim.x)
-            pub[q] = red[q];
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-            __hip_atomic_store(count, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __hip_atomic_store(gen, target, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+    const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
+    const int owners = ns < G ? ns : G;
+    flag_barrier(flags, ++target, g, true, t < G && g < owners ? t : -1, stats);
+    const cpx<double>* pp = reinterpret_cast<const cpx<double>*>(part);
+    cpx<double>* pb = reinterpret_cast<cpx<double>*>(pub);
+    for (int s = g + wv * G; s < ns; s += G * (LT1 / 64)) {
+        cpx<double> v[kLittleMaxGrid / 64];
+#pragma unroll
+        for (int i = 0; i < kLittleMaxGrid / 64; ++i) {
+            const int q = lane + 64 * i;
+            v[i] = q < G ? ld_agent(pp + (long)(s0 + s) * G + q) : cpx<double>{0.0, 0.0};
         }
-        __syncthreads();
-        return;
-    }
-    if (threadIdx.x == 0) {
-        long spin = 0;
-        while (__hip_atomic_load(gen, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < target) {
-            __builtin_amdgcn_s_sleep(1);
-            if (++spin > kSpinLimit) {
-                atomicOr(&stats[2], 4);
-                break;
-            }
+        double re = 0.0, im = 0.0;
+#pragma unroll
+        for (int i = 0; i < kLittleMaxGrid / 64; ++i) {
+            re += v[i].re;
+            im += v[i].im;
         }
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+        re = wave_sum(re);
+        im = wave_sum(im);
+        if (lane == 0)
+            st_agent(pb + s, cpx<double>{re, im});
     }
-    __syncthreads();
-    for (int q = threadIdx.x; q < 2 * ns; q += blockDim.x)
-        red[q] = pub[q];
+    flag_barrier(rflags, target, g, g < owners, t < owners ? t : -1, stats);
+    for (int s = t; s < ns; s += LT1) {
+        const cpx<double> v = ld_agent(pb + s);
+        red[2 * s] = v.re;
+        red[2 * s + 1] = v.im;
+    }
     __syncthreads();
 }
 
 // y_blk = alpha s_blk + beta sum_{d0 <= d < d1} Mat[blk][d] u_{nbr_d(blk)} for
 // the blocks at the listed owned positions (list null: positions 0..nlist-1).
-// Mat is stored transposed, Mat[blk][d][l][k] = (block d of blk)[k][l], so
-// the threads of a block's rows k read Mat coalesced in k (the vector entry
-// u_{nbr_d}[l] is the same address for all of them). A thread sums all
-// terms of one row (or, when the rows do not fill the workgroup, those of a
-// contiguous range of d, the ranges meeting in lds in a fixed order), with
-// kApplyChunk matrix and vector loads of kApplyD neighbour blocks in flight
-// at a time, and writes its row without waiting for the others: y may alias
-// u where the rows written and the entries read lie on different blocks (the
-// even-odd updates). Ends with a workgroup barrier.
+// u is an exchanged vector: the neighbours' entries are fetched into LDS, ucap
+// blocks at a time. Mat is stored transposed, Mat[blk][d][l][k] = (block d of
+// blk)[k][l], so the threads of a block's rows k read Mat coalesced in k. A
+// thread sums all terms of one row (or, when the rows do not fill the
+// workgroup, those of a contiguous range of d, the ranges meeting in lds in a
+// fixed order), with kApplyChunk matrix loads of kApplyD neighbour blocks in
+// flight at a time, and writes its row without waiting for the others: y may
+// alias u where the rows written and the entries read lie on different blocks
+// (the even-odd updates). y is written for exchange. Ends with a workgroup
+// barrier.
 constexpr int kApplyChunk = 8;
 template <typename T>
 __device__ inline void apply_blocks(const LittleCtx<T>& c, const int* list, int nlist, const cpx<T>* __restrict__ Mat,
@@ -296,80 +306,88 @@ __device__ inline void apply_blocks(const LittleCtx<T>& c, const int* list, int 
     const Geom& g = c.a.g;
     const int Ns = c.a.Ns;
     const int nd = d1 - d0;
-    const int rows = nlist * Ns;
-    const int ng = rows > 0 ? max(1, min(LT1 / rows, nd)) : 1;
-    const int per = (nd + ng - 1) / ng;
-    for (int t0 = 0; t0 < ng * rows; t0 += LT1) {
-        const int task = t0 + c.t;
-        if (task < ng * rows) {
-            const int gq = task / rows, row = task - gq * rows;
-            const int ib = row / Ns, k = row - ib * Ns;
-            const int own = list ? list[ib] : ib;
+    for (int b0 = 0; b0 < nlist; b0 += c.ucap) {
+        const int nb = min(c.ucap, nlist - b0);
+        const int rows = nb * Ns;
+        for (int q = c.t; q < rows * nd; q += LT1) {
+            const int l = q % Ns, bd = q / Ns;
+            const int ib = bd / nd, d = d0 + bd - ib * nd;
+            const int own = list ? list[b0 + ib] : b0 + ib;
             const int blk = owned_block(c.g, c.G, own);
-            const int da = d0 + gq * per, dz = min(d1, da + per);
-            double re = 0.0, im = 0.0;
-            for (int db = da; db < dz; db += kApplyD) {
-                const cpx<T>* M[kApplyD];
-                const cpx<T>* uu[kApplyD];
+            const int nbr = d == 0 ? blk : (c.nbr ? c.nbr[8 * own + d - 1] : nbr_block(g, blk, d));
+            c.us[q] = ld_agent(u + (long)nbr * Ns + l);
+        }
+        __syncthreads();
+        const int ng = max(1, min(LT1 / rows, nd));
+        const int per = (nd + ng - 1) / ng;
+        for (int t0 = 0; t0 < ng * rows; t0 += LT1) {
+            const int task = t0 + c.t;
+            if (task < ng * rows) {
+                const int gq = task / rows, row = task - gq * rows;
+                const int ib = row / Ns, k = row - ib * Ns;
+                const int blk = owned_block(c.g, c.G, list ? list[b0 + ib] : b0 + ib);
+                const int da = d0 + gq * per, dz = min(d1, da + per);
+                double re = 0.0, im = 0.0;
+                for (int db = da; db < dz; db += kApplyD) {
+                    const cpx<T>* M[kApplyD];
+                    const cpx<T>* uu[kApplyD];
 #pragma unroll
-                for (int v = 0; v < kApplyD; ++v) {
-                    const int d = min(db + v, dz - 1);  // past dz: a valid block, dropped below
-                    const int nb = d == 0 ? blk : (c.nbr ? c.nbr[8 * own + d - 1] : nbr_block(g, blk, d));
-                    M[v] = Mat + ((long)blk * 9 + d) * Ns * Ns + k;
-                    uu[v] = u + (long)nb * Ns;
+                    for (int v = 0; v < kApplyD; ++v) {
+                        const int d = min(db + v, dz - 1);  // past dz: a valid block, dropped below
+                        M[v] = Mat + ((long)blk * 9 + d) * Ns * Ns + k;
+                        uu[v] = c.us + (ib * nd + d - d0) * Ns;
+                    }
+                    for (int l0 = 0; l0 < Ns; l0 += kApplyChunk) {
+                        cpx<T> mv[kApplyD][kApplyChunk];
+#pragma unroll
+                        for (int v = 0; v < kApplyD; ++v)
+#pragma unroll
+                            for (int q = 0; q < kApplyChunk; ++q)
+                                mv[v][q] = M[v][(long)min(l0 + q, Ns - 1) * Ns];  // past Ns: re-read, dropped below
+#pragma unroll
+                        for (int v = 0; v < kApplyD; ++v)
+#pragma unroll
+                            for (int q = 0; q < kApplyChunk; ++q)
+                                if (db + v < dz && l0 + q < Ns) {
+                                    const cpx<T> p = mv[v][q], w = uu[v][l0 + q];
+                                    re += (double)p.re * (double)w.re - (double)p.im * (double)w.im;
+                                    im += (double)p.re * (double)w.im + (double)p.im * (double)w.re;
+                                }
+                    }
                 }
-                for (int l0 = 0; l0 < Ns; l0 += kApplyChunk) {
-                    cpx<T> mv[kApplyD][kApplyChunk], uv[kApplyD][kApplyChunk];
-#pragma unroll
-                    for (int v = 0; v < kApplyD; ++v)
-#pragma unroll
-                        for (int q = 0; q < kApplyChunk; ++q) {
-                            const int l = min(l0 + q, Ns - 1);  // past Ns: re-read, dropped below
-                            mv[v][q] = M[v][(long)l * Ns];
-                            uv[v][q] = uu[v][l];
-                        }
-#pragma unroll
-                    for (int v = 0; v < kApplyD; ++v)
-#pragma unroll
-                        for (int q = 0; q < kApplyChunk; ++q)
-                            if (db + v < dz && l0 + q < Ns) {
-                                const cpx<T> p = mv[v][q], w = uv[v][q];
-                                re += (double)p.re * (double)w.re - (double)p.im * (double)w.im;
-                                im += (double)p.re * (double)w.im + (double)p.im * (double)w.re;
-                            }
+                if (ng == 1) {
+                    const long i = (long)blk * Ns + k;
+                    double yr = beta * re, yi = beta * im;
+                    if (alpha != 0.0) {
+                        yr += alpha * (double)s[i].re;
+                        yi += alpha * (double)s[i].im;
+                    }
+                    st_agent(y + i, cpx<T>{(T)yr, (T)yi});
+                } else {
+                    lds[2 * task] = re;
+                    lds[2 * task + 1] = im;
                 }
             }
-            if (ng == 1) {
+        }
+        __syncthreads();
+        if (ng > 1) {
+            for (int row = c.t; row < rows; row += LT1) {
+                double sr = 0.0, si = 0.0;
+                for (int gq = 0; gq < ng; ++gq) {
+                    sr += lds[2 * (gq * rows + row)];
+                    si += lds[2 * (gq * rows + row) + 1];
+                }
+                const int ib = row / Ns, k = row - ib * Ns;
+                const int blk = owned_block(c.g, c.G, list ? list[b0 + ib] : b0 + ib);
                 const long i = (long)blk * Ns + k;
-                double yr = beta * re, yi = beta * im;
+                double yr = beta * sr, yi = beta * si;
                 if (alpha != 0.0) {
                     yr += alpha * (double)s[i].re;
                     yi += alpha * (double)s[i].im;
                 }
-                y[i] = cpx<T>{(T)yr, (T)yi};
-            } else {
-                lds[2 * task] = re;
-                lds[2 * task + 1] = im;
+                st_agent(y + i, cpx<T>{(T)yr, (T)yi});
             }
-        }
-    }
-    if (ng > 1) {
-        __syncthreads();
-        for (int row = c.t; row < rows; row += LT1) {
-            double sr = 0.0, si = 0.0;
-            for (int gq = 0; gq < ng; ++gq) {
-                sr += lds[2 * (gq * rows + row)];
-                si += lds[2 * (gq * rows + row) + 1];
-            }
-            const int ib = row / Ns, k = row - ib * Ns;
-            const int blk = owned_block(c.g, c.G, list ? list[ib] : ib);
-            const long i = (long)blk * Ns + k;
-            double yr = beta * sr, yi = beta * si;
-            if (alpha != 0.0) {
-                yr += alpha * (double)s[i].re;
-                yi += alpha * (double)s[i].im;
-            }
-            y[i] = cpx<T>{(T)yr, (T)yi};
+            __syncthreads();
         }
     }
     __syncthreads();
@@ -386,10 +404,8 @@ __device__ inline void partial_norm2(const LittleCtx<T>& c, const cpx<T>* __rest
         s += (double)z.re * (double)z.re + (double)z.im * (double)z.im;
     }
     s = block_sum(s, sh);
-    if (c.t == 0) {
-        c.a.part[((long)slot * c.G + c.g) * 2] = s;
-        c.a.part[((long)slot * c.G + c.g) * 2 + 1] = 0.0;
-    }
+    if (c.t == 0)
+        c.put(slot, s, 0.0);
 }
 
 // Partial sums of one Gram-Schmidt pass over the vector entries, one
@@ -446,10 +462,8 @@ __device__ inline void partial_pass(const LittleCtx<T>& c, const cpx<T>* chi, in
         for (int u = 0; u < kSlotUnroll; ++u) {
             const int s = sb + u * NW;
             const double sr = wave_sum(acc[u].x), si = wave_sum(acc[u].y);
-            if (s < ns && lane == 0) {
-                c.a.part[((long)(slot0 + s) * c.G + c.g) * 2] = sr;
-                c.a.part[((long)(slot0 + s) * c.G + c.g) * 2 + 1] = si;
-            }
+            if (s < ns && lane == 0)
+                c.put(slot0 + s, sr, si);
         }
     }
 }
@@ -476,8 +490,7 @@ __device__ inline void partial_norm2_q(const LittleCtx<T>& c, const cpx<T>* __re
         acc.y = wave_sum(acc.y);
         if (lane == 0) {
             const int slot = s == 0 ? sn : SQ + s - 1;  // (W_l, v) follow the nq (Z_l, v)
-            c.a.part[((long)slot * c.G + c.g) * 2] = acc.x;
-            c.a.part[((long)slot * c.G + c.g) * 2 + 1] = acc.y;
+            c.put(slot, acc.x, acc.y);
         }
     }
 }
@@ -498,10 +511,8 @@ __device__ inline void partial_zdots(const LittleCtx<T>& c, const cpx<T>* __rest
         }
         acc.x = wave_sum(acc.x);
         acc.y = wave_sum(acc.y);
-        if (lane == 0) {
-            c.a.part[((long)(SQ + s) * c.G + c.g) * 2] = acc.x;
-            c.a.part[((long)(SQ + s) * c.G + c.g) * 2 + 1] = acc.y;
-        }
+        if (lane == 0)
+            c.put(SQ + s, acc.x, acc.y);
     }
 }
 
@@ -565,6 +576,16 @@ __device__ inline void combine_terms(const LittleCtx<T>& c, int nterm, CF cf, VF
 //   v_o = (D^-1 w)_o - M_oe v_e.
 // Even-odd workspaces: w1 = D^-1 w (all blocks); w2 holds the reduced source
 // on even blocks and the intermediate M_oe u on odd blocks.
+//
+// What bounds it: the matrices, 16 Nb Ns^2 entries a step, where they exceed
+// the caches (64 x 32^3, Ns = 24: 302 MB in FP32, 604 in FP64), else the latency of
+// its exchanges. Those go through agent-scope atomics and flags without cache
+// maintenance, so the Krylov vectors, and matrices that fit, are read from the
+// workgroup's own L2 instead of beyond it after each barrier; a workgroup waits
+// for its neighbours only before it applies A. MI355X, with fenced barriers
+// before and now: 48 x 24^3 (Ns = 20) 55 and 41 us a step in FP32, 2.91 and
+// 2.27 ms a solve in FP64; 64 x 32^3 1.82 and 1.46 ms a solve in FP32, 7.05 and
+// 6.36 in FP64.
 template <typename T, bool EO> __global__ __launch_bounds__(LT1) void k_little_gcr(LittleArgs<T> a)
 {
     // FP64: the residue norm inside a cycle follows from the coefficients
@@ -587,52 +608,62 @@ template <typename T, bool EO> __global__ __launch_bounds__(LT1) void k_little_g
     __shared__ double sh[16];
     __shared__ double wn2_s, rn2_s;
     __shared__ int second_s;
-    __shared__ int last_s;
     __shared__ double lds[2 * LT1];
-    __shared__ int l_even[EO ? kMaxOwned : 1], l_odd[EO ? kMaxOwned : 1];  // owned positions by colour
-    __shared__ int n_even_s, n_odd_s;
-    __shared__ int nbr_tab[8 * kMaxOwned];  // neighbours of the owned blocks, computed once
-
+    // neighbour vectors of ucap blocks, the owned positions by colour (a pair has one of either),
+    // and the neighbours of the owned blocks where they fit (tab)
+    extern __shared__ char dyn[];
     const int G = (int)gridDim.x, gi = (int)blockIdx.x, t = (int)threadIdx.x;
     const int nbg = owned_count(a.g.Nb, gi, G);
-    const bool tab = nbg <= kMaxOwned;
+    const bool tab = a.tab != 0;
+    cpx<T>* us = reinterpret_cast<cpx<T>*>(dyn);
+    int* l_even = reinterpret_cast<int*>(us + (size_t)a.ucap * (EO ? 8 : 9) * a.Ns);
+    int* l_odd = l_even + nbg / 2;
+    int* nbr_tab = l_odd + nbg / 2;
     if (tab)
         for (int q = t; q < 8 * nbg; q += LT1)
             nbr_tab[q] = nbr_block(a.g, owned_block(gi, G, q >> 3), 1 + (q & 7));
-    if (EO && t == 0) {
-        int ne = 0, no = 0;
-        for (int i = 0; i < nbg; ++i) {
-            if (block_colour(a.g, owned_block(gi, G, i)))
-                l_odd[no++] = i;
-            else
-                l_even[ne++] = i;
+    if (EO)
+        for (int q = t; q < nbg / 2; q += LT1) {
+            const int odd = block_colour(a.g, owned_block(gi, G, 2 * q));
+            l_even[q] = 2 * q + odd;
+            l_odd[q] = 2 * q + 1 - odd;
         }
-        n_even_s = ne;
-        n_odd_s = no;
-    }
     __syncthreads();
-    const int n_even = EO ? n_even_s : 0, n_odd = EO ? n_odd_s : 0;
-    LittleCtx<T> c{a, G, gi, t, (long)a.g.Nb * a.Ns, EO ? l_even : nullptr, EO ? n_even : nbg, tab ? nbr_tab : nullptr};
+    const int n_even = EO ? nbg / 2 : 0, n_odd = n_even;
+    LittleCtx<T> c{a, G, gi, t, (long)a.g.Nb * a.Ns, EO ? l_even : nullptr, EO ? n_even : nbg, tab ? nbr_tab : nullptr,
+                   us, a.ucap};
     const double tol2 = a.tol_dev ? (*a.tol_dev) * (*a.tol_dev) : a.tol2;
-    unsigned long long bar_target = 0;
-    if (c.t == 0)
-        bar_target = __hip_atomic_load(a.bar_gen, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    unsigned* const flags = reinterpret_cast<unsigned*>(a.bar_gen);
+    unsigned* const rflags = flags + kLittleMaxGrid;
+    unsigned target = __hip_atomic_load(flags + gi, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (t == 0)  // raised by some reductions only: not to fall behind by more than a launch
+        __hip_atomic_store(rflags + gi, target, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    // Barriers after which a workgroup reads its neighbours' blocks wait for their owners only: what they
+    // read is not overwritten before the next reduction, which every workgroup takes part in
+    const bool few = 8 * nbg <= LT1 && tab;
+    auto owner = [&](int own) { return (nbr_tab[8 * own + (t & 7)] >> 1) % G; };
+    auto wait_for = [&](const int* list, int n) {
+        return few ? ((t >> 3) < n ? owner(list ? list[t >> 3] : t >> 3) : -1) : t < G ? t : -1;
+    };
+    const int wait_1 = wait_for(EO ? l_odd : nullptr, EO ? n_odd : nbg), wait_2 = EO ? wait_for(l_even, n_even) : -1;
+    auto sync_1 = [&]() { flag_barrier(flags, ++target, gi, true, wait_1, a.stats); };  // before op's first half
+    auto sync_2 = [&]() { flag_barrier(flags, ++target, gi, true, wait_2, a.stats); };  // before its second
     const long N = c.N;
     const int R = c.R();
     // op: y = A u (plain) or y = u - M_eo M_oe u on even blocks (one more barrier)
     auto op = [&](const cpx<T>* u, cpx<T>* y) {
         if (EO) {
             apply_blocks(c, l_odd, n_odd, a.Mt, 1, 9, u, (const cpx<T>*)nullptr, 0.0, 1.0, a.w2, lds);
-            grid_barrier(a.bar_count, a.bar_gen, bar_target, a.stats);
+            sync_2();
             apply_blocks(c, l_even, n_even, a.Mt, 1, 9, (const cpx<T>*)a.w2, u, 1.0, -1.0, y, lds);
         } else {
             apply_blocks(c, (const int*)nullptr, nbg, a.At, 0, 9, u, (const cpx<T>*)nullptr, 0.0, 1.0, y, lds);
         }
     };
-    // a grid barrier whose last arrival reduces slots [s0, s0 + ns) into red for everyone
+    // a barrier of all workgroups that reduces slots [s0, s0 + ns) into red for everyone
     double* const pub = a.part + (long)NSLOT * G * 2;
     auto barrier_reduce = [&](int s0, int ns) {
-        grid_barrier_reduce(a.bar_count, a.bar_gen, bar_target, a.stats, a.part, pub, G, s0, ns, red, &last_s);
+        reduce_slots(flags, rflags, target, a.stats, a.part, pub, G, gi, s0, ns, red);
     };
     // red[q] = red[from + q], q < n (then a workgroup barrier)
     auto shift_red = [&](int from, int n) {
@@ -645,7 +676,7 @@ template <typename T, bool EO> __global__ __launch_bounds__(LT1) void k_little_g
     const cpx<T>* rhs = a.w;
     if (EO) {
         apply_blocks(c, (const int*)nullptr, nbg, a.Mt, 0, 1, a.w, (const cpx<T>*)nullptr, 0.0, 1.0, a.w1, lds);
-        grid_barrier(a.bar_count, a.bar_gen, bar_target, a.stats);
+        sync_2();
         apply_blocks(c, l_even, n_even, a.Mt, 1, 9, (const cpx<T>*)a.w1, (const cpx<T>*)a.w1, 1.0, -1.0, a.w2, lds);
         rhs = a.w2;
     }
@@ -705,14 +736,14 @@ template <typename T, bool EO> __global__ __launch_bounds__(LT1) void k_little_g
             a.r[i] = cpx<T>{(T)((double)a.r[i].re - sr), (T)((double)a.r[i].im - si)};
         });
         combine_terms(c, nq, cq, [&](int l) { return a.Z + (long)l * N; }, lds, [&](int, long i, double sr, double si) {
-            a.x[i] = cpx<T>{(T)((double)a.x[i].re + sr), (T)((double)a.x[i].im + si)};
+            st_agent(a.x + i, cpx<T>{(T)((double)a.x[i].re + sr), (T)((double)a.x[i].im + si)});
         });
     };
 
     // x = 0, r = rhs, ||rhs||^2 and (Q, rhs); then r leaves span Q
     for (int e = c.t; e < R; e += LT1) {
         long i = c.entry(e);
-        a.x[i] = cpx<T>{0, 0};
+        st_agent(a.x + i, cpx<T>{0, 0});
         a.r[i] = rhs[i];
     }
     partial_norm2_q(c, rhs, SW);
@@ -759,13 +790,13 @@ template <typename T, bool EO> __global__ __launch_bounds__(LT1) void k_little_g
                 if (k == 0)
                     for (int e = c.t; e < R; e += LT1) {
                         long i = c.entry(e);
-                        xk[i] = a.r[i];  // xi_k = r (else written by the previous step's update)
+                        st_agent(xk + i, a.r[i]);  // xi_k = r (else written by the previous step's update)
                     }
-                grid_barrier(a.bar_count, a.bar_gen, bar_target, a.stats);  // S1: xi_k complete everywhere
+                sync_1();  // S1: xi_k complete where it is read
             } else {
                 for (int e = c.t; e < R; e += LT1) {
                     long i = c.entry(e);
-                    xk[i] = a.r[i];
+                    st_agent(xk + i, a.r[i]);
                 }
                 partial_norm2(c, a.r, SC, sh);
                 barrier_reduce(SC, 1);  // S1: r complete everywhere
@@ -908,7 +939,7 @@ template <typename T, bool EO> __global__ __launch_bounds__(LT1) void k_little_g
                     double ri = (double)a.r[i].im - (cr0 * yi + ci0 * yr);
                     a.r[i] = cpx<T>{(T)rr, (T)ri};
                     if (kTrackNorm && k + 1 < a.nkv)
-                        xnext[i] = cpx<T>{(T)rr, (T)ri};  // xi_{k+1} = r
+                        st_agent(xnext + i, cpx<T>{(T)rr, (T)ri});  // xi_{k+1} = r
                 });
             ++iters;
             __syncthreads();
@@ -946,7 +977,7 @@ template <typename T, bool EO> __global__ __launch_bounds__(LT1) void k_little_g
             },
             [&](int j) { return j < k ? a.xi + (long)j * N : a.Z + (long)(j - k) * N; }, lds,
             [&](int, long i, double sr, double si) {
-                a.x[i] = cpx<T>{(T)((double)a.x[i].re + sr), (T)((double)a.x[i].im + si)};
+                st_agent(a.x + i, cpx<T>{(T)((double)a.x[i].re + sr), (T)((double)a.x[i].im + si)});
             });
         if (kTrackNorm && hit && tol2 >= kLooseTol2) {
             converged = true;
@@ -954,7 +985,7 @@ template <typename T, bool EO> __global__ __launch_bounds__(LT1) void k_little_g
             break;
         }
         // recompute r = rhs - op(x)
-        grid_barrier(a.bar_count, a.bar_gen, bar_target, a.stats);
+        sync_1();
         op(a.x, a.r);
         __syncthreads();
         for (int e = c.t; e < R; e += LT1) {
@@ -990,7 +1021,7 @@ template <typename T, bool EO> __global__ __launch_bounds__(LT1) void k_little_g
         // update unless the solve ended without the residue recomputation,
         // and none followed the projection along Z that may come after it
         if (nq > 0 || skipped)
-            grid_barrier(a.bar_count, a.bar_gen, bar_target, a.stats);
+            sync_1();
         apply_blocks(c, l_odd, n_odd, a.Mt, 1, 9, (const cpx<T>*)a.x, (const cpx<T>*)a.w1, 1.0, -1.0, a.x, lds);
     }
     if (c.g == 0 && c.t == 0) {
@@ -1020,55 +1051,6 @@ template <typename T, bool EO> __global__ __launch_bounds__(LT1) void k_little_g
 // takes 0.58 ms (k_little_gcr: 1.20), 18 us a step of which 8 are the reduction
 // over 256 workgroups; on 8^4 9 us a step (30). P_L of five fields on 8^4 0.26 ms
 // (one batched solve: 2.5).
-
-template <typename T> __device__ inline cpx<T> ld_agent(const cpx<T>* p)
-{
-    if constexpr (sizeof(T) == 4) {
-        const unsigned long long b = __hip_atomic_load(reinterpret_cast<const unsigned long long*>(p), __ATOMIC_RELAXED,
-                                                       __HIP_MEMORY_SCOPE_AGENT);
-        return cpx<T>{(T)__uint_as_float((unsigned)b), (T)__uint_as_float((unsigned)(b >> 32))};
-    } else {
-        const double* q = reinterpret_cast<const double*>(p);
-        const double re = __hip_atomic_load(q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        const double im = __hip_atomic_load(q + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        return cpx<T>{(T)re, (T)im};
-    }
-}
-template <typename T> __device__ inline void st_agent(cpx<T>* p, cpx<T> v)
-{
-    if constexpr (sizeof(T) == 4) {
-        const unsigned long long b = (unsigned long long)__float_as_uint((float)v.re) |
-                                     ((unsigned long long)__float_as_uint((float)v.im) << 32);
-        __hip_atomic_store(reinterpret_cast<unsigned long long*>(p), b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    } else {
-        double* q = reinterpret_cast<double*>(p);
-        __hip_atomic_store(q, (double)v.re, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_store(q + 1, (double)v.im, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-}
-
-// With `raise`, sets this workgroup's flag to `target` once all its threads'
-// stores have completed; then every thread with wait >= 0 waits until the flag
-// of workgroup `wait` has reached it (the count may wrap). Polling is bounded;
-// on timeout a failure is recorded and the thread goes on.
-__device__ inline void flag_barrier(unsigned* flags, unsigned target, int g, bool raise, int wait, int* stats)
-{
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();
-    if (threadIdx.x == 0 && raise)
-        __hip_atomic_store(flags + g, target, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (wait >= 0) {
-        long spin = 0;
-        while ((int)(__hip_atomic_load(flags + wait, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) - target) < 0) {
-            __builtin_amdgcn_s_sleep(1);
-            if (++spin > kSpinLimit) {
-                atomicOr(&stats[2], 4);
-                break;
-            }
-        }
-    }
-    __syncthreads();
-}
 
 // sums over aligned groups of 8 and 16 lanes, in every lane
 __device__ inline double sum8(double v)
@@ -1115,6 +1097,8 @@ template <typename T, int NL> __global__ __launch_bounds__(LT1) void k_little_gc
     unsigned* const flags = reinterpret_cast<unsigned*>(a.bar_gen) + (long)src * 2 * kLittleMaxGrid;  // one per workgroup
     unsigned* const rflags = flags + kLittleMaxGrid;                 // of the reductions
     unsigned target = __hip_atomic_load(flags + g, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (t == 0)  // raised by some reductions only: not to fall behind by more than a launch
+        __hip_atomic_store(rflags + g, target, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     cpx<T>* const ex = a.w1;  // exchanged vectors: the operator's argument (even) and intermediate (odd blocks)
     double* const pub = a.part + (long)NSLOT * G * 2;
 
@@ -2141,7 +2125,7 @@ template <typename T>
 void launch_impl(const Geom& g, int Ns, int nkv, int maxiter, double tol, const double* tol_dev, const cpx<T>* At,
                  const cpx<T>* Mt, const cpx<T>* Q, const cpx<T>* Z, int nq, int oblique, const double* Ainv,
                  const double* Gw, const cpx<T>* w, cpx<T>* x, cpx<T>* r,
-                 cpx<T>* xi, cpx<T>* chi, cpx<T>* w1, cpx<T>* w2, double* part, int* stats, unsigned* bar_count,
+                 cpx<T>* xi, cpx<T>* chi, cpx<T>* w1, cpx<T>* w2, double* part, int* stats,
                  unsigned long long* bar_gen, int grid_size, hipStream_t s, bool cooperative)
 {
     LittleArgs<T> a;
@@ -2170,29 +2154,36 @@ void launch_impl(const Geom& g, int Ns, int nkv, int maxiter, double tol, const 
         fail(DFL_EINVAL, "oblique little deflation needs the inverse and Gram matrices");
     a.part = part;
     a.stats = stats;
-    a.bar_count = bar_count;
-    a.bar_gen = bar_gen;
+    a.bar_gen = bar_gen + kLittleFlags;
+    // dynamic LDS: the neighbour vectors of up to kLittleStage bytes, the block lists and, where it fits, the
+    // neighbour table
+    const int nbg = 2 * ((g.Nb / 2 + grid_size - 1) / grid_size);
+    const size_t per_block = (size_t)(Mt ? 8 : 9) * Ns * sizeof(cpx<T>);
+    a.ucap = std::max(1, std::min(Mt ? nbg / 2 : nbg, (int)(kLittleStage / per_block)));
+    a.tab = nbg <= kMaxOwned;
+    const size_t lds = a.ucap * per_block + sizeof(int) * (size_t)(Mt || a.tab ? nbg * (a.tab ? 9 : 1) : 0);
     const void* fn = Mt ? reinterpret_cast<const void*>(&k_little_gcr<T, true>)
                         : reinterpret_cast<const void*>(&k_little_gcr<T, false>);
+    static std::once_flag attr[2];
+    set_max_lds_once(attr[Mt ? 1 : 0], fn, kLittleDynLds);
     if (!cooperative) {
         if (Mt)
-            hipLaunchKernelGGL((k_little_gcr<T, true>), dim3(grid_size), dim3(LT1), 0, s, a);
+            hipLaunchKernelGGL((k_little_gcr<T, true>), dim3(grid_size), dim3(LT1), lds, s, a);
         else
-            hipLaunchKernelGGL((k_little_gcr<T, false>), dim3(grid_size), dim3(LT1), 0, s, a);
+            hipLaunchKernelGGL((k_little_gcr<T, false>), dim3(grid_size), dim3(LT1), lds, s, a);
         HIPCHECK(hipGetLastError());
         return;
     }
     void* args[] = {&a};
-    HIPCHECK(hipLaunchCooperativeKernel(fn, dim3(grid_size), dim3(LT1), args, 0, s));
+    HIPCHECK(hipLaunchCooperativeKernel(fn, dim3(grid_size), dim3(LT1), args, (unsigned)lds, s));
 }
 
 }  // namespace
 
-// The barrier and reduction costs grow with the workgroup count (a barrier
-// takes about 2.2 us at 64 and 3.4 us at 128 workgroups on MI355X), the
-// apply's bandwidth with it. Default four blocks per workgroup: with the
-// even-odd operator each apply covers two blocks, one round of the 512
-// threads for Ns up to 32 (measured on 16^4: 64 workgroups beat 32, 48 and
+// The barrier and reduction costs grow with the workgroup count, the apply's
+// bandwidth with it. Default four blocks per workgroup: with the even-odd
+// operator each apply covers two blocks, one round of the 512 threads for Ns
+// up to 32 (measured on 16^4 in this kernel: 64 workgroups beat 32, 48 and
 // 128). At most kLittleMaxGrid workgroups. Up to 512 blocks the kernel with one
 // block pair per workgroup takes the even-odd solves (pair): it has no cache
 // maintenance in its barriers and no memory access between them.
@@ -2226,9 +2217,11 @@ int little_gcr_resident_limit(bool multi)
     HIPCHECK(hipGetDevice(&dev));
     HIPCHECK(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
     int per_cu = 1 << 30;
-    auto occ = [&](const void* fn, int threads) {
+    auto occ = [&](const void* fn, int threads, size_t lds = 0) {
         int n = 0;
-        HIPCHECK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, fn, threads, 0));
+        if (lds)
+            HIPCHECK(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
+        HIPCHECK(hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, fn, threads, lds));
         per_cu = n < per_cu ? n : per_cu;
     };
     if (multi) {
@@ -2237,10 +2230,10 @@ int little_gcr_resident_limit(bool multi)
         occ(reinterpret_cast<const void*>(&k_little_gcr_multi<double, true>), LT);
         occ(reinterpret_cast<const void*>(&k_little_gcr_multi<float, true>), LT);
     } else {
-        occ(reinterpret_cast<const void*>(&k_little_gcr<double, true>), LT1);
-        occ(reinterpret_cast<const void*>(&k_little_gcr<double, false>), LT1);
-        occ(reinterpret_cast<const void*>(&k_little_gcr<float, true>), LT1);
-        occ(reinterpret_cast<const void*>(&k_little_gcr<float, false>), LT1);
+        occ(reinterpret_cast<const void*>(&k_little_gcr<double, true>), LT1, kLittleDynLds);
+        occ(reinterpret_cast<const void*>(&k_little_gcr<double, false>), LT1, kLittleDynLds);
+        occ(reinterpret_cast<const void*>(&k_little_gcr<float, true>), LT1, kLittleDynLds);
+        occ(reinterpret_cast<const void*>(&k_little_gcr<float, false>), LT1, kLittleDynLds);
         occ(reinterpret_cast<const void*>(&k_little_gcr_pair<double, 24>), LT1);
         occ(reinterpret_cast<const void*>(&k_little_gcr_pair<double, 32>), LT1);
         occ(reinterpret_cast<const void*>(&k_little_gcr_pair<float, 24>), LT1);
@@ -2260,11 +2253,11 @@ template <typename T>
 void launch_little_gcr(const Geom& g, int Ns, int nkv, int maxiter, double tol, const double* tol_dev, const cpx<T>* At,
                        const cpx<T>* Mt, cpx<T>* w1, cpx<T>* w2, const cpx<T>* Q, const cpx<T>* Z, int nq, int oblique,
                        const double* Ainv, const double* Gw, const cpx<T>* w,
-                       cpx<T>* x, cpx<T>* r, cpx<T>* xi, cpx<T>* chi, double* part, int* stats, unsigned* bar_count,
+                       cpx<T>* x, cpx<T>* r, cpx<T>* xi, cpx<T>* chi, double* part, int* stats,
                        unsigned long long* bar_gen, int grid, hipStream_t s, bool cooperative)
 {
     launch_impl<T>(g, Ns, nkv, maxiter, tol, tol_dev, At, Mt, Q, Z, nq, oblique, Ainv, Gw, w, x, r, xi, chi, w1, w2, part,
-                   stats, bar_count, bar_gen, grid, s, cooperative);
+                   stats, bar_gen, grid, s, cooperative);
 }
 
 int little_pair_sources(const Geom& g, int Ns, int grid, int resident)
@@ -2376,11 +2369,11 @@ INST_MULTI(float)
 
 template void launch_little_gcr<double>(const Geom&, int, int, int, double, const double*, const c64*, const c64*,
                                         c64*, c64*, const c64*, const c64*, int, int, const double*, const double*,
-                                        const c64*, c64*, c64*, c64*, c64*, double*, int*, unsigned*,
+                                        const c64*, c64*, c64*, c64*, c64*, double*, int*,
                                         unsigned long long*, int, hipStream_t, bool);
 template void launch_little_gcr<float>(const Geom&, int, int, int, double, const double*, const c32*, const c32*,
                                        c32*, c32*, const c32*, const c32*, int, int, const double*, const double*,
-                                       const c32*, c32*, c32*, c32*, c32*, double*, int*, unsigned*,
+                                       const c32*, c32*, c32*, c32*, c32*, double*, int*,
                                        unsigned long long*, int, hipStream_t, bool);
 
 }  // namespace dfl
