@@ -1359,7 +1359,7 @@ int dfl_create(dfl_ctx** out, const dfl_params* p, void* hip_stream)
             fail(DFL_EHIP, "the little GCR kernels cannot be resident on this device");
         if (p->little_eo && p->little_gdefl != 2)
             c->lpair = std::min(little_pair_sources(c->g, p->Ns, c->lgrid, resident), (int)R);
-        size_t part = little_gcr_partial_doubles(c->lgrid) * std::max(1, c->lpair);
+        size_t part = std::max(little_gcr_partial_doubles(c->lgrid), little_pair_partial_doubles(c->lgrid) * c->lpair);
         if (R > 1) {
             size_t nfin = 0, nac = 0;
             part = std::max(part, little_gcr_multi_doubles(c->lgrid_multi, (int)R, &nfin, &nac));

@@ -11,6 +11,7 @@
 
 #include "common.h"
 #include "dfl.h"
+#include "little_slots.h"
 
 namespace dfl {
 
@@ -63,12 +64,10 @@ struct LinksBF16 {
 constexpr int kRedBlocks = 480;   // fixed grid of the partial-sum kernels (deterministic)
 constexpr int kRedThreads = 256;
 constexpr int kMaxDot = 64;       // most vectors in one multi-dot
-constexpr int kMaxLittleNkv = 32; // most Krylov vectors of the little GCR
 constexpr int kLittleMaxGrid = 256;  // workgroups of the cooperative little GCR (one per CU)
 constexpr int kLittleFlags = 32;        // barrier words before the per-workgroup flags
 constexpr int kLittleBarWords = kLittleMaxGrid;  // flags of one source (two per workgroup), in 64-bit words
 constexpr int kMaxLittleRhs = 16;    // right-hand sides of one batched little solve
-constexpr int kMaxLittleDefl = 32;   // global deflation directions of the little system
 constexpr int kCloverComp = 36;         // complex entries of the clover term per site (two packed 6 x 6 blocks)
 constexpr int kLittleMaxGridMulti = 256;  // workgroups of the batched little GCR (one per CU)
 
@@ -442,8 +441,9 @@ void launch_little_gcr(const Geom& g, int Ns, int nkv, int maxiter, double tol, 
 // The even-odd solves with one block pair per workgroup (minimal-residual
 // deflation): sources that one launch takes side by side with `resident`
 // workgroups on the device, 0 if the grid of little_gcr_grid is not one
-// workgroup per pair; part (little_gcr_partial_doubles each) and the flags
+// workgroup per pair; part (little_pair_partial_doubles each) and the flags
 // (kLittleBarWords each, after the kLittleFlags words of bar) are per source.
+size_t little_pair_partial_doubles(int grid);
 int little_pair_sources(const Geom& g, int Ns, int grid, int resident);
 template <typename T>
 void launch_little_gcr_pair(const Geom& g, int Ns, int nkv, int maxiter, double tol, const double* tol_dev,

@@ -38,16 +38,7 @@ constexpr int LT = 1024;            // threads per workgroup of the many-source 
 constexpr int LT1 = 512;            // threads per workgroup of the single-source solver: a few blocks per
                                     // workgroup need no more, and 512 threads leave 256 VGPRs per lane
 constexpr long kSpinLimit = 1L << 24;  // ~0.5 s of polling before a barrier gives up
-constexpr int NK = kMaxLittleNkv;
-// partial-sum slots
-constexpr int NQ = kMaxLittleDefl;   // most global deflation directions of the little system
-constexpr int SA = 0;                 // first pass: (chi_j, chi_k) j<k | (chi_j, r) j<k | ||chi_k||^2 | (chi_k, r) | (Q_l, chi_k)
-constexpr int SB = 2 * NK + 2 + NQ;   // second pass, same layout
-constexpr int SC = 2 * SB;            // ||r||^2 inside a cycle
-constexpr int SR = SC + 1;            // ||r||^2 after a restart
-constexpr int SW = SC + 2;            // ||w||^2
-constexpr int SQ = SC + 3;            // (Q_l, r), or (Z_l, r) then (W_l, r), at the start and after a restart
-constexpr int NSLOT = SQ + 2 * NQ;
+using namespace little;              // the partial-sum slots
 static_assert(NK + NQ <= 64, "the coefficient step gives each projection one lane of a wavefront");
 
 template <typename T> struct LittleArgs {
@@ -1066,8 +1057,6 @@ __device__ inline double sum16(double v)
     return v + wave_detail::row<0x140>(v);
 }
 
-constexpr int kPairAllRead = 16;  // up to so many workgroups, each sums all partial sums itself
-
 template <typename T, int NL> __global__ __launch_bounds__(LT1) void k_little_gcr_pair(LittleArgs<T> a)
 {
     constexpr bool kTrackNorm = sizeof(T) == sizeof(double);
@@ -1089,7 +1078,7 @@ template <typename T, int NL> __global__ __launch_bounds__(LT1) void k_little_gc
     a.w += (long)src * a.g.Nb * Ns;
     a.x += (long)src * a.g.Nb * Ns;
     a.w1 += (long)src * a.g.Nb * Ns;
-    a.part += (long)src * NSLOT * (G + 1) * 2;
+    a.part += (long)src * NSLOT_PAIR * (G + 1) * 2;
     const int lane = t & 63, wv = t >> 6;
     const int first_even = block_colour(a.g, 2 * g) == 0;
     const int be = 2 * g + (first_even ? 0 : 1), bo = 2 * g + (first_even ? 1 : 0);
@@ -1100,10 +1089,10 @@ template <typename T, int NL> __global__ __launch_bounds__(LT1) void k_little_gc
     if (t == 0)  // raised by some reductions only: not to fall behind by more than a launch
         __hip_atomic_store(rflags + g, target, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     cpx<T>* const ex = a.w1;  // exchanged vectors: the operator's argument (even) and intermediate (odd blocks)
-    double* const pub = a.part + (long)NSLOT * G * 2;
+    double* const pub = a.part + (long)NSLOT_PAIR * G * 2;
 
-    // waits for the owners of the odd (even) block's neighbours only: what they read is not overwritten
-    // before the next reduction, which every workgroup takes part in
+    // waits for the owners of the odd (even) block's neighbours only: the exchanged vectors that they read are
+    // not overwritten before the next reduction, which every workgroup takes part in
     const int wait_o = t < 8 ? nbr_block(a.g, bo, t + 1) >> 1 : -1, wait_e = t < 8 ? nbr_block(a.g, be, t + 1) >> 1 : -1;
     auto sync_odd = [&]() { flag_barrier(flags, ++target, g, true, wait_o, a.stats); };
     auto sync_even = [&]() { flag_barrier(flags, ++target, g, true, wait_e, a.stats); };
@@ -1348,7 +1337,7 @@ template <typename T, int NL> __global__ __launch_bounds__(LT1) void k_little_gc
                 }
                 reduce(slot0, ns);
             };
-            pass(SA);
+            pass(pair_first_slot(k));
             const int q0 = 2 * k + 2;
             if (t < 64) {
                 const int ri = t < k ? 2 * t : 2 * (q0 + t - k);
@@ -2264,6 +2253,8 @@ int little_pair_sources(const Geom& g, int Ns, int grid, int resident)
 {
     return 2 * grid == g.Nb && Ns <= 32 ? std::max(1, resident / grid) : 0;
 }
+
+size_t little_pair_partial_doubles(int grid) { return (size_t)NSLOT_PAIR * (grid + 1) * 2; }
 
 template <typename T>
 void launch_little_gcr_pair(const Geom& g, int Ns, int nkv, int maxiter, double tol, const double* tol_dev,
