@@ -174,13 +174,13 @@ template <typename L> __device__ inline su3<float> expand_lds(const Link2<L>& l,
 
 // B4: 4^4 blocks, whose extents, in-block strides and LDS plane size are
 // compile-time constants (every LDS access of a hop is then an immediate
-// offset from the thread's own address). Blocks of 257..512 sites run one per
-// CU.
-template <typename L, bool B4>
-__global__ __launch_bounds__(B4 ? 256 : 512, 2) void k_sap_rl(Geom g, SapGeom sg, L U, const c32* __restrict__ rho,
-                                               const double* __restrict__ rho_nrm2, c32* __restrict__ psi,
-                                               float diag, int nmr, int colour, int nrhs, int init,
-                                               c64* __restrict__ out64)
+// offset from the thread's own address). BIG: blocks of 257..512 sites, one per
+// CU, the lanes' products summed in FP64.
+template <typename L, bool B4, bool BIG>
+__global__ __launch_bounds__(BIG ? 512 : 256, 2) void k_sap_rl(Geom g, SapGeom sg, L U, const c32* __restrict__ rho,
+                                                               const double* __restrict__ rho_nrm2,
+                                                               c32* __restrict__ psi, float diag, int nmr, int colour,
+                                                               int nrhs, int init, c64* __restrict__ out64)
 {
     const int Vsb = B4 ? 256 : sg.Vsb;
     int sbl[4], lst[4];
@@ -294,8 +294,9 @@ __global__ __launch_bounds__(B4 ? 256 : 512, 2) void k_sap_rl(Geom g, SapGeom sg
                     acc.s[al].c[a] = cpx<float>{-2.0f * diag * r.s[al].c[a].re, -2.0f * diag * r.s[al].c[a].im};
         }
         __syncthreads();
-        // the lane's products summed in FP32, the block sums in FP64
-        float fr_re = 0.0f, fr_im = 0.0f, fqq = 0.0f;
+        // the lane's products, then the block sums in FP64
+        using S = std::conditional_t<BIG, double, float>;
+        S fr_re = 0, fr_im = 0, fqq = 0;
         if (active) {
 #pragma unroll
             for (int h = 0; h < 8; ++h) {
@@ -322,8 +323,8 @@ __global__ __launch_bounds__(B4 ? 256 : 512, 2) void k_sap_rl(Geom g, SapGeom sg
             for (int al = 0; al < 4; ++al)
 #pragma unroll
                 for (int a = 0; a < 3; ++a) {
-                    const float qa = acc.s[al].c[a].re, qb = acc.s[al].c[a].im;
-                    const float ra = r.s[al].c[a].re, rb = r.s[al].c[a].im;
+                    const S qa = acc.s[al].c[a].re, qb = acc.s[al].c[a].im;
+                    const S ra = r.s[al].c[a].re, rb = r.s[al].c[a].im;
                     fr_re = fmadd(qb, rb, fmadd(qa, ra, fr_re));
                     fr_im = fmadd(-qb, ra, fmadd(qa, rb, fr_im));
                     fqq = fmadd(qb, qb, fmadd(qa, qa, fqq));
@@ -333,10 +334,9 @@ __global__ __launch_bounds__(B4 ? 256 : 512, 2) void k_sap_rl(Geom g, SapGeom sg
         block_products<B4 ? 4 : 0>(sre, sim, sqq, red, lane, wid, nw);
         if (!(sqq > 0.0))
             break;  // zero residue on this block: uniform across the workgroup
-        const double inv = -2.0 / sqq;
         // with q = D_Lambda r = -acc / 2: alpha = (q, r) / ||q||^2 = -2 (acc, r) / ||acc||^2,
         // x += alpha r, r -= alpha q = r + (alpha / 2) acc
-        const c32 alpha{(float)(inv * sre), (float)(inv * sim)};
+        const c32 alpha{(float)(-2.0 * sre / sqq), (float)(-2.0 * sim / sqq)};
         const c32 half{0.5f * alpha.re, 0.5f * alpha.im};
 #pragma unroll
         for (int al = 0; al < 4; ++al)
@@ -521,8 +521,7 @@ __global__ __launch_bounds__(B4 ? 256 : 512, 2) void k_sap_cl(Geom g, SapGeom sg
                 site_clover(-2.0f, r, acc);
         }
         __syncthreads();
-        // the lane's products summed in FP32, the block sums in FP64
-        float fr_re = 0.0f, fr_im = 0.0f, fqq = 0.0f;
+        double sre = 0.0, sim = 0.0, sqq = 0.0;  // (squares of FP32 entries would leave FP32's range)
         if (active) {
 #pragma unroll
             for (int h = 0; h < 8; ++h) {
@@ -550,21 +549,20 @@ __global__ __launch_bounds__(B4 ? 256 : 512, 2) void k_sap_cl(Geom g, SapGeom sg
             for (int al = 0; al < 4; ++al)
 #pragma unroll
                 for (int a = 0; a < 3; ++a) {
-                    const float qa = acc.s[al].c[a].re, qb = acc.s[al].c[a].im;
+                    const double qa = acc.s[al].c[a].re, qb = acc.s[al].c[a].im;
                     const c32 r = lr[(3 * al + a) * Vsb + t];
-                    fr_re = fmadd(qb, r.im, fmadd(qa, r.re, fr_re));
-                    fr_im = fmadd(-qb, r.re, fmadd(qa, r.im, fr_im));
-                    fqq = fmadd(qb, qb, fmadd(qa, qa, fqq));
+                    const double ra = r.re, rb = r.im;
+                    sre = fmadd(qb, rb, fmadd(qa, ra, sre));
+                    sim = fmadd(-qb, ra, fmadd(qa, rb, sim));
+                    sqq = fmadd(qb, qb, fmadd(qa, qa, sqq));
                 }
         }
-        double sre = fr_re, sim = fr_im, sqq = fqq;
         block_products<B4 ? 4 : 0>(sre, sim, sqq, red, lane, wid, nw);
         if (!(sqq > 0.0))
             break;  // zero residue on this block: uniform across the workgroup
         // with q = D_Lambda r = -acc / 2: alpha = (q, r) / ||q||^2 = -2 (acc, r) / ||acc||^2,
         // x += alpha r, r -= alpha q = r + (alpha / 2) acc
-        const double inv = -2.0 / sqq;
-        const c32 alpha{(float)(inv * sre), (float)(inv * sim)};
+        const c32 alpha{(float)(-2.0 * sre / sqq), (float)(-2.0 * sim / sqq)};
         const c32 half{0.5f * alpha.re, 0.5f * alpha.im};
         if (active) {
 #pragma unroll
@@ -919,17 +917,18 @@ __global__ __launch_bounds__(512, 1) void k_sap_pair(Geom g, SapGeom sg, L U, co
 #pragma unroll
             for (int i = 0; i < 6; ++i)
                 q[i] = cpx<T>{0, 0};
-        // the lane's products summed in its precision, the block sums in FP64
-        T fr_re = 0, fr_im = 0, fqq = 0;
+        // the lane's products, then the block sums in FP64
+        using S = std::conditional_t<F64 || IMP, double, float>;
+        S fr_re = 0, fr_im = 0, fqq = 0;
 #pragma unroll
         for (int i = 0; i < 6; ++i) {
             const int al = i / 3, a = i % 3;
             const cpx<T> ao{pair_sum(acc.s[al].c[a].re, acc.s[al + 2].c[a].re),
                             pair_sum(acc.s[al].c[a].im, acc.s[al + 2].c[a].im)};
             q[i] = cpx<T>{q[i].re - T(0.5) * ao.re, q[i].im - T(0.5) * ao.im};
-            const T qa = q[i].re, qb = q[i].im;
+            const S qa = q[i].re, qb = q[i].im;
             const cpx<T> r = active ? r_of(i) : cpx<T>{0, 0};
-            const T ra = r.re, rb = r.im;
+            const S ra = r.re, rb = r.im;
             fr_re = fmadd(qb, rb, fmadd(qa, ra, fr_re));
             fr_im = fmadd(-qb, ra, fmadd(qa, rb, fr_im));
             fqq = fmadd(qb, qb, fmadd(qa, qa, fqq));
@@ -938,8 +937,7 @@ __global__ __launch_bounds__(512, 1) void k_sap_pair(Geom g, SapGeom sg, L U, co
         block_products<B4 ? 8 : 0>(sre, sim, sqq, red, lane, wid, nw);
         if (!(sqq > 0.0))
             break;  // zero residue on this block: uniform across the workgroup
-        const double inv = 1.0 / sqq;
-        const cpx<T> alpha{(T)(inv * sre), (T)(inv * sim)};
+        const cpx<T> alpha{(T)(sre / sqq), (T)(sim / sqq)};
         if (F64 ? active : true) {
 #pragma unroll
             for (int i = 0; i < 6; ++i) {
@@ -1187,8 +1185,7 @@ __global__ __launch_bounds__(512, 2) void k_sap_big(Geom g, SapGeom sg, Links64 
             break;  // zero residue on this block: uniform across the workgroup
         // with q = D_Lambda r = -acc / 2: alpha = (q, r) / ||q||^2 = -2 (acc, r) / ||acc||^2,
         // psi += alpha r, r -= alpha q = r + (alpha / 2) acc
-        const double inv = -2.0 / sqq;
-        const c64 alpha{inv * sre, inv * sim};
+        const c64 alpha{-2.0 * sre / sqq, -2.0 * sim / sqq};
         const c64 ha{0.5 * alpha.re, 0.5 * alpha.im};
         if (active) {
 #pragma unroll
@@ -1230,7 +1227,7 @@ void launch_pair(const Geom& g, const SapGeom& sg, L U, const cpx<T>* rho, const
         go(attr[1], &k_sap_pair<T, L, false, IMP>);
 }
 
-template <typename L, bool B4, bool IMP>
+template <typename L, bool B4, bool IMP, bool BIG>
 void launch_rl_kernel(const Geom& g, const SapGeom& sg, L U, const c32* rho, const double* rho_nrm2, c32* psi,
                       float m0, int nmr, int colour, int nrhs, int init, c64* out64, hipStream_t s, const c32* clov)
 {
@@ -1241,8 +1238,8 @@ void launch_rl_kernel(const Geom& g, const SapGeom& sg, L U, const c32* rho, con
         hipLaunchKernelGGL((k_sap_cl<L, B4>), grid, threads, (size_t)(24 + 2 * kLC) * sg.Vsb * sizeof(c32), s, g, sg,
                            U, rho, rho_nrm2, psi, 4.0f + m0, nmr, colour, nrhs, init, out64, Clover<float>{clov});
     } else {
-        set_max_lds_once(attr, reinterpret_cast<const void*>(&k_sap_rl<L, B4>), 160 * 1024 - 1024);
-        hipLaunchKernelGGL((k_sap_rl<L, B4>), grid, threads, (size_t)36 * sg.Vsb * sizeof(c32), s, g, sg, U, rho,
+        set_max_lds_once(attr, reinterpret_cast<const void*>(&k_sap_rl<L, B4, BIG>), 160 * 1024 - 1024);
+        hipLaunchKernelGGL((k_sap_rl<L, B4, BIG>), grid, threads, (size_t)36 * sg.Vsb * sizeof(c32), s, g, sg, U, rho,
                            rho_nrm2, psi, 4.0f + m0, nmr, colour, nrhs, init, out64);
     }
 }
@@ -1262,9 +1259,13 @@ void launch_rl(const Geom& g, const SapGeom& sg, L U, const c32* rho, const doub
     if (nrhs == 1 && !sg.one_rl && sg.Vsb <= 256)
         launch_pair<float, L, IMP>(g, sg, U, rho, rho_nrm2, psi, m0, nmr, colour, nrhs, init, out64, s, clov);
     else if (is_b4(sg))
-        launch_rl_kernel<L, true, IMP>(g, sg, U, rho, rho_nrm2, psi, m0, nmr, colour, nrhs, init, out64, s, clov);
+        launch_rl_kernel<L, true, IMP, false>(g, sg, U, rho, rho_nrm2, psi, m0, nmr, colour, nrhs, init, out64, s, clov);
+    else if (sg.Vsb <= 256)
+        launch_rl_kernel<L, false, IMP, false>(g, sg, U, rho, rho_nrm2, psi, m0, nmr, colour, nrhs, init, out64, s,
+                                               clov);
     else
-        launch_rl_kernel<L, false, IMP>(g, sg, U, rho, rho_nrm2, psi, m0, nmr, colour, nrhs, init, out64, s, clov);
+        launch_rl_kernel<L, false, IMP, true>(g, sg, U, rho, rho_nrm2, psi, m0, nmr, colour, nrhs, init, out64, s,
+                                              clov);
 }
 
 template <typename L>
