@@ -387,25 +387,23 @@ __device__ inline void clover_mul(const cpx<T> (&e)[18], const cpx<T> (&v)[6], c
         }
 }
 
-// o += f C(x) p for site s
-template <typename T>
-__device__ inline void clover_add(const Clover<T>& C, long s, const spinor<T>& p, spinor<T>& o, T f = T(1))
+// o += C(x) p for site s: C p summed by itself and added with one rounding (o is
+// the larger part)
+template <typename T> __device__ inline void clover_add(const Clover<T>& C, long s, const spinor<T>& p, spinor<T>& o)
 {
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
-        cpx<T> v[6], w[6];
+        cpx<T> e[18], v[6], w[6];
+        clover_load(C, s, h, e);
 #pragma unroll
         for (int i = 0; i < 6; ++i) {
-            const cpx<T> x = p.s[2 * h + i / 3].c[i % 3];
-            v[i] = f == T(1) ? x : f * x;
-            w[i] = o.s[2 * h + i / 3].c[i % 3];
+            v[i] = p.s[2 * h + i / 3].c[i % 3];
+            w[i] = cpx<T>{0, 0};
         }
-        cpx<T> e[18];
-        clover_load(C, s, h, e);
         clover_mul(e, v, w);
 #pragma unroll
         for (int i = 0; i < 6; ++i)
-            o.s[2 * h + i / 3].c[i % 3] = w[i];
+            o.s[2 * h + i / 3].c[i % 3] += w[i];
     }
 }
 
