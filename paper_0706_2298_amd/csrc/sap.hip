@@ -971,10 +971,10 @@ template <typename T, typename L>
 void launch(const Geom& g, const SapGeom& sg, L U, const cpx<T>* rho, const double* rho_nrm2, cpx<T>* psi, T m0,
             int nmr, int colour, int nrhs, int init, c64* out64, hipStream_t s, const cpx<T>* clov);
 
-// o += f C(x) p, or o = f (dg + C(x)) p with SET, the entries read nine at a time
-// and the chirality blocks one after the other (few live registers)
-template <bool SET, typename T>
-__device__ inline void clover_add_low(const Clover<T>& C, int s, T f, T dg, const spinor<T>& p, spinor<T>& o)
+// o = f (dg + C(x)) p, the entries read nine at a time and the chirality blocks
+// one after the other (few live registers)
+template <typename T>
+__device__ inline void clover_set_low(const Clover<T>& C, int s, T f, T dg, const spinor<T>& p, spinor<T>& o)
 {
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
@@ -982,7 +982,7 @@ __device__ inline void clover_add_low(const Clover<T>& C, int s, T f, T dg, cons
         auto v = [&](int i) { return f * p.s[2 * h + i / 3].c[i % 3]; };
 #pragma unroll
         for (int i = 0; i < 6; ++i)
-            w[i] = SET ? dg * v(i) : o.s[2 * h + i / 3].c[i % 3];
+            w[i] = dg * v(i);
 #pragma unroll
         for (int part = 0; part < 2; ++part) {
 #pragma unroll
@@ -1017,12 +1017,15 @@ __device__ inline void clover_add_low(const Clover<T>& C, int s, T f, T dg, cons
 // per CU. A site holds its four forward links only (two rows, 96 registers) and
 // works on both ends of each: U_mu(x) times the projected neighbour x + mu for
 // itself, and U_mu(x)^+ times its own projected residue for x + mu, which takes
-// it from LDS; so every link is read once per sweep. The residue is held in
-// registers and mirrored in LDS for the neighbours; the block solution is added
-// to psi step by step, each site's own values only. Bound by latency: one block
-// fills a CU's registers, and its eight wavefronts meet at ten barriers a step.
-// 8 x 4^3 blocks on 32 x 16^3: with the clover term 125 us per sweep where the
-// links re-read at every step took 171; three fields without it 150 (239).
+// it from LDS; so the MR steps read no link. (The residue before them reads the
+// eight links of a site, and the clover entries are read again in every step:
+// they fit neither registers nor LDS.) The residue lives in LDS alone, the block
+// solution in registers, and psi is read and written once. Bound by latency: one
+// block fills a CU's registers, and its eight wavefronts meet at ten barriers a
+// step.
+// 8 x 4^3 blocks on 32 x 16^3: with the clover term 102 us per sweep where the
+// links re-read at every step took 168; three fields without it 146 (238). With
+// the residue in registers too, and psi updated in every step, 125 and 150.
 template <bool IMP>
 __global__ __launch_bounds__(512, 2) void k_sap_big(Geom g, SapGeom sg, Links64 U, const c64* __restrict__ rho,
                                                     c64* __restrict__ psi, double diag, int nmr, int colour, int nrhs,
@@ -1073,8 +1076,8 @@ __global__ __launch_bounds__(512, 2) void k_sap_big(Geom g, SapGeom sg, Links64 
     const bool clv = IMP && C.c != nullptr;
 
     // residual with the full operator
-    spinor<double> r;
-    zero(r);
+    spinor<double> xs;
+    zero(xs);
     if (active) {
         spinor<double> acc, self;
         zero(acc);
@@ -1085,11 +1088,13 @@ __global__ __launch_bounds__(512, 2) void k_sap_big(Geom g, SapGeom sg, Links64 
             self = load_spinor(psi, g.V, s);
         spinor<double> d = finish(self, acc, diag);
         if (clv && init == 0)
-            clover_add_low<false>(C, (int)s, 1.0, 0.0, self, d);
+            clover_add(C, s, self, d);
         const spinor<double> b = load_spinor(rho, g.V, s);
 #pragma unroll
         for (int al = 0; al < 4; ++al)
-            r.s[al] = b.s[al] - d.s[al];
+#pragma unroll
+            for (int a = 0; a < 3; ++a)
+                lr[(3 * al + a) * sg.Vsb + t] = b.s[al].c[a] - d.s[al].c[a];
     }
     LinkRows<Links64> lk[4];
     if (active)
@@ -1097,8 +1102,7 @@ __global__ __launch_bounds__(512, 2) void k_sap_big(Geom g, SapGeom sg, Links64 
         for (int mu = 0; mu < 4; ++mu)
             lk[mu] = load_rows(U, mu, s);
 
-    int step = 0;
-    for (; step < nmr; ++step) {
+    for (int step = 0; step < nmr; ++step) {
         // (unknown to the compiler here: addresses are formed in the step, not kept over all of them)
         int Vsb = sg.Vsb, sc = (int)s;
         asm volatile("" : "+s"(Vsb), "+v"(sc));
@@ -1106,13 +1110,14 @@ __global__ __launch_bounds__(512, 2) void k_sap_big(Geom g, SapGeom sg, Links64 
         // hops, so the MR coefficient follows from it without forming D_Lambda r
         spinor<double> acc;
         if (active) {
+            spinor<double> r;
 #pragma unroll
             for (int al = 0; al < 4; ++al)
 #pragma unroll
                 for (int a = 0; a < 3; ++a)
-                    lr[(3 * al + a) * Vsb + t] = r.s[al].c[a];
+                    r.s[al].c[a] = lr[(3 * al + a) * Vsb + t];
             if (clv) {
-                clover_add_low<true>(C, sc, -2.0, diag, r, acc);
+                clover_set_low(C, sc, -2.0, diag, r, acc);
             } else {
 #pragma unroll
                 for (int al = 0; al < 4; ++al)
@@ -1135,10 +1140,10 @@ __global__ __launch_bounds__(512, 2) void k_sap_big(Geom g, SapGeom sg, Links64 
 #pragma unroll
                 for (int K = 0; K < 2; ++K) {
                     // (1 + g_mu) r(x) and (1 - g_mu) r(x + mu), their colour vector K
-                    const c64* pn = lr + t + lst;
-                    const cvec3<double> v =
-                        mul_dag(u, K == 0 ? pair_project<MU, 0, double>([&](int c) { return r.s[c / 3].c[c % 3]; }, -1.0)
-                                          : pair_project<MU, 1, double>([&](int c) { return r.s[c / 3].c[c % 3]; }, -1.0));
+                    const c64 *po = lr + t, *pn = po + lst;
+                    const auto own = [&](int c) { return po[c * Vsb]; };
+                    const cvec3<double> v = mul_dag(u, K == 0 ? pair_project<MU, 0, double>(own, -1.0)
+                                                              : pair_project<MU, 1, double>(own, -1.0));
 #pragma unroll
                     for (int a = 0; a < 3; ++a)
                         ex[(3 * K + a) * Vsb + t] = v.c[a];
@@ -1174,7 +1179,8 @@ __global__ __launch_bounds__(512, 2) void k_sap_big(Geom g, SapGeom sg, Links64 
 #pragma unroll
                 for (int a = 0; a < 3; ++a) {
                     const double qa = acc.s[al].c[a].re, qb = acc.s[al].c[a].im;
-                    const double ra = r.s[al].c[a].re, rb = r.s[al].c[a].im;
+                    const c64 r = lr[(3 * al + a) * Vsb + t];
+                    const double ra = r.re, rb = r.im;
                     sre = fmadd(qb, rb, fmadd(qa, ra, sre));
                     sim = fmadd(-qb, ra, fmadd(qa, rb, sim));
                     sqq = fmadd(qb, qb, fmadd(qa, qa, sqq));
@@ -1184,7 +1190,7 @@ __global__ __launch_bounds__(512, 2) void k_sap_big(Geom g, SapGeom sg, Links64 
         if (!(sqq > 0.0))
             break;  // zero residue on this block: uniform across the workgroup
         // with q = D_Lambda r = -acc / 2: alpha = (q, r) / ||q||^2 = -2 (acc, r) / ||acc||^2,
-        // psi += alpha r, r -= alpha q = r + (alpha / 2) acc
+        // x += alpha r, r -= alpha q = r + (alpha / 2) acc
         const c64 alpha{-2.0 * sre / sqq, -2.0 * sim / sqq};
         const c64 ha{0.5 * alpha.re, 0.5 * alpha.im};
         if (active) {
@@ -1192,16 +1198,25 @@ __global__ __launch_bounds__(512, 2) void k_sap_big(Geom g, SapGeom sg, Links64 
             for (int al = 0; al < 4; ++al)
 #pragma unroll
                 for (int a = 0; a < 3; ++a) {
-                    const uint32_t at = toff<c64>(sc, 3 * al + a, 12);
-                    const c64 x = init == 0 || step > 0 ? ld(psi, at) : c64{0.0, 0.0};
-                    st(psi, at, cfma(alpha, r.s[al].c[a], x));
-                    r.s[al].c[a] = cfma(ha, acc.s[al].c[a], r.s[al].c[a]);
+                    const int e = (3 * al + a) * Vsb + t;
+                    const c64 r = lr[e];
+                    xs.s[al].c[a] = cfma(alpha, r, xs.s[al].c[a]);
+                    lr[e] = cfma(ha, acc.s[al].c[a], r);
                 }
         }
     }
-    if (active && init > 0 && step == 0) {  // psi was not written before
-        zero(r);
-        store_spinor(psi, g.V, s, r);
+
+    if (active) {
+#pragma unroll
+        for (int al = 0; al < 4; ++al)
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+                const uint32_t at = toff<c64>(s, 3 * al + a, 12);
+                c64 p = xs.s[al].c[a];
+                if (init == 0)
+                    p += ld(psi, at);
+                st(psi, at, p);
+            }
     }
 }
 
