@@ -283,16 +283,22 @@ __global__ __launch_bounds__(BIG ? 512 : 256, 2) void k_sap_rl(Geom g, SapGeom s
                 for (int a = 0; a < 3; ++a)
                     lr[(3 * al + a) * Vsb + t] = r.s[al].c[a];
         }
-        // acc = -2 D_Lambda r: it starts at -2 diag r and collects the inside
-        // hops, so the MR coefficient follows from it without forming D_Lambda r
+        // acc = -2 D_Lambda r: it starts at -2 diag r (BIG: ends with it, the hops are
+        // summed by themselves) and collects the inside hops, so the MR coefficient
+        // follows from it without forming D_Lambda r
         spinor<float> acc;
-        if (active) {
+        zero(acc);
+        auto add_diag = [&] {
 #pragma unroll
             for (int al = 0; al < 4; ++al)
 #pragma unroll
-                for (int a = 0; a < 3; ++a)
-                    acc.s[al].c[a] = cpx<float>{-2.0f * diag * r.s[al].c[a].re, -2.0f * diag * r.s[al].c[a].im};
-        }
+                for (int a = 0; a < 3; ++a) {
+                    acc.s[al].c[a].re = fmadd(-2.0f * diag, r.s[al].c[a].re, acc.s[al].c[a].re);
+                    acc.s[al].c[a].im = fmadd(-2.0f * diag, r.s[al].c[a].im, acc.s[al].c[a].im);
+                }
+        };
+        if (active && !BIG)
+            add_diag();
         __syncthreads();
         // the lane's products, then the block sums in FP64
         using S = std::conditional_t<BIG, double, float>;
@@ -319,6 +325,8 @@ __global__ __launch_bounds__(BIG ? 512 : 256, 2) void k_sap_rl(Geom g, SapGeom s
                 if (h & 1)
                     asm volatile("" ::: "memory");
             }
+            if (BIG)
+                add_diag();
 #pragma unroll
             for (int al = 0; al < 4; ++al)
 #pragma unroll
@@ -367,7 +375,7 @@ __global__ __launch_bounds__(BIG ? 512 : 256, 2) void k_sap_rl(Geom g, SapGeom s
 // 48 x 24^3, 95 without the term). So the residue lives in LDS alone, the block
 // solution too, the third link rows are rebuilt for every use, and of every
 // chirality block's entries kLC are in LDS, the others in registers: one read
-// of everything per sweep, two blocks of 256 sites per CU: 139 us.
+// of everything per sweep, two blocks of 256 sites per CU: 144 us.
 constexpr int kLC = 5;  // LDS entries of a chirality block (of 18)
 template <typename L, bool B4>
 __global__ __launch_bounds__(B4 ? 256 : 512, 2) void k_sap_cl(Geom g, SapGeom sg, L U, const c32* __restrict__ rho,
@@ -430,8 +438,9 @@ __global__ __launch_bounds__(B4 ? 256 : 512, 2) void k_sap_cl(Geom g, SapGeom sg
     }
     const bool clv = C.c != nullptr;
     c32 cl[2][18 - kLC];
-    // o += f C p at this site
-    auto site_clover = [&](float f, const spinor<float>& p, spinor<float>& o) {
+    // o += f C p at this site for the p with component (3 * spin + colour) p(c); C p
+    // is summed by itself (o is the larger part)
+    auto site_clover = [&](float f, const auto& p, spinor<float>& o) {
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
             c32 e[18], v[6], w[6];
@@ -440,13 +449,14 @@ __global__ __launch_bounds__(B4 ? 256 : 512, 2) void k_sap_cl(Geom g, SapGeom sg
                 e[q] = q < kLC ? lc[(kLC * h + q) * Vsb + t] : cl[h][q < kLC ? 0 : q - kLC];
 #pragma unroll
             for (int i = 0; i < 6; ++i) {
-                v[i] = f * p.s[2 * h + i / 3].c[i % 3];
-                w[i] = o.s[2 * h + i / 3].c[i % 3];
+                v[i] = f * p(6 * h + i);
+                w[i] = c32{0.0f, 0.0f};
             }
             clover_mul(e, v, w);
 #pragma unroll
             for (int i = 0; i < 6; ++i)
-                o.s[2 * h + i / 3].c[i % 3] = w[i];
+                o.s[2 * h + i / 3].c[i % 3] += w[i];
+            asm volatile("" ::: "memory");
         }
     };
 
@@ -491,7 +501,7 @@ __global__ __launch_bounds__(B4 ? 256 : 512, 2) void k_sap_cl(Geom g, SapGeom sg
             self = load_spinor(psi, g.V, s);
         spinor<float> d = finish(self, acc, diag);
         if (clv && init == 0)
-            site_clover(1.0f, self, d);
+            site_clover(1.0f, [&](int c) { return self.s[c / 3].c[c % 3]; }, d);
         spinor<float> b = load_spinor(rho, g.V, s);
         if (rho_nrm2)
             scale_spinor(b, rs);
@@ -505,21 +515,10 @@ __global__ __launch_bounds__(B4 ? 256 : 512, 2) void k_sap_cl(Geom g, SapGeom sg
     }
 
     for (int stp = 0; stp < nmr; ++stp) {
-        // acc = -2 D_Lambda r: it starts at -2 (diag + C) r and collects the inside
-        // hops, so the MR coefficient follows from it without forming D_Lambda r
+        // acc = -2 D_Lambda r: the inside hops, then -2 (diag + C) r; the MR
+        // coefficient follows from it without forming D_Lambda r
         spinor<float> acc;
-        if (active) {
-            spinor<float> r;
-#pragma unroll
-            for (int al = 0; al < 4; ++al)
-#pragma unroll
-                for (int a = 0; a < 3; ++a) {
-                    r.s[al].c[a] = lr[(3 * al + a) * Vsb + t];
-                    acc.s[al].c[a] = -2.0f * diag * r.s[al].c[a];
-                }
-            if (clv)
-                site_clover(-2.0f, r, acc);
-        }
+        zero(acc);
         __syncthreads();
         double sre = 0.0, sim = 0.0, sqq = 0.0;  // (squares of FP32 entries would leave FP32's range)
         if (active) {
@@ -545,6 +544,17 @@ __global__ __launch_bounds__(B4 ? 256 : 512, 2) void k_sap_cl(Geom g, SapGeom sg
                 }
                 asm volatile("" ::: "memory");
             }
+            const c32* own = lr + t;
+#pragma unroll
+            for (int al = 0; al < 4; ++al)
+#pragma unroll
+                for (int a = 0; a < 3; ++a) {
+                    const c32 r = own[(3 * al + a) * Vsb];
+                    acc.s[al].c[a].re = fmadd(-2.0f * diag, r.re, acc.s[al].c[a].re);
+                    acc.s[al].c[a].im = fmadd(-2.0f * diag, r.im, acc.s[al].c[a].im);
+                }
+            if (clv)
+                site_clover(-2.0f, [&](int c) { return own[c * Vsb]; }, acc);
 #pragma unroll
             for (int al = 0; al < 4; ++al)
 #pragma unroll
