@@ -890,31 +890,34 @@ __global__ __launch_bounds__(256) void k_sum_chunks(const float* __restrict__ pa
     dW[e] = s;
 }
 
-// db[co] = sum_y g[co][y], one workgroup per channel; sixteen loads in flight
-// per thread (V is a multiple of 64), summed in pairs in a fixed order
+// db[co] = sum_y g[co][y] in FP64, rounded once, one workgroup per channel;
+// sixteen loads in flight per thread (V is a multiple of 64), summed in pairs in
+// a fixed order
 __global__ __launch_bounds__(1024) void k_bias_grad(const float* __restrict__ g, long V, float* __restrict__ db)
 {
-    __shared__ float sh[16];
+    __shared__ double sh[16];
     const float* gc = g + (long)blockIdx.x * V;
-    float a[16];
+    double a[16];
 #pragma unroll
     for (int k = 0; k < 16; ++k)
-        a[k] = 0.f;
+        a[k] = 0.0;
     for (long y = threadIdx.x; y < V; y += 16 * 1024) {
+        float v[16];
 #pragma unroll
         for (int k = 0; k < 16; ++k)
-            if (y + 1024 * k < V)
-                a[k] += gc[y + 1024 * k];
+            v[k] = y + 1024 * k < V ? gc[y + 1024 * k] : 0.f;
+#pragma unroll
+        for (int k = 0; k < 16; ++k)
+            a[k] += (double)v[k];
     }
 #pragma unroll
     for (int h = 8; h > 0; h >>= 1)
 #pragma unroll
         for (int k = 0; k < h; ++k)
             a[k] += a[k + h];
-    float s = a[0];
-    s = block_sum(s, sh);
+    const double s = block_sum(a[0], sh);
     if (threadIdx.x == 0)
-        db[blockIdx.x] = s;
+        db[blockIdx.x] = (float)s;
 }
 
 // canonical site index of native site s
