@@ -16,7 +16,6 @@ namespace dfl {
 
 namespace {
 
-constexpr int kCO = 16;        // output channels per workgroup of the convolution
 constexpr int kWT = 64;        // output channels per workgroup of the weight gradient
 constexpr int kWS = 64;        // sites per LDS tile of the weight gradient
 constexpr int kMaxCin = 96;
@@ -25,6 +24,8 @@ struct Lat {
     int L[4];
     long str[4];  // canonical strides (x3 fastest)
     long V;
+    int W3;       // x3 extent of a staged row: L[3], or that of a segment (see Tile)
+    int nseg;     // segments of a row, 0: tiles are runs of whole rows' sites
 };
 
 // delta[mu][o+1]: index shift of the neighbour x + o mu_hat of site i
@@ -60,80 +61,6 @@ __device__ inline float silu_grad_f(float z)
     return s * (1.0f + z * (1.0f - s));
 }
 
-// The vector kernel, for lattices whose rows along x3 are too long for the
-// staged tiles of the matrix-core kernels (conv_lds_bytes):
-// out[oc][i] = bias[oc] + sum_t sum_ic Wt(t, ic, oc) in[ic][i + s*o_t]
-//   forward (TRANS = false, s = +1): Wt(t, ic, oc) = W[t][ic][oc], nic = Cin
-//   input gradient (TRANS = true, s = -1): Wt(t, ic, oc) = W[t][oc][ic], nic = Cout of W
-// Epilogue: forward stores z and optionally a = silu(z); the input gradient
-// is optionally multiplied by silu'(zprev[oc][i]).
-template <bool TRANS>
-__global__ __launch_bounds__(256) void k_conv(Lat lt, const float* __restrict__ in, int nic,
-                                              const float* __restrict__ W, int w_cin, int w_cout,
-                                              const float* __restrict__ bias, int noc, float* __restrict__ out,
-                                              float* __restrict__ act, const float* __restrict__ zprev)
-{
-    __shared__ float4 ws[kMaxCin * kCO / 4 > 576 * kCO / 4 ? kMaxCin * kCO / 4 : 576 * kCO / 4];
-    const long V = lt.V;
-    const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-    const int oc0 = blockIdx.y * kCO;
-    long dl[4][3];
-    if (i < V)
-        tap_shifts(lt, i, TRANS ? -1 : 1, dl);
-    float acc[kCO];
-#pragma unroll
-    for (int j = 0; j < kCO; ++j)
-        acc[j] = (bias && oc0 + j < noc) ? bias[oc0 + j] : 0.f;
-    float* wsf = reinterpret_cast<float*>(ws);
-    for (int t = 0; t < 81; ++t) {
-        __syncthreads();
-        for (int e = threadIdx.x; e < nic * kCO; e += blockDim.x) {
-            int ic, j;
-            if (TRANS) {
-                ic = e % nic;
-                j = e / nic;
-            } else {
-                ic = e / kCO;
-                j = e % kCO;
-            }
-            float w = 0.f;
-            if (oc0 + j < noc)
-                w = TRANS ? W[((long)t * w_cin + oc0 + j) * w_cout + ic] : W[((long)t * w_cin + ic) * w_cout + oc0 + j];
-            wsf[ic * kCO + j] = w;
-        }
-        __syncthreads();
-        if (i < V) {
-            const int o0 = t / 27, o1 = (t / 9) % 3, o2 = (t / 3) % 3, o3 = t % 3;
-            const long nb = i + dl[0][o0] + dl[1][o1] + dl[2][o2] + dl[3][o3];
-            const float* src = in + nb;
-            for (int ic = 0; ic < nic; ++ic) {
-                const float x = src[(long)ic * V];
-#pragma unroll
-                for (int q = 0; q < kCO / 4; ++q) {
-                    const float4 w = ws[ic * (kCO / 4) + q];
-                    acc[4 * q] += x * w.x;
-                    acc[4 * q + 1] += x * w.y;
-                    acc[4 * q + 2] += x * w.z;
-                    acc[4 * q + 3] += x * w.w;
-                }
-            }
-        }
-    }
-    if (i >= V)
-        return;
-#pragma unroll
-    for (int j = 0; j < kCO; ++j) {
-        if (oc0 + j >= noc)
-            continue;
-        float v = acc[j];
-        if (TRANS && zprev)
-            v *= silu_grad_f(zprev[(long)(oc0 + j) * V + i]);
-        out[(long)(oc0 + j) * V + i] = v;
-        if (!TRANS && act)
-            act[(long)(oc0 + j) * V + i] = silu_f(v);
-    }
-}
-
 // ------------------------------------------------------- staged site tiles
 //
 // The matrix-core convolutions work on tiles of T consecutive canonical sites.
@@ -142,10 +69,14 @@ __global__ __launch_bounds__(256) void k_conv(Lat lt, const float* __restrict__ 
 // of one (x0, x1) plane are staged in LDS ("slots" of L3 + 2 positions); all
 // nine taps (o2, o3) then read the same staged values at a constant shift of
 // o2 (L3 + 2) + o3 positions. Any lattice works: a tile may start inside a
-// row and cross planes.
+// row and cross planes. Where long rows make that halo too large (more than
+// kCPos positions), a tile is a segment of one row instead, the shortest of
+// equal parts of at most T sites, staged with its neighbours only (slots of
+// W3 + 2 positions).
 struct Tile {
     long site0;   // first site
-    int n;        // sites (T, fewer at the end of the lattice)
+    int n;        // sites (T, fewer at the end of the lattice or in segments)
+    int x3_0;     // x3 of the slots' first site
     int x2_0;     // x2 of the first row
     int plane0;   // its plane x0 L1 + x1
     int slots;    // staged rows
@@ -153,8 +84,16 @@ struct Tile {
 __device__ inline Tile make_tile(const Lat& lt, long tile, int T)
 {
     Tile t;
-    t.site0 = tile * T;
-    t.n = (int)(lt.V - t.site0 < T ? lt.V - t.site0 : T);
+    t.x3_0 = 0;
+    if (lt.nseg) {
+        const long row = tile / lt.nseg;
+        t.x3_0 = (int)(tile - row * lt.nseg) * lt.W3;
+        t.site0 = row * lt.L[3] + t.x3_0;
+        t.n = lt.L[3] - t.x3_0 < lt.W3 ? lt.L[3] - t.x3_0 : lt.W3;
+    } else {
+        t.site0 = tile * T;
+        t.n = (int)(lt.V - t.site0 < T ? lt.V - t.site0 : T);
+    }
     const long r0 = t.site0 / lt.L[3], r1 = (t.site0 + t.n - 1) / lt.L[3];
     t.plane0 = (int)(r0 / lt.L[2]);
     t.x2_0 = (int)(r0 - (long)t.plane0 * lt.L[2]);
@@ -168,10 +107,10 @@ __device__ inline int tile_pos(const Lat& lt, const Tile& t, int i)
 {
     const long s = t.site0 + i;
     const long r = s / lt.L[3];
-    const int x3 = (int)(s - r * lt.L[3]);
+    const int x3 = (int)(s - r * lt.L[3]) - t.x3_0;
     const int pl = (int)(r / lt.L[2]);
     const int x2 = (int)(r - (long)pl * lt.L[2]);
-    return ((pl - t.plane0) * (lt.L[2] + 2) + x2 + 1 - t.x2_0) * (lt.L[3] + 2) + x3 + 1;
+    return ((pl - t.plane0) * (lt.L[2] + 2) + x2 + 1 - t.x2_0) * (lt.W3 + 2) + x3 + 1;
 }
 // a staged position's source: x0, x1 of its plane and the index in the plane
 struct Src {
@@ -179,9 +118,9 @@ struct Src {
 };
 __device__ inline Src pos_source(const Lat& lt, const Tile& t, int p)
 {
-    const int w3 = lt.L[3] + 2, w2 = lt.L[2] + 2;
+    const int w3 = lt.W3 + 2, w2 = lt.L[2] + 2;
     const int slot = p / w3;
-    int x3 = p - slot * w3 - 1;
+    int x3 = t.x3_0 + p - slot * w3 - 1;
     x3 = x3 < 0 ? x3 + lt.L[3] : (x3 >= lt.L[3] ? x3 - lt.L[3] : x3);
     const int u = slot + t.x2_0;
     const int seg = u / w2;
@@ -206,8 +145,13 @@ __device__ inline long src_site(const Lat& lt, const Src& r, int d0, int d1)
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-// k_conv's map on the matrix cores (v_mfma_f32_32x32x2f32, FP32 products and
-// sums), one GEMM per tap: out[oc][x] += sum_ic Wt(t, ic, oc) in[ic][x + s o_t].
+// out[oc][i] = bias[oc] + sum_t sum_ic Wt(t, ic, oc) in[ic][i + s o_t]
+//   forward (TRANS = false, s = +1): Wt(t, ic, oc) = W[t][ic][oc], nic = Cin
+//   input gradient (TRANS = true, s = -1): Wt(t, ic, oc) = W[t][oc][ic], nic = Cout of W
+// Epilogue: forward stores z and optionally a = silu(z); the input gradient
+// is optionally multiplied by silu'(zprev[oc][i]).
+// On the matrix cores (v_mfma_f32_32x32x2f32, FP32 products and sums), one GEMM
+// per tap: out[oc][x] += sum_ic Wt(t, ic, oc) in[ic][x + s o_t].
 // Workgroup: a tile of 128 sites and 32 OT output channels, wavefront w the
 // sites 32 w .. 32 w + 31 of all of them. For each (o0, o1) and each chunk of
 // 32 input channels the tile is staged as [position][channel], and the weights
@@ -226,6 +170,7 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 // ms), 576 -> 32 (input gradient) 2.06 ms = 95 TFLOP/s (8.97 ms), 32 -> 32
 // 0.12 ms (0.31 ms); a large FP32 matrix product reaches 154 TFLOP/s.
 constexpr int kCT = 128;  // sites per tile
+constexpr int kCPos = 512;  // most staged positions (two per thread)
 constexpr int kCK = 32;   // input channels per LDS chunk
 constexpr int kCP = 36;   // LDS row stride in floats
 template <bool TRANS, int OT>
@@ -244,12 +189,12 @@ __global__ __launch_bounds__(256, 2) void k_conv_mfma(Lat lt, int ntiles, const 
         return;
     const int sgn = TRANS ? -1 : 1;
     const Tile tl = make_tile(lt, tile_id, kCT);
-    const int w3 = lt.L[3] + 2;
+    const int w3 = lt.W3 + 2;
     const int np = tl.slots * w3;
     const int oc0 = blockIdx.y * OCT;
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int col = lane & 31, kh = lane >> 5;
-    // this thread's staged positions (npos <= 512)
+    // this thread's staged positions (npos <= kCPos)
     Src src[2];
 #pragma unroll
     for (int k = 0; k < 2; ++k)
@@ -553,7 +498,7 @@ __global__ __launch_bounds__(256, 2) void k_conv_bf16_tile(Lat lt, int ntiles, c
     if (tile_id >= ntiles)
         return;
     const Tile tl = make_tile(lt, tile_id, T);
-    const int w3 = lt.L[3] + 2;
+    const int w3 = lt.W3 + 2;
     const int np = tl.slots * w3;
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int col = lane & 31, kh = lane >> 5;
@@ -733,7 +678,7 @@ __global__ __launch_bounds__(384, 4) void k_conv_wgrad_mfma(Lat lt, const float*
     const int l01 = blockIdx.x % 9, ci0 = blockIdx.x / 9 % nct * 32, co0 = blockIdx.x / 9 / nct * CO;
     const int o0 = l01 / 3 - 1, o1 = l01 % 3 - 1;
     const int o2 = w % 3 - 1, half = w / 3;
-    const int w3 = lt.L[3] + 2;
+    const int w3 = lt.W3 + 2;
     const int nc = cin - ci0 < 32 ? cin - ci0 : 32;
     const int ntiles = (int)((lt.V + kCT - 1) / kCT);
     const int tile1 = min(ntiles, (int)(blockIdx.y + 1) * tiles);
@@ -816,7 +761,8 @@ __global__ __launch_bounds__(384, 4) void k_conv_wgrad_mfma(Lat lt, const float*
     }
 }
 
-// The same with vector instructions, for the lattices of k_conv, partial over a
+// The same with vector instructions, where the rows are too long for tiles of
+// whole rows, partial over a
 // chunk of sites:
 // part[chunk][t][ci][co] = sum_{y in chunk} in[ci][y + o_t] g[co][y].
 // Workgroup (t, co tile of kWT, site chunk); thread (ci group, co), the
@@ -1220,6 +1166,8 @@ Lat make_lat(const Geom& g)
     for (int mu = 2; mu >= 0; --mu)
         lt.str[mu] = lt.str[mu + 1] * lt.L[mu + 1];
     lt.V = g.V;
+    lt.W3 = lt.L[3];
+    lt.nseg = 0;
     return lt;
 }
 
@@ -1243,17 +1191,12 @@ int conv_tile_positions(const Geom& g, int T)
     return (rows + 2 * planes) * (L3 + 2);
 }
 
-// LDS of the FP32 tile kernels, in bytes; 0 if the lattice's rows are too long
-// for them (more than 512 staged positions): the vector kernels serve those.
-size_t conv_lds_bytes(const Geom& g, int ot)
-{
-    const int np = conv_tile_positions(g, kCT);
-    return np > 512 ? 0 : sizeof(float) * ((size_t)np * kCP + (size_t)3 * 32 * ot * kCP);
-}
+// LDS of the FP32 weight-gradient tiles, in bytes; 0 if the lattice's rows are
+// too long for them (more than kCPos staged positions): the vector kernel serves those.
 size_t wgrad_lds_bytes(const Geom& g, bool pair)
 {
     const int np = conv_tile_positions(g, kCT);
-    return np > 512 ? 0 : sizeof(float) * ((size_t)np * kCP + (size_t)kCT * ((pair ? 64 : 32) + 4) + kCT);
+    return np > kCPos ? 0 : sizeof(float) * ((size_t)np * kCP + (size_t)kCT * ((pair ? 64 : 32) + 4) + kCT);
 }
 
 // Two workgroups of the matrix-core weight gradient fit a CU, so the ranges of
@@ -1332,25 +1275,33 @@ template <bool TRANS>
 void launch_conv(const Geom& g, const float* in, int nic, const float* W, int w_cin, int w_cout, const float* bias,
                  int noc, float* out, float* act, const float* zprev, hipStream_t s)
 {
-    const Lat lt = make_lat(g);
+    Lat lt = make_lat(g);
+    int np = conv_tile_positions(g, kCT);
+    long ntiles = (g.V + kCT - 1) / kCT;
+    if (np > kCPos) {
+        // Tiles of whole rows' sites stage up to three rows and their halo; from
+        // about L3 = 72 on they pass kCPos, and a tile becomes a segment of one
+        // row. MI355X, forward on 8^3 x 160, 32 -> 32 channels 256 us and 32 -> 288
+        // 2.00 ms, with vector instructions 489 us and 3.17 ms.
+        lt.nseg = (lt.L[3] + kCT - 1) / kCT;
+        lt.W3 = (lt.L[3] + lt.nseg - 1) / lt.nseg;
+        lt.nseg = (lt.L[3] + lt.W3 - 1) / lt.W3;  // none of them empty
+        np = 3 * (lt.W3 + 2);
+        ntiles = g.V / lt.L[3] * lt.nseg;
+    }
     const int ot = noc <= 32 ? 1 : 2;
-    const size_t lds = conv_lds_bytes(g, ot);
-    const int np = conv_tile_positions(g, kCT);
-    const int ntiles = (int)((g.V + kCT - 1) / kCT);
+    const size_t lds = sizeof(float) * ((size_t)np * kCP + (size_t)3 * 32 * ot * kCP);
     const dim3 grid((unsigned)pad_grid(ntiles), (noc + 32 * ot - 1) / (32 * ot));
     static std::once_flag attr[2];  // per instantiation
-    if (lds && ot == 1) {
-        set_max_lds_once(attr[0], reinterpret_cast<const void*>(&k_conv_mfma<TRANS, 1>), 128 * 1024);
-        hipLaunchKernelGGL((k_conv_mfma<TRANS, 1>), grid, dim3(256), lds, s, lt, ntiles, in, nic, W, w_cin, w_cout,
-                           bias, noc, np, out, act, zprev);
-    } else if (lds) {
-        set_max_lds_once(attr[1], reinterpret_cast<const void*>(&k_conv_mfma<TRANS, 2>), 128 * 1024);
-        hipLaunchKernelGGL((k_conv_mfma<TRANS, 2>), grid, dim3(256), lds, s, lt, ntiles, in, nic, W, w_cin, w_cout,
-                           bias, noc, np, out, act, zprev);
-    } else {
-        hipLaunchKernelGGL(k_conv<TRANS>, dim3(site_blocks(g.V), (noc + kCO - 1) / kCO), dim3(256), 0, s, lt, in, nic,
-                           W, w_cin, w_cout, bias, noc, out, act, zprev);
-    }
+    auto launch = [&](std::once_flag& f, auto* kernel) {
+        set_max_lds_once(f, reinterpret_cast<const void*>(kernel), 128 * 1024);
+        hipLaunchKernelGGL(kernel, grid, dim3(256), lds, s, lt, (int)ntiles, in, nic, W, w_cin, w_cout, bias, noc, np,
+                           out, act, zprev);
+    };
+    if (ot == 1)
+        launch(attr[0], &k_conv_mfma<TRANS, 1>);
+    else
+        launch(attr[1], &k_conv_mfma<TRANS, 2>);
 }
 
 }  // namespace
