@@ -53,9 +53,10 @@ int conv4d_forward(dfl_ctx *ctx, const float *in_dev, int cin, const float *W_de
  * about 2^-7 sum_o sum_ci |W| |in| (two roundings of 2^-8 relative each).
  * For inference (the start fields of section 5.3); training uses the FP32
  * map. Needs L3 % 32 == 0 and L2 % 4 == 0 (DFL_EINVAL otherwise); the
- * context keeps BF16 copies of the weights (at most 81 x 96 x 576 entries) and
- * of the input (at most 96 V entries), grown on first use (synchronises then). Channel limits and overlap rules
- * as conv4d_forward. */
+ * context keeps BF16 copies of the weights (at most 81 x 96 x 576 entries,
+ * grown on first use, synchronises then) and of the input (96 V entries, made
+ * on first use; without room for it the call is slower). Channel limits and
+ * overlap rules as conv4d_forward. */
 int conv4d_forward_bf16(dfl_ctx *ctx, const float *in_dev, int cin, const float *W_dev, const float *b_dev,
                         int cout, float *z_dev, float *a_dev);
 

@@ -1010,17 +1010,27 @@ int max_multi_fields(const dfl_ctx* c)
     return c->p.sap_prec == DFL_F64 ? c->p.Ns : std::max(c->p.Ns, c->p.nrhs_max);
 }
 
-template <typename T> T* grow(dfl_ctx* c, T* p, size_t& have, size_t need)
+template <typename T> void grow(dfl_ctx* c, T*& p, size_t& have, size_t need)
 {
     if (need <= have)
-        return p;
+        return;
     sync(c);
     if (p)
         HIPCHECK(hipFree(p));
+    p = nullptr;
     have = 0;
-    T* q = alloc_dev<T>(c, need);
+    p = alloc_dev<T>(c, need);
     have = need;
-    return q;
+}
+
+// whether the caller is capturing the context's stream, where nothing can be allocated or waited for
+bool stream_captured(const dfl_ctx* c)
+{
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(c->stream, &st) == hipSuccess)
+        return st != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();
+    return true;
 }
 
 // Block Gram-Schmidt (eq. (4.2)) of the Ns fields at src into Phi and the
@@ -1050,7 +1060,7 @@ void build_subspace(dfl_ctx* c, const c64* src, double mA)
     // the transposed order, where those faces are whole tiles or long runs.
     const bool tl = all || little_columns_transposable(Ns, chunk);
     if (tl)
-        c->PhiT = grow<c64>(c, c->PhiT, c->PhiT_n, (size_t)F * Ns);
+        grow(c, c->PhiT, c->PhiT_n, (size_t)F * Ns);
     // block Gram-Schmidt (eq. (4.2)); the 256-site block kernel also writes the
     // transposed copy and the FP32 copy of the basis
     const bool copies = launch_block_gs64(c->g, c->Phi, Ns, 1e-10, c->dflag, c->gsR, c->stream,
@@ -1918,14 +1928,18 @@ int conv4d_forward_bf16(dfl_ctx* c, const float* in, int cin, const float* W, co
         fail(DFL_EINVAL, "outputs must not overlap the input");
     if (!conv_bf16_fits(c->g))
         fail(DFL_EINVAL, "the BF16 convolution needs L3 % 32 == 0 and L2 % 4 == 0");
-    c->net_wbf = grow<uint16_t>(c, c->net_wbf, c->net_wbf_n, conv_bf16_weight_elems(cin, cout));
-    try {
-        c->net_xbf = grow<uint16_t>(c, c->net_xbf, c->net_xbf_n, conv_bf16_input_elems(c->g, cin, cout));
-    } catch (const dfl::Error& e) {
-        if (e.code != DFL_ENOMEM)
-            throw;
-        (void)hipGetLastError();  // no room for the rounded input: the kernel that rounds as it reads
-        c->net_xbf = nullptr;
+    grow(c, c->net_wbf, c->net_wbf_n, conv_bf16_weight_elems(cin, cout));
+    // The rounded input has room for the most channels at once, so that its address stays (calls may have been
+    // captured); without it (no room, tried once, or in a capture before it exists) the kernel that rounds as it reads.
+    if (!c->net_xbf && !c->net_no_xbf && conv_bf16_input_elems(c->g) && !stream_captured(c)) {
+        try {
+            c->net_xbf = alloc_dev<uint16_t>(c, conv_bf16_input_elems(c->g));
+        } catch (const dfl::Error& e) {
+            if (e.code != DFL_ENOMEM)
+                throw;
+            (void)hipGetLastError();
+            c->net_no_xbf = true;
+        }
     }
     launch_conv_forward_bf16(c->g, in, cin, W, b, cout, z, a, c->net_wbf, c->net_xbf, c->stream);
     HIPCHECK(hipGetLastError());
@@ -1948,7 +1962,8 @@ int conv4d_backward(dfl_ctx* c, const float* in, int cin, const float* W, int co
         fail(DFL_EINVAL, "din must not overlap g or in");
     WgradPlan plan;
     conv_wgrad_plan(c->g, cin, cout, ~size_t(0) / 16, &plan);
-    c->net_part = grow<float>(c, c->net_part, c->net_part_n, plan.floats);
+    // (room for every number of channels at once where that is bounded: calls may have been captured)
+    grow(c, c->net_part, c->net_part_n, plan.mfma ? kWgradFloats : plan.floats);
     launch_conv_backward(c->g, in, cin, W, cout, g, dW, db, din, z_in, c->net_part, plan, c->stream);
     HIPCHECK(hipGetLastError());
     API_END

@@ -168,8 +168,8 @@ struct dfl_ctx {
     size_t net_part_n = 0;
     uint16_t* net_wbf = nullptr; // BF16 weights of the BF16 forward
     size_t net_wbf_n = 0;
-    uint16_t* net_xbf = nullptr; // and its input, site-major in BF16
-    size_t net_xbf_n = 0;
+    uint16_t* net_xbf = nullptr; // and its input, site-major in BF16 (kNetMaxCin channels)
+    bool net_no_xbf = false;     // there was no room for that
     dfl::c64* PhiT = nullptr;    // the basis in the transposed in-block order (assembly of the
     size_t PhiT_n = 0;           // face columns along x2 and x3)
     dfl::c64* loss_Y = nullptr;  // deficit loss: per-block G^-1 Psi^+ T
@@ -375,12 +375,15 @@ struct WgradPlan {
     size_t floats;
 };
 bool conv_wgrad_plan(const Geom& g, int cin, int cout, size_t cap, WgradPlan* p);
+// most floats of an mfma plan: 512 workgroups, each with nine taps of 32 x 64 or two partials of 32 x 32 channels
+constexpr size_t kWgradFloats = size_t(512) * 9 * 2048;
 // BF16-operand forward (FP32 sums) for lattices with L3 % 32 == 0 and L2 % 4 == 0
 // (conv_bf16_fits); Wb holds conv_bf16_weight_elems(cin, cout) BF16 entries,
-// Xb (the rounded input, site-major; may be null) conv_bf16_input_elems
+// Xb (the rounded input, site-major; may be null) conv_bf16_input_elems, enough
+// for any number of channels (0: not used on this lattice)
 bool conv_bf16_fits(const Geom& g);
 size_t conv_bf16_weight_elems(int cin, int cout);
-size_t conv_bf16_input_elems(const Geom& g, int cin, int cout);
+size_t conv_bf16_input_elems(const Geom& g);
 void launch_conv_forward_bf16(const Geom& g, const float* in, int cin, const float* W, const float* b, int cout,
                               float* z, float* a, uint16_t* Wb, uint16_t* Xb, hipStream_t s);
 void launch_conv_backward(const Geom& g, const float* in, int cin, const float* W, int cout, const float* gr,

@@ -1344,9 +1344,9 @@ size_t conv_bf16_weight_elems(int cin, int cout)
     return 81ul * (size_t)cinP * (size_t)coutP;
 }
 
-size_t conv_bf16_input_elems(const Geom& g, int cin, int cout)
+size_t conv_bf16_input_elems(const Geom& g)
 {
-    return bf16_tile_ns(g, cout) ? (size_t)((cin + kBK - 1) / kBK * kBK) * (size_t)g.V : 0;
+    return bf16_tile_ns(g, 1) ? (size_t)((kNetMaxCin + kBK - 1) / kBK * kBK) * (size_t)g.V : 0;
 }
 
 void launch_conv_forward_bf16(const Geom& g, const float* in, int cin, const float* W, const float* b, int cout,
