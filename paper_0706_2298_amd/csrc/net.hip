@@ -734,9 +734,10 @@ __global__ __launch_bounds__(384, 4) void k_conv_wgrad_mfma(Lat lt, const float*
         __syncthreads();
         const float* xb = xs + o2 * w3 * kCP + col;
         const float* gb = gs + (PAIR ? half * 32 : 0) + col;
-        const int k0 = (PAIR ? 0 : half * (kCT / 2)) + kh;  // first site of this lane
+        const int s0 = PAIR ? 0 : half * (kCT / 2), k0 = s0 + kh;  // first site of this lane
+        const int nk = min(NK, (tl.n - s0) / 2);  // (V, hence tl.n, is a multiple of 64)
 #pragma unroll 4
-        for (int k = 0; k < NK; ++k) {
+        for (int k = 0; k < nk; ++k) {
             const int i = k0 + 2 * k;
             const float* xp = xb + ptab[i];
             const float b = gb[i * GP];
