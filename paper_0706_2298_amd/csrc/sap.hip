@@ -8,9 +8,9 @@
 // belong to blocks of the other colour, which no workgroup of this launch
 // writes, so there is no race. Inside the MR loop the current residue r is
 // exchanged through LDS (12 planes x |block|), and the block reductions of a
-// step use DPP wavefront sums plus one LDS pass. Every kernel reads the links
-// once per sweep and keeps them on the chip for the MR steps (spare lanes of
-// the last wavefront only join the reductions):
+// step use DPP wavefront sums plus one LDS pass. Every kernel keeps the links on
+// the chip for the MR steps (spare lanes of the last wavefront only join the
+// reductions), the first three as the residue has read them:
 //   k_sap_rl    FP32, one lane per site
 //   k_sap_cl    the same with the clover term or antiperiodic time
 //   k_sap_pair  two lanes per site: FP64 blocks of up to 256 sites, and FP32
@@ -623,7 +623,7 @@ __global__ __launch_bounds__(B4 ? 256 : 512, 2) void k_sap_cl(Geom g, SapGeom sg
 // Both leave room for two wavefronts per SIMD, one block of 256 sites per CU.
 // FP64, 4^4 blocks: 20 fields on 16^4 360 us per sweep (links re-read at every
 // step: 579), one field on 8^4 29 us (61), with the clover term on 32 x 16^3
-// 58 us. The vector units are busy half of the time, the rest is the latency of
+// 55 us (138). The vector units are busy half of the time, the rest is the latency of
 // the LDS reads, barriers and first loads at two wavefronts per SIMD.
 
 // x + s*y, x + s*i*y and x - s*i*y with the lane's sign s
@@ -977,10 +977,6 @@ __global__ __launch_bounds__(512, 1) void k_sap_pair(Geom g, SapGeom sg, L U, co
     }
 }
 
-template <typename T, typename L>
-void launch(const Geom& g, const SapGeom& sg, L U, const cpx<T>* rho, const double* rho_nrm2, cpx<T>* psi, T m0,
-            int nmr, int colour, int nrhs, int init, c64* out64, hipStream_t s, const cpx<T>* clov);
-
 // o = f (dg + C(x)) p, the entries read nine at a time and the chirality blocks
 // one after the other (few live registers)
 template <typename T>
@@ -1274,9 +1270,9 @@ void launch_rl_kernel(const Geom& g, const SapGeom& sg, L U, const c32* rho, con
 // CU at two wavefronts per SIMD (16^4 and 32 x 16^3 with 4^4 blocks: 11% faster
 // than one lane per site). Several fields, one field with many blocks per
 // colour, or larger blocks: one lane per site, two blocks of up to 256 sites
-// per CU (16 fields on 16^4: 12% faster than the generic kernel at three blocks
-// per CU, which re-reads the links every MR step, and 28% faster than lane
-// pairs; one field on 64 x 32^3: 346 against 475 us per sweep with lane pairs).
+// per CU (16 fields on 16^4: 12% faster than three blocks per CU with the links
+// re-read at every MR step, and 28% faster than lane pairs; one field on 64 x
+// 32^3: 346 against 475 us per sweep with lane pairs).
 template <typename L, bool IMP>
 void launch_rl(const Geom& g, const SapGeom& sg, L U, const c32* rho, const double* rho_nrm2, c32* psi, float m0,
                int nmr, int colour, int nrhs, int init, c64* out64, hipStream_t s, const c32* clov)
@@ -1303,8 +1299,9 @@ void launch32(const Geom& g, const SapGeom& sg, L U, const c32* rho, const doubl
         launch_rl<L, false>(g, sg, U, rho, rho_nrm2, psi, m0, nmr, colour, nrhs, init, out64, s, clov);
 }
 
-// FP64: lane pairs for blocks of up to 256 sites, one lane per site and link
-// for larger ones.
+// FP64: lane pairs for blocks of up to 256 sites (55 us per sweep of one improved
+// field on 32 x 16^3, with one lane per site and links re-read 138). Pairs of
+// larger blocks would need twice a CU's registers: one lane per site and link.
 void launch64(const Geom& g, const SapGeom& sg, Links64 U, const c64* rho, c64* psi, double m0, int nmr, int colour,
               int nrhs, int init, hipStream_t s, const c64* clov)
 {
