@@ -174,13 +174,15 @@ template <typename L> __device__ inline su3<float> expand_lds(const Link2<L>& l,
 
 // B4: 4^4 blocks, whose extents, in-block strides and LDS plane size are
 // compile-time constants (every LDS access of a hop is then an immediate
-// offset from the thread's own address). BIG: blocks of 257..512 sites, one per
-// CU, the lanes' products summed in FP64.
-template <typename L, bool B4, bool BIG>
-__global__ __launch_bounds__(BIG ? 512 : 256, 2) void k_sap_rl(Geom g, SapGeom sg, L U, const c32* __restrict__ rho,
-                                                               const double* __restrict__ rho_nrm2,
-                                                               c32* __restrict__ psi, float diag, int nmr, int colour,
-                                                               int nrhs, int init, c64* __restrict__ out64)
+// offset from the thread's own address). WIDE: antiperiodic time, blocks of
+// 257..512 sites (one per CU); the lanes' products are summed in FP64, the block
+// hops by themselves.
+template <typename L, bool B4, bool WIDE>
+__global__ __launch_bounds__(WIDE && !B4 ? 512 : 256, 2) void k_sap_rl(Geom g, SapGeom sg, L U, const c32* __restrict__ rho,
+                                                                      const double* __restrict__ rho_nrm2,
+                                                                      c32* __restrict__ psi, float diag, int nmr,
+                                                                      int colour, int nrhs, int init,
+                                                                      c64* __restrict__ out64)
 {
     const int Vsb = B4 ? 256 : sg.Vsb;
     int sbl[4], lst[4];
@@ -256,6 +258,8 @@ __global__ __launch_bounds__(BIG ? 512 : 256, 2) void k_sap_rl(Geom g, SapGeom s
             const bool inside = step > 0 ? yl[mu] + 1 < sbl[mu] : yl[mu] > 0;
             if (init == 0 || (init == 1 && !inside)) {
                 spinor<float> p = load_spinor(psi, g.V, tn);
+                if (WIDE && mu == 0 && crosses_time(g, n, y, mu, step))
+                    negate(p);
                 if (step > 0)
                     hop_fwd_rt(mu, u, p, acc);
                 else
@@ -283,7 +287,7 @@ __global__ __launch_bounds__(BIG ? 512 : 256, 2) void k_sap_rl(Geom g, SapGeom s
                 for (int a = 0; a < 3; ++a)
                     lr[(3 * al + a) * Vsb + t] = r.s[al].c[a];
         }
-        // acc = -2 D_Lambda r: it starts at -2 diag r (BIG: ends with it, the hops are
+        // acc = -2 D_Lambda r: it starts at -2 diag r (WIDE: ends with it, the hops are
         // summed by themselves) and collects the inside hops, so the MR coefficient
         // follows from it without forming D_Lambda r
         spinor<float> acc;
@@ -297,11 +301,11 @@ __global__ __launch_bounds__(BIG ? 512 : 256, 2) void k_sap_rl(Geom g, SapGeom s
                     acc.s[al].c[a].im = fmadd(-2.0f * diag, r.s[al].c[a].im, acc.s[al].c[a].im);
                 }
         };
-        if (active && !BIG)
+        if (active && !WIDE)
             add_diag();
         __syncthreads();
         // the lane's products, then the block sums in FP64
-        using S = std::conditional_t<BIG, double, float>;
+        using S = std::conditional_t<WIDE, double, float>;
         S fr_re = 0, fr_im = 0, fqq = 0;
         if (active) {
 #pragma unroll
@@ -325,7 +329,7 @@ __global__ __launch_bounds__(BIG ? 512 : 256, 2) void k_sap_rl(Geom g, SapGeom s
                 if (h & 1)
                     asm volatile("" ::: "memory");
             }
-            if (BIG)
+            if (WIDE)
                 add_diag();
 #pragma unroll
             for (int al = 0; al < 4; ++al)
@@ -369,7 +373,7 @@ __global__ __launch_bounds__(BIG ? 512 : 256, 2) void k_sap_rl(Geom g, SapGeom s
     }
 }
 
-// The same for the clover term and antiperiodic time. Beside the links the 36
+// The same with the clover term. Beside the links the 36
 // clover entries of a site fit neither registers nor LDS, and re-reading them
 // at every MR step is paid in exposed latency (192 us per sweep of one field on
 // 48 x 24^3, 95 without the term). So the residue lives in LDS alone, the block
@@ -436,11 +440,10 @@ __global__ __launch_bounds__(B4 ? 256 : 512, 2) void k_sap_cl(Geom g, SapGeom sg
         }
         s = site_compose(g, n, y);
     }
-    const bool clv = C.c != nullptr;
     c32 cl[2][18 - kLC];
     // o += f C p at this site for the p with component (3 * spin + colour) p(c); C p
     // is summed by itself (o is the larger part)
-    auto site_clover = [&](float f, const auto& p, spinor<float>& o) {
+    auto site_clover = [&](int Vsb, float f, const auto& p, spinor<float>& o) {
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
             c32 e[18], v[6], w[6];
@@ -485,23 +488,21 @@ __global__ __launch_bounds__(B4 ? 256 : 512, 2) void k_sap_cl(Geom g, SapGeom sg
             if (h & 1)
                 asm volatile("" ::: "memory");  // two hops' loads in flight at a time
         }
-        if (clv) {
 #pragma unroll
-            for (int h = 0; h < 2; ++h)
+        for (int h = 0; h < 2; ++h)
 #pragma unroll
-                for (int q = 0; q < 18; ++q) {
-                    const c32 e = ld(C.c, toff<c32>(s, 18 * h + q, kCloverComp));
-                    if (q < kLC)
-                        lc[(kLC * h + q) * Vsb + t] = e;
-                    else
-                        cl[h][q < kLC ? 0 : q - kLC] = e;
-                }
-        }
+            for (int q = 0; q < 18; ++q) {
+                const c32 e = ld(C.c, toff<c32>(s, 18 * h + q, kCloverComp));
+                if (q < kLC)
+                    lc[(kLC * h + q) * Vsb + t] = e;
+                else
+                    cl[h][q < kLC ? 0 : q - kLC] = e;
+            }
         if (init == 0)
             self = load_spinor(psi, g.V, s);
         spinor<float> d = finish(self, acc, diag);
-        if (clv && init == 0)
-            site_clover(1.0f, [&](int c) { return self.s[c / 3].c[c % 3]; }, d);
+        if (init == 0)
+            site_clover(Vsb, 1.0f, [&](int c) { return self.s[c / 3].c[c % 3]; }, d);
         spinor<float> b = load_spinor(rho, g.V, s);
         if (rho_nrm2)
             scale_spinor(b, rs);
@@ -514,7 +515,12 @@ __global__ __launch_bounds__(B4 ? 256 : 512, 2) void k_sap_cl(Geom g, SapGeom sg
             }
     }
 
+    const int V0 = Vsb;
     for (int stp = 0; stp < nmr; ++stp) {
+        // (unknown to the compiler here: addresses are formed in the step, not kept over all of them)
+        int Vsb = V0;
+        if (!B4)
+            asm volatile("" : "+s"(Vsb));
         // acc = -2 D_Lambda r: the inside hops, then -2 (diag + C) r; the MR
         // coefficient follows from it without forming D_Lambda r
         spinor<float> acc;
@@ -553,8 +559,7 @@ __global__ __launch_bounds__(B4 ? 256 : 512, 2) void k_sap_cl(Geom g, SapGeom sg
                     acc.s[al].c[a].re = fmadd(-2.0f * diag, r.re, acc.s[al].c[a].re);
                     acc.s[al].c[a].im = fmadd(-2.0f * diag, r.im, acc.s[al].c[a].im);
                 }
-            if (clv)
-                site_clover(-2.0f, [&](int c) { return own[c * Vsb]; }, acc);
+            site_clover(Vsb, -2.0f, [&](int c) { return own[c * Vsb]; }, acc);
 #pragma unroll
             for (int al = 0; al < 4; ++al)
 #pragma unroll
@@ -732,7 +737,8 @@ template <typename L> __device__ inline auto pair_link(const L& U, int mu, long 
     return w;
 }
 
-// IMP: clover term (C.c non-null) and antiperiodic time
+// IMP: clover term (C.c non-null); FP32: or antiperiodic time, and the lanes'
+// products summed in FP64
 constexpr int kPC = 7;
 template <typename T, typename L, bool B4, bool IMP>
 __global__ __launch_bounds__(512, 1) void k_sap_pair(Geom g, SapGeom sg, L U, const cpx<T>* __restrict__ rho,
@@ -829,7 +835,7 @@ __global__ __launch_bounds__(512, 1) void k_sap_pair(Geom g, SapGeom sg, L U, co
                 lk[mu][q] = w.m[q / 3][q % 3];
             if (init == 0 || (init == 1 && !inside[mu])) {
                 spinor<T> p = load_spinor(psi, g.V, tn);
-                if (IMP && mu == 0 && crosses_time(g, n, y, mu, hb ? -1 : +1))
+                if ((F64 || IMP) && mu == 0 && crosses_time(g, n, y, mu, hb ? -1 : +1))
                     negate(p);
                 hop_pair_rt(mu, w, [&](int c) { return p.s[c / 3].c[c % 3]; }, sgn, acc);
             }
@@ -842,7 +848,7 @@ __global__ __launch_bounds__(512, 1) void k_sap_pair(Geom g, SapGeom sg, L U, co
     auto r_of = [&](int i) { return F64 ? lr[(c0 + i) * Vsb + ts] : rr[F64 ? 0 : i]; };
     // the lane's clover block
     cpx<T> cl[18];
-    const bool clv = IMP && C.c && active;
+    const bool clv = IMP && (F64 || C.c) && active;
     if (clv) {
         clover_load(C, s, hb, cl);
         if (F64)
@@ -1248,19 +1254,20 @@ void launch_pair(const Geom& g, const SapGeom& sg, L U, const cpx<T>* rho, const
         go(attr[1], &k_sap_pair<T, L, false, IMP>);
 }
 
-template <typename L, bool B4, bool IMP, bool BIG>
+// one lane per site: with the clover term (CLV), else k_sap_rl
+template <typename L, bool B4, bool CLV, bool WIDE>
 void launch_rl_kernel(const Geom& g, const SapGeom& sg, L U, const c32* rho, const double* rho_nrm2, c32* psi,
                       float m0, int nmr, int colour, int nrhs, int init, c64* out64, hipStream_t s, const c32* clov)
 {
     const dim3 grid(sg.n_per_colour * nrhs), threads(((sg.Vsb + 63) / 64) * 64);
     static std::once_flag attr;  // one per kernel instantiation
-    if constexpr (IMP) {
+    if constexpr (CLV) {
         set_max_lds_once(attr, reinterpret_cast<const void*>(&k_sap_cl<L, B4>), 160 * 1024 - 1024);
         hipLaunchKernelGGL((k_sap_cl<L, B4>), grid, threads, (size_t)(24 + 2 * kLC) * sg.Vsb * sizeof(c32), s, g, sg,
                            U, rho, rho_nrm2, psi, 4.0f + m0, nmr, colour, nrhs, init, out64, Clover<float>{clov});
     } else {
-        set_max_lds_once(attr, reinterpret_cast<const void*>(&k_sap_rl<L, B4, BIG>), 160 * 1024 - 1024);
-        hipLaunchKernelGGL((k_sap_rl<L, B4, BIG>), grid, threads, (size_t)36 * sg.Vsb * sizeof(c32), s, g, sg, U, rho,
+        set_max_lds_once(attr, reinterpret_cast<const void*>(&k_sap_rl<L, B4, WIDE>), 160 * 1024 - 1024);
+        hipLaunchKernelGGL((k_sap_rl<L, B4, WIDE>), grid, threads, (size_t)36 * sg.Vsb * sizeof(c32), s, g, sg, U, rho,
                            rho_nrm2, psi, 4.0f + m0, nmr, colour, nrhs, init, out64);
     }
 }
@@ -1273,30 +1280,20 @@ void launch_rl_kernel(const Geom& g, const SapGeom& sg, L U, const c32* rho, con
 // per CU (16 fields on 16^4: 12% faster than three blocks per CU with the links
 // re-read at every MR step, and 28% faster than lane pairs; one field on 64 x
 // 32^3: 346 against 475 us per sweep with lane pairs).
-template <typename L, bool IMP>
-void launch_rl(const Geom& g, const SapGeom& sg, L U, const c32* rho, const double* rho_nrm2, c32* psi, float m0,
-               int nmr, int colour, int nrhs, int init, c64* out64, hipStream_t s, const c32* clov)
-{
-    if (nrhs == 1 && !sg.one_rl && sg.Vsb <= 256)
-        launch_pair<float, L, IMP>(g, sg, U, rho, rho_nrm2, psi, m0, nmr, colour, nrhs, init, out64, s, clov);
-    else if (is_b4(sg))
-        launch_rl_kernel<L, true, IMP, false>(g, sg, U, rho, rho_nrm2, psi, m0, nmr, colour, nrhs, init, out64, s, clov);
-    else if (sg.Vsb <= 256)
-        launch_rl_kernel<L, false, IMP, false>(g, sg, U, rho, rho_nrm2, psi, m0, nmr, colour, nrhs, init, out64, s,
-                                               clov);
-    else
-        launch_rl_kernel<L, false, IMP, true>(g, sg, U, rho, rho_nrm2, psi, m0, nmr, colour, nrhs, init, out64, s,
-                                              clov);
-}
-
 template <typename L>
 void launch32(const Geom& g, const SapGeom& sg, L U, const c32* rho, const double* rho_nrm2, c32* psi, float m0,
               int nmr, int colour, int nrhs, int init, c64* out64, hipStream_t s, const c32* clov)
 {
-    if (clov || g.tsign < 0)
-        launch_rl<L, true>(g, sg, U, rho, rho_nrm2, psi, m0, nmr, colour, nrhs, init, out64, s, clov);
+    auto go = [&](auto launch) { launch(g, sg, U, rho, rho_nrm2, psi, m0, nmr, colour, nrhs, init, out64, s, clov); };
+    const bool b4 = is_b4(sg), anti = g.tsign < 0;
+    if (nrhs == 1 && !sg.one_rl && sg.Vsb <= 256)
+        clov || anti ? go(&launch_pair<float, L, true>) : go(&launch_pair<float, L, false>);
+    else if (clov)
+        b4 ? go(&launch_rl_kernel<L, true, true, true>) : go(&launch_rl_kernel<L, false, true, true>);
+    else if (anti || sg.Vsb > 256)
+        b4 ? go(&launch_rl_kernel<L, true, false, true>) : go(&launch_rl_kernel<L, false, false, true>);
     else
-        launch_rl<L, false>(g, sg, U, rho, rho_nrm2, psi, m0, nmr, colour, nrhs, init, out64, s, clov);
+        b4 ? go(&launch_rl_kernel<L, true, false, false>) : go(&launch_rl_kernel<L, false, false, false>);
 }
 
 // FP64: lane pairs for blocks of up to 256 sites (55 us per sweep of one improved
@@ -1306,7 +1303,7 @@ void launch64(const Geom& g, const SapGeom& sg, Links64 U, const c64* rho, c64* 
               int nrhs, int init, hipStream_t s, const c64* clov)
 {
     if (sg.Vsb <= 256) {
-        if (clov || g.tsign < 0)
+        if (clov)
             launch_pair<double, Links64, true>(g, sg, U, rho, nullptr, psi, m0, nmr, colour, nrhs, init, nullptr, s,
                                                clov);
         else
