@@ -16,6 +16,8 @@ namespace dfl {
 
 namespace {
 
+constexpr int kCO = 16;        // output channels per workgroup of the vector convolution
+constexpr int kCN = 8;         // its most input channels
 constexpr int kWT = 64;        // output channels per workgroup of the weight gradient
 constexpr int kWS = 64;        // sites per LDS tile of the weight gradient
 constexpr int kMaxCin = 96;
@@ -59,6 +61,80 @@ __device__ inline float silu_grad_f(float z)
 {
     const float s = 1.0f / (1.0f + __expf(-z));
     return s * (1.0f + z * (1.0f - s));
+}
+
+// out[oc][i] = bias[oc] + sum_t sum_ic Wt(t, ic, oc) in[ic][i + s o_t]
+//   forward (TRANS = false, s = +1): Wt(t, ic, oc) = W[t][ic][oc], nic = Cin
+//   input gradient (TRANS = true, s = -1): Wt(t, ic, oc) = W[t][oc][ic], nic = Cout of W
+// Epilogue: forward stores z and optionally a = silu(z); the input gradient
+// is optionally multiplied by silu'(zprev[oc][i]).
+// The vector kernel, for few input channels on many sites (launch_conv), where
+// the matrix-core kernel spends its time on staging 32 channels that are not there.
+template <bool TRANS>
+__global__ __launch_bounds__(256) void k_conv(Lat lt, const float* __restrict__ in, int nic,
+                                              const float* __restrict__ W, int w_cin, int w_cout,
+                                              const float* __restrict__ bias, int noc, float* __restrict__ out,
+                                              float* __restrict__ act, const float* __restrict__ zprev)
+{
+    __shared__ float4 ws[576 * kCO / 4];  // (with room for kCN channels only the channel loop compiles to a slower form)
+    const long V = lt.V;
+    const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
+    const int oc0 = blockIdx.y * kCO;
+    long dl[4][3];
+    if (i < V)
+        tap_shifts(lt, i, TRANS ? -1 : 1, dl);
+    float acc[kCO];
+#pragma unroll
+    for (int j = 0; j < kCO; ++j)
+        acc[j] = (bias && oc0 + j < noc) ? bias[oc0 + j] : 0.f;
+    float* wsf = reinterpret_cast<float*>(ws);
+    for (int t = 0; t < 81; ++t) {
+        __syncthreads();
+        for (int e = threadIdx.x; e < nic * kCO; e += blockDim.x) {
+            int ic, j;
+            if (TRANS) {
+                ic = e % nic;
+                j = e / nic;
+            } else {
+                ic = e / kCO;
+                j = e % kCO;
+            }
+            float w = 0.f;
+            if (oc0 + j < noc)
+                w = TRANS ? W[((long)t * w_cin + oc0 + j) * w_cout + ic] : W[((long)t * w_cin + ic) * w_cout + oc0 + j];
+            wsf[ic * kCO + j] = w;
+        }
+        __syncthreads();
+        if (i < V) {
+            const int o0 = t / 27, o1 = (t / 9) % 3, o2 = (t / 3) % 3, o3 = t % 3;
+            const long nb = i + dl[0][o0] + dl[1][o1] + dl[2][o2] + dl[3][o3];
+            const float* src = in + nb;
+            for (int ic = 0; ic < nic; ++ic) {
+                const float x = src[(long)ic * V];
+#pragma unroll
+                for (int q = 0; q < kCO / 4; ++q) {
+                    const float4 w = ws[ic * (kCO / 4) + q];
+                    acc[4 * q] += x * w.x;
+                    acc[4 * q + 1] += x * w.y;
+                    acc[4 * q + 2] += x * w.z;
+                    acc[4 * q + 3] += x * w.w;
+                }
+            }
+        }
+    }
+    if (i >= V)
+        return;
+#pragma unroll
+    for (int j = 0; j < kCO; ++j) {
+        if (oc0 + j >= noc)
+            continue;
+        float v = acc[j];
+        if (TRANS && zprev)
+            v *= silu_grad_f(zprev[(long)(oc0 + j) * V + i]);
+        out[(long)(oc0 + j) * V + i] = v;
+        if (!TRANS && act)
+            act[(long)(oc0 + j) * V + i] = silu_f(v);
+    }
 }
 
 // ------------------------------------------------------- staged site tiles
@@ -145,12 +221,7 @@ __device__ inline long src_site(const Lat& lt, const Src& r, int d0, int d1)
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-// out[oc][i] = bias[oc] + sum_t sum_ic Wt(t, ic, oc) in[ic][i + s o_t]
-//   forward (TRANS = false, s = +1): Wt(t, ic, oc) = W[t][ic][oc], nic = Cin
-//   input gradient (TRANS = true, s = -1): Wt(t, ic, oc) = W[t][oc][ic], nic = Cout of W
-// Epilogue: forward stores z and optionally a = silu(z); the input gradient
-// is optionally multiplied by silu'(zprev[oc][i]).
-// On the matrix cores (v_mfma_f32_32x32x2f32, FP32 products and sums), one GEMM
+// k_conv's map on the matrix cores (v_mfma_f32_32x32x2f32, FP32 products and sums), one GEMM
 // per tap: out[oc][x] += sum_ic Wt(t, ic, oc) in[ic][x + s o_t].
 // Workgroup: a tile of 128 sites and 32 OT output channels, wavefront w the
 // sites 32 w .. 32 w + 31 of all of them. For each (o0, o1) and each chunk of
@@ -1290,7 +1361,18 @@ void launch_conv(const Geom& g, const float* in, int nic, const float* W, int w_
         np = 3 * (lt.W3 + 2);
         ntiles = g.V / lt.L[3] * lt.nseg;
     }
-    const int ot = noc <= 32 ? 1 : 2;
+    // 64 output channels a workgroup, or 32 where that would leave CUs idle (4^3 x 32, 32 -> 96 channels: 133 us with
+    // 64, 73 with 32)
+    const long groups = (noc + 63) / 64;
+    const int ot = noc <= 32 || ntiles * groups < 256 ? 1 : 2;
+    // Few input channels and enough workgroups for every CU (more than two rounds of 32 output channels for five to
+    // eight channels): the vector kernel. 32 x 16^3, 1 -> 1 channels 47 us (matrix cores 94), 4 -> 16 64 (116), 8 -> 16
+    // 90 (118); 16^4, 1 -> 1 40 (51), 5 -> 40 86 (92), 8 -> 16 86 (57); 8^4, 1 -> 1 42 (39).
+    if ((nic <= 4 && ntiles * groups >= 256) || (nic <= kCN && ntiles * ((noc + 31) / 32) > 512)) {
+        hipLaunchKernelGGL(k_conv<TRANS>, dim3(site_blocks(g.V), (noc + kCO - 1) / kCO), dim3(256), 0, s, lt, in, nic,
+                           W, w_cin, w_cout, bias, noc, out, act, zprev);
+        return;
+    }
     const size_t lds = sizeof(float) * ((size_t)np * kCP + (size_t)3 * 32 * ot * kCP);
     const dim3 grid((unsigned)pad_grid(ntiles), (noc + 32 * ot - 1) / (32 * ot));
     static std::once_flag attr[2];  // per instantiation
