@@ -601,13 +601,15 @@ void little_solve_impl(dfl_ctx* c, const c64* w, c64* v, double tol, dfl_prec pr
     const long n = (long)c->g.Nb * c->p.Ns;
     const int Ns = c->p.Ns, nkv = c->p.little_nkv, mi = c->p.little_maxiter;
     const bool eo_multi = nb > 1 && c->eo_ok && little_eo_fits(c->g, c->lgrid_multi);
-    // Few blocks: one block pair per workgroup, lpair sources side by side. Launches of it follow one another,
-    // so many sources that take more than a few go to the batched kernel. MI355X, P_L of Ns = 20 and mixed-precision
-    // solves, pair against batched: 256 blocks (lpair 2), eight sources 2.5 against 3.1 ms and 44 against 45 ms,
-    // twelve 3.8 against 3.7 and 68 against 60; 384 and 512 blocks (lpair 1), three sources 2.1 and 2.2 ms against
-    // 2.7 and 3.1, four 2.7 and 2.8 against 2.9 and 3.3 but solves of four 46.8 against 44.7 and 51.9 against 51.6,
-    // sixteen (512 blocks) 10.8 against 5.2 and 197 against 130.
-    const bool pair = c->lpair > 0 && c->eo_ok && nb <= (c->lpair > 1 ? 4 : 3) * c->lpair;
+    // Few blocks: one block pair per workgroup, lpair sources side by side. Launches of it follow one another and
+    // take as long for few fields as for many, so many sources, or some of few fields, go to the batched kernel.
+    // MI355X, P_L and mixed-precision solves with Ns = 20, pair against batched: 256 blocks (lpair 2), eight sources
+    // 2.5 against 3.1 ms and 44 against 45 ms, twelve 3.8 against 3.7 and 68 against 60; 384 and 512 blocks (lpair 1),
+    // three sources 2.1 and 2.2 ms against 2.7 and 3.1, four 2.7 and 2.8 against 2.9 and 3.3 but solves of four 46.8
+    // against 44.7 and 51.9 against 51.6, sixteen (512 blocks) 10.8 against 5.2 and 197 against 130. P_L on 512 blocks
+    // with Ns = 13, three sources 0.68 against 0.66 ms, with Ns = 4, two 0.32 against 0.31 and three 0.46 against 0.36.
+    const int launches = Ns <= 8 ? 1 : Ns <= 16 ? 2 : c->lpair > 1 ? 4 : 3;
+    const bool pair = c->lpair > 0 && c->eo_ok && nb <= launches * c->lpair;
     if (prec == DFL_F64) {
         ProfScope ps(c, DFL_PROF_LITTLE);
         if (pair)
@@ -1363,7 +1365,7 @@ int dfl_create(dfl_ctx** out, const dfl_params* p, void* hip_stream)
         c->lt = alloc_dev<c64>(c, N);
         c->lw32 = alloc_dev<c32>(c, R * N);
         c->lx32 = alloc_dev<c32>(c, R * N);
-        c->lgrid = little_gcr_grid(c->g, p->little_grid, p->little_eo && p->Ns <= 32 && p->little_gdefl != 2);
+        c->lgrid = little_gcr_grid(c->g, p->little_grid, p->little_eo && p->little_gdefl != 2);
         c->lgrid_multi = little_gcr_multi_grid(c->g, p->little_grid);
         // every workgroup of the grid-barrier kernels must be resident at
         // once (graph replays launch them as ordinary kernels)

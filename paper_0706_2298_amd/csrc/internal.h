@@ -408,8 +408,8 @@ constexpr int kLossMaxN = 32;      // fields and targets of the deficit loss
 
 // ---------------------------------------------------------------- little.hip
 // workgroups of the little GCR: requested (0: Nb / 4, or Nb / 2 for up to 512 blocks with
-// `pair`: even-odd solves, Ns <= 32, no oblique deflation), clamped to 1..min(Nb / 2, kLittleMaxGrid)
-int little_gcr_grid(const Geom& g, int requested, bool pair);
+// `eo`: even-odd solves, no oblique deflation), clamped to 1..min(Nb / 2, kLittleMaxGrid)
+int little_gcr_grid(const Geom& g, int requested, bool eo);
 size_t little_gcr_partial_doubles(int grid_size);
 // workgroups of the batched little GCR: twice the requested single-source
 // grid (0: Nb / 4), at most one per compute unit and half the block count

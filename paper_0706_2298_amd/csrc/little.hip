@@ -2172,13 +2172,14 @@ void launch_impl(const Geom& g, int Ns, int nkv, int maxiter, double tol, const 
 // The barrier and reduction costs grow with the workgroup count, the apply's
 // bandwidth with it. Default four blocks per workgroup: with the even-odd
 // operator each apply covers two blocks, one round of the 512 threads for Ns
-// up to 32 (measured on 16^4 in this kernel: 64 workgroups beat 32, 48 and
-// 128). At most kLittleMaxGrid workgroups. Up to 512 blocks the kernel with one
-// block pair per workgroup takes the even-odd solves (pair): it has no cache
-// maintenance in its barriers and no memory access between them.
-int little_gcr_grid(const Geom& g, int requested, bool pair)
+// up to 32. At most kLittleMaxGrid workgroups. Even-odd solves of up to 512
+// blocks: one block pair per workgroup, which for Ns up to 32 the kernel with
+// the matrices in registers takes; beyond, in this kernel, 16^4 with Ns = 40
+// (256 blocks) 562 us a solve with 128 workgroups, 638 with 64; but oblique
+// deflation (Ns = 20) 560 and 544, and the plain operator 643 and 658.
+int little_gcr_grid(const Geom& g, int requested, bool eo)
 {
-    int G = requested > 0 ? requested : pair && g.Nb <= 2 * kLittleMaxGrid ? g.Nb / 2 : g.Nb / 4;
+    int G = requested > 0 ? requested : eo && g.Nb <= 2 * kLittleMaxGrid ? g.Nb / 2 : g.Nb / 4;
     if (G > kLittleMaxGrid)
         G = kLittleMaxGrid;
     if (G > g.Nb / 2)
