@@ -379,7 +379,7 @@ __global__ __launch_bounds__(WIDE && !B4 ? 512 : 256, 2) void k_sap_rl(Geom g, S
 // 48 x 24^3, 95 without the term). So the residue lives in LDS alone, the block
 // solution too, the third link rows are rebuilt for every use, and of every
 // chirality block's entries kLC are in LDS, the others in registers: one read
-// of everything per sweep, two blocks of 256 sites per CU: 144 us.
+// of everything per sweep, two blocks of 256 sites per CU: 145 us.
 constexpr int kLC = 5;  // LDS entries of a chirality block (of 18)
 template <typename L, bool B4>
 __global__ __launch_bounds__(B4 ? 256 : 512, 2) void k_sap_cl(Geom g, SapGeom sg, L U, const c32* __restrict__ rho,
